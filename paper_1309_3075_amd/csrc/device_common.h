@@ -68,4 +68,35 @@ __device__ inline double block_sum(double v, double* smem) {
   return r;
 }
 
+// Block partial sums of one launch added up inside it.  Every block of the launch (n_blocks of
+// them, one slot each) calls this with its sum on thread 0; the last one to arrive sums the slots
+// in order (the same order whichever block is last) and writes out[0], and host_out[0] when given.
+// A launch of its own for that sum took 1.7-4.8 us plus the gap before it.  `arrived` is 0 before
+// the launch and again after it; the slots and the counter go through device-scope atomics, since
+// blocks on different XCDs do not share an L2.
+template <int NT>
+__device__ inline void sum_blocks_in_last(double block_total, double* slots, int slot, int n_blocks,
+                                          unsigned* arrived, double* out, double* host_out, double* smem) {
+  __shared__ int last;
+  if (threadIdx.x == 0) {
+    __hip_atomic_store(&slots[slot], block_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // the slot is written through to device scope before the counter moves; a full release would
+    // also write back whatever else the XCD's L2 holds
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const unsigned before = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last = before + 1 == (unsigned)n_blocks;
+  }
+  __syncthreads();
+  if (!last) return;
+  double acc = 0.0;
+  for (int k = threadIdx.x; k < n_blocks; k += NT)
+    acc += __hip_atomic_load(&slots[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const double tot = block_sum<NT>(acc, smem);
+  if (threadIdx.x == 0) {
+    out[0] = tot;
+    if (host_out) host_out[0] = tot;
+    __hip_atomic_store(arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
 }  // namespace epochlik

@@ -168,10 +168,12 @@ int fastpath_post(EpochInstance* in) {
   return EPOCH_OK;
 }
 
-int fastpath_root(EpochInstance* in) {
+int fastpath_root(EpochInstance* in, double* host_logL, bool* delivered) {
   in->eval_gen++;  // new weights or root frequencies change the branch adjoints too
+  if (delivered) *delivered = host_logL && in->gen_nchunks == 1 && in->codon_nchunks == 1;
   if (!nuc(in) && !codon(in) && in->gen_nchunks > 1) return EPOCH_OK;  // formed with the chunks' partials
-  EPOCH_PHASE(2, nuc(in) ? launch_nuc_root(in) : (codon(in) ? launch_codon_root(in) : launch_root_generic(in)));
+  EPOCH_PHASE(2, nuc(in) ? launch_nuc_root(in, host_logL)
+                         : (codon(in) ? launch_codon_root(in, host_logL) : launch_root_generic(in, host_logL)));
   return EPOCH_OK;
 }
 

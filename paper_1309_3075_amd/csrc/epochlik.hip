@@ -169,6 +169,39 @@ int download(EpochInstance* in, void* dst, const void* src, size_t bytes) {
   return hip_check(hipStreamSynchronize(in->stream), "download sync");
 }
 
+// Results on their way to the host: the small ones through the instance's pinned buffer, written
+// by one launch (launch_publish), the large ones by a copy into the caller's memory.  The line lies
+// where the copy out of the pinned buffer costs what the direct copy's own staging does.
+constexpr size_t kPublishDoubles = 1 << 16;
+struct Delivery {
+  EpochInstance* in;
+  const double* src[4];
+  double* dst[4];
+  size_t n[4], at[4];
+  int count = 0;
+  size_t used = 1;  // entry 0 of the pinned buffer is logL
+  // doubles that hold every result an evaluation of this instance can publish
+  static size_t doubles(const EpochInstance* in) {
+    auto part = [](size_t n) { return n > kPublishDoubles ? 0 : n; };
+    return 2 + part(in->P) + part(in->n_nodes) + part((size_t)in->S * in->K * in->K);
+  }
+  int add(double* user, const void* device, size_t len) {
+    if (len > kPublishDoubles)
+      return hip_check(hipMemcpyAsync(user, device, len * sizeof(double), hipMemcpyDeviceToHost, in->stream), "download");
+    src[count] = static_cast<const double*>(device);
+    dst[count] = user;
+    n[count] = len;
+    at[count] = used;
+    used += len;
+    ++count;
+    return EPOCH_OK;
+  }
+  int launch() { return launch_publish(in, src, n, count, in->host_out + 1); }
+  void collect() const {  // after the stream's synchronisation
+    for (int k = 0; k < count; ++k) std::copy(in->host_out + at[k], in->host_out + at[k] + n[k], dst[k]);
+  }
+};
+
 bool all_finite(const double* x, size_t n) {
   for (size_t i = 0; i < n; ++i)
     if (!std::isfinite(x[i])) return false;
@@ -243,11 +276,15 @@ int stage_reserve(EpochInstance* in, size_t bytes) {
   if (in->stage_bytes >= bytes) return EPOCH_OK;
   if (in->stage_host) (void)hipHostFree(in->stage_host);
   in->stage_host = nullptr;
+  in->host_out = nullptr;
   in->stage_bytes = 0;
-  if (hipHostMalloc(&in->stage_host, bytes, hipHostMallocDefault) != hipSuccess) {
+  // the evaluation's results share the allocation (every evaluation needs an eigensystem first)
+  const size_t at = (bytes + 255) / 256 * 256;
+  if (hipHostMalloc(&in->stage_host, at + Delivery::doubles(in) * sizeof(double), hipHostMallocDefault) != hipSuccess) {
     in->stage_host = nullptr;
     return set_error(EPOCH_ERR_OOM, "pinned staging buffer of %zu bytes", bytes);
   }
+  in->host_out = reinterpret_cast<double*>(static_cast<char*>(in->stage_host) + at);
   in->stage_bytes = bytes;
   return EPOCH_OK;
 }
@@ -391,6 +428,7 @@ int epoch_create(const EpochConfig* cfg, EpochInstance** out) {
   }
   A(in->site, P * sizeof(double));
   A(in->blocksum, ((P + 63) / 64 + 1) * sizeof(double));
+  A(in->arrived, sizeof(unsigned));
   A(in->result, std::max<size_t>(8, std::max(in->codon_nchunks, in->gen_nchunks) + 1) * sizeof(double));
   if (grad) {
     A(in->Gpart, (size_t)in->n_chunks * n * C * KK * sizeof(double));
@@ -411,6 +449,7 @@ int epoch_create(const EpochConfig* cfg, EpochInstance** out) {
   if (rc == EPOCH_OK) rc = hip_check(hipMemsetAsync(in->eigTT.ptr, 0, in->eigTT.bytes, in->stream), "memset");
   if (rc == EPOCH_OK) rc = hip_check(hipMemsetAsync(in->eig64T.ptr, 0, in->eig64T.bytes, in->stream), "memset");
   if (rc == EPOCH_OK) rc = hip_check(hipMemsetAsync(in->amb.ptr, 0, in->amb.bytes, in->stream), "memset");
+  if (rc == EPOCH_OK) rc = hip_check(hipMemsetAsync(in->arrived.ptr, 0, in->arrived.bytes, in->stream), "memset");
   if (rc == EPOCH_OK) rc = hip_check(hipStreamSynchronize(in->stream), "create sync");
   if (rc != EPOCH_OK) {
     std::string keep = g_error;
@@ -474,7 +513,7 @@ int epoch_destroy(EpochInstance* in) {
                     &in->qseg, &in->qscratch, &in->chain_items, &in->chain_scratch, &in->dQ, &in->seglist, &in->gslots, &in->codon_dev, &in->codon_aux,
                     &in->eigTT, &in->eig64T, &in->qtau, &in->nuc_nodes, &in->walk_ops,
                     &in->walk_tcol, &in->walk_dpart, &in->walk_dummy, &in->walk_slots, &in->inc_dev, &in->tg_i,
-                    &in->tg_d, &in->amb})
+                    &in->tg_d, &in->amb, &in->arrived})
     release(*b);
   delete in;
   return EPOCH_OK;
@@ -965,22 +1004,20 @@ int epoch_evaluate(EpochInstance* in, uint32_t what, double* logL, double* site_
   if (!in->have_weights) return set_error(EPOCH_ERR_STATE, "epoch_set_pattern_weights has not been called");
   if (!in->have_pi) return set_error(EPOCH_ERR_STATE, "epoch_set_root_frequencies has not been called");
   in->P_valid = in->partials_valid = in->logL_valid = false;
+  Delivery out{in};
+  bool delivered = false;
   EPOCH_TRY(fastpath_pstage(in));
   EPOCH_TRY(fastpath_post(in));
-  EPOCH_TRY(fastpath_root(in));
+  EPOCH_TRY(fastpath_root(in, in->host_out, &delivered));
   if (gb || gq) EPOCH_TRY(fastpath_gradient(in, gq));
-  EPOCH_TRY(hip_check(hipMemcpyAsync(logL, in->result.ptr, sizeof(double), hipMemcpyDeviceToHost, in->stream),
-                      "logL download"));
-  if (site_logL)
-    EPOCH_TRY(hip_check(hipMemcpyAsync(site_logL, in->site.ptr, (size_t)in->P * sizeof(double),
-                                       hipMemcpyDeviceToHost, in->stream), "site download"));
-  if (gb)
-    EPOCH_TRY(hip_check(hipMemcpyAsync(d_branch, in->dbranch.ptr, (size_t)in->n_nodes * sizeof(double),
-                                       hipMemcpyDeviceToHost, in->stream), "gradient download"));
-  if (gq)
-    EPOCH_TRY(hip_check(hipMemcpyAsync(d_Q, in->dQ.ptr, (size_t)in->S * in->K * in->K * sizeof(double),
-                                       hipMemcpyDeviceToHost, in->stream), "gradient download"));
+  if (!delivered) EPOCH_TRY(out.add(logL, in->result.ptr, 1));
+  if (site_logL) EPOCH_TRY(out.add(site_logL, in->site.ptr, in->P));
+  if (gb) EPOCH_TRY(out.add(d_branch, in->dbranch.ptr, in->n_nodes));
+  if (gq) EPOCH_TRY(out.add(d_Q, in->dQ.ptr, (size_t)in->S * in->K * in->K));
+  EPOCH_TRY(out.launch());
   EPOCH_TRY(hip_check(hipStreamSynchronize(in->stream), "evaluation sync"));
+  if (delivered) *logL = in->host_out[0];
+  out.collect();
   in->P_valid = in->partials_valid = true;
   const int rc = classify_logL(in, *logL);
   if (rc == EPOCH_WARN_UNDERFLOW) {  // the gradient pass divided by zero site likelihoods

@@ -35,6 +35,7 @@ struct CodonProblem {
   double* dbranch;
   double* site;
   double* blocksum;
+  unsigned* arrived;       // blocks of the root launch that have delivered their share of logL
   double* result;
   const int32_t* left;
   const int32_t* right;
@@ -172,6 +173,7 @@ struct EpochInstance {
   epochlik::DevBuf pre;        // T [N-1][C][P][Kp]
   epochlik::DevBuf site;       // double [P]
   epochlik::DevBuf blocksum;   // double [ceil(P/256)+1]
+  epochlik::DevBuf arrived;    // uint32: blocks of the root launch that have delivered their share (0 between launches)
   epochlik::DevBuf result;     // double [4]
   epochlik::DevBuf Gpart;      // double [chunks][n][C][Kp][Kp]
   epochlik::DevBuf G;          // double [n][C][Kp][Kp]
@@ -233,6 +235,7 @@ struct EpochInstance {
   size_t stage_bytes = 0;
   hipEvent_t stage_event = nullptr;
   bool stage_pending = false;
+  double* host_out = nullptr;  // behind the staging area: the kernels write an evaluation's results here
   bool ev_pending[EPOCH_N_PHASES] = {};
   double phase_ms[EPOCH_N_PHASES] = {};
   int64_t phase_count[EPOCH_N_PHASES] = {};
@@ -289,18 +292,18 @@ int launch_grad_Q_mfma(EpochInstance* in);
 bool grad_Q_mfma_supported(const EpochInstance* in);
 int launch_grad_Q(EpochInstance* in);  // matrix-core kernels where they apply, else generic
 int launch_post_generic(EpochInstance* in);
-int launch_root_generic(EpochInstance* in);
+int launch_root_generic(EpochInstance* in, double* host_logL = nullptr);
 int launch_pre_generic(EpochInstance* in);
 int launch_grad_branch_generic(EpochInstance* in);
 int launch_grad_Q_generic(EpochInstance* in);
-int launch_final_sum(EpochInstance* in, int n_blocks);
+int launch_publish(EpochInstance* in, const double* const* src, const size_t* n, int count, double* host_dst);
 int launch_chunk_sum(EpochInstance* in, int n);  // result[0] = result[1] + ... + result[n], in order
 int launch_grad_reduce(EpochInstance* in, int n_chunks, const int32_t* chunks_per_node);
 
 // 4-state kernels (kernels_nuc.hip)
 int launch_nuc_post(EpochInstance* in);
 int launch_nuc_post_nodes(EpochInstance* in, const int32_t* d_nodes, const int32_t* level_off);
-int launch_nuc_root(EpochInstance* in);
+int launch_nuc_root(EpochInstance* in, double* host_logL = nullptr);
 int launch_nuc_pre_grad(EpochInstance* in);
 int nuc_slots(int P, int C, int rmin);
 void nuc_pre_order_nodes(const EpochInstance* in, std::vector<int32_t>& nodes, std::vector<int>& fuse);
@@ -319,7 +322,7 @@ int launch_walk_pre_grad(EpochInstance* in);
 // 64-state MFMA kernels (kernels_codon.hip)
 int launch_codon_post(EpochInstance* in);
 int launch_codon_post_schedule(EpochInstance* in, const CodonSchedule& sc, const int2* d_items);
-int launch_codon_root(EpochInstance* in);
+int launch_codon_root(EpochInstance* in, double* host_logL = nullptr);
 int launch_codon_pre_grad(EpochInstance* in);
 int codon_prepare(EpochInstance* in);
 CodonProblem codon_descriptor(const EpochInstance* in, int c, const int32_t* gslots, float* gpart);
@@ -327,7 +330,7 @@ constexpr size_t kCodonSlotBytes = 64 * 64 * sizeof(float);  // one FP32 64x64 p
 void codon_build_schedule(const std::vector<const EpochInstance*>& insts, int target_blocks, CodonSchedule& out,
                           std::vector<std::vector<int32_t>>& gslots);
 int codon_launch_post(const CodonSchedule& sc, const CodonProblem* d_probs, const int2* d_items, hipStream_t st);
-int codon_launch_root(const CodonSchedule& sc, const CodonProblem* d_probs, hipStream_t st);
+int codon_launch_root(const CodonSchedule& sc, const CodonProblem* d_probs, hipStream_t st, double* host_logL = nullptr);
 size_t codon_dpart_bytes(const CodonSchedule& sc);
 int codon_launch_pre_grad(const CodonSchedule& sc, const CodonProblem* d_probs, const int2* d_items,
                           const int2* d_reduce_items, double* dpart, hipStream_t st, bool accumulate, bool finish);

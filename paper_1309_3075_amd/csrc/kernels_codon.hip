@@ -238,42 +238,57 @@ __device__ inline float dmax(float a, float b) { return fmaxf(a, b); }
 __device__ inline double dmax(double a, double b) { return fmax(a, b); }
 
 // ---------------------------------------------------------------------------
-// Root: one thread per pattern, in FP64; block partial sums of w_p log L_p per
+// Root: sixteen lanes per pattern (each a 16- or 32-byte piece of the partial's row, so a
+// wavefront reads four whole rows at once), in FP64; block partial sums of w_p log L_p per
 // instance (blockIdx.y runs over descriptors; those of categories above 0 have
-// nothing to do).  One category: L_p = sum_i pi_i x_root(p, i) 2^E_p.  Several
+// nothing to do), added up by the instance's last block.  One thread per pattern, walking its
+// row alone, took 14 us on 10,000 codon patterns and 21 us on 2,003 patterns of four categories.  One category: L_p = sum_i pi_i x_root(p, i) 2^E_p.  Several
 // (text after Eq. 4, rate categories): each category c has its own scale
 // exponent E_c, so L_p = 2^Emax sum_c w_c l_c 2^(E_c - Emax) with
 // l_c = sum_i pi_i x_c(p, i); the pre-order pass of category c then weighs
 // pattern p by w_p w_c l_c 2^E_c / L_p (its posterior share), written to that
 // category's weightsT.
+constexpr int kRootPatterns = 64;  // patterns per block
 template <typename T, int NT>
-__global__ __launch_bounds__(256) void codon_root_kernel(const CodonProblem* __restrict__ probs) {
+__global__ __launch_bounds__(256) void codon_root_kernel(const CodonProblem* __restrict__ probs,
+                                                         double* __restrict__ host_logL) {
   EPOCH_DIMS(NT);
+  constexpr int PER = NT;                   // states per lane
+  constexpr int STEPS = kRootPatterns / 16;  // patterns per sixteen-lane group
   __shared__ double sm[256];
   const CodonProblem& pr = probs[blockIdx.y];
   if (pr.cat_index != 0) return;  // uniform
   const int P = pr.P, K = pr.K;
-  if ((int)blockIdx.x * 256 >= P) return;  // uniform
-  const int p = blockIdx.x * 256 + threadIdx.x;
+  const int n_blocks = (P + kRootPatterns - 1) / kRootPatterns;
+  if ((int)blockIdx.x >= n_blocks) return;  // uniform
+  const int grp = threadIdx.x >> 4, r = threadIdx.x & 15;
   const size_t slot = pr.root - pr.N;
+  double piv[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) piv[i] = PER * r + i < K ? pr.pi[PER * r + i] : 0.0;
+  // sum_i pi_i x(p, i) of one category on every lane of the group
+  auto pi_dot = [&](const CodonProblem& pc, int p) {
+    const T* x = reinterpret_cast<const T*>(pc.part) + (slot * P + p) * KP + PER * r;
+    double acc = 0.0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) acc += piv[i] * (double)x[i];
+    return row16_sum(acc);
+  };
   double contrib = 0.0;
-  if (p < P) {
+#pragma unroll
+  for (int k = 0; k < STEPS; ++k) {
+    const int p = blockIdx.x * kRootPatterns + 16 * k + grp;
+    const int pc = min(p, P - 1);
     double s;
     if (pr.n_cats == 1) {
-      double L = 0.0;
-      const T* x = reinterpret_cast<const T*>(pr.part) + (slot * P + p) * KP;
-      for (int i = 0; i < K; ++i) L += pr.pi[i] * (double)x[i];
-      s = log(L) + (double)pr.scales[slot * P + p] * kLn2;
+      s = log(pi_dot(pr, pc)) + (double)pr.scales[slot * P + pc] * kLn2;
     } else {
       double l[kMaxCategories];
       int e[kMaxCategories], emax = INT_MIN;
       for (int c = 0; c < pr.n_cats; ++c) {
-        const CodonProblem& pc = probs[blockIdx.y + c];
-        const T* x = reinterpret_cast<const T*>(pc.part) + (slot * P + p) * KP;
-        double acc = 0.0;
-        for (int i = 0; i < K; ++i) acc += pr.pi[i] * (double)x[i];
-        l[c] = pr.cat[kMaxCategories + c] * acc;
-        e[c] = pc.scales[slot * P + p];
+        const CodonProblem& q = probs[blockIdx.y + c];
+        l[c] = pr.cat[kMaxCategories + c] * pi_dot(q, pc);
+        e[c] = q.scales[slot * P + pc];
         if (l[c] > 0.0) emax = max(emax, e[c]);
       }
       double L = 0.0;
@@ -282,26 +297,17 @@ __global__ __launch_bounds__(256) void codon_root_kernel(const CodonProblem* __r
         L += l[c];
       }
       s = L > 0.0 ? log(L) + (double)emax * kLn2 : -INFINITY;
-      for (int c = 0; c < pr.n_cats; ++c)
-        reinterpret_cast<T*>(probs[blockIdx.y + c].weightsT)[p] = L > 0.0 ? (T)(pr.weights[p] * (l[c] / L)) : T(0);
+      if (p < P && r == 0)
+        for (int c = 0; c < pr.n_cats; ++c)
+          reinterpret_cast<T*>(probs[blockIdx.y + c].weightsT)[p] = L > 0.0 ? (T)(pr.weights[p] * (l[c] / L)) : T(0);
     }
-    pr.site[p] = s;
-    contrib = pr.weights[p] * s;
+    if (p < P && r == 0) {
+      pr.site[p] = s;
+      contrib += pr.weights[p] * s;
+    }
   }
   const double tot = block_sum<256>(contrib, sm);
-  if (threadIdx.x == 0) pr.blocksum[blockIdx.x] = tot;
-}
-
-// Ordered sum of each problem's block partial sums into its result[0].
-__global__ __launch_bounds__(256) void codon_final_kernel(const CodonProblem* __restrict__ probs) {
-  __shared__ double sm[256];
-  const CodonProblem& pr = probs[blockIdx.x];
-  if (pr.cat_index != 0) return;  // uniform
-  const int nb = (pr.P + 255) / 256;
-  double acc = 0.0;
-  for (int k = threadIdx.x; k < nb; k += 256) acc += pr.blocksum[k];
-  const double tot = block_sum<256>(acc, sm);
-  if (threadIdx.x == 0) pr.result[0] = tot;
+  sum_blocks_in_last<256>(tot, pr.blocksum, blockIdx.x, n_blocks, pr.arrived, pr.result, host_logL, sm);
 }
 
 // ---------------------------------------------------------------------------
@@ -980,6 +986,7 @@ CodonProblem codon_descriptor(const EpochInstance* in, int c, const int32_t* gsl
   d.dbranch = static_cast<double*>(in->dbranch.ptr);
   d.site = static_cast<double*>(in->site.ptr);
   d.blocksum = static_cast<double*>(in->blocksum.ptr);
+  d.arrived = static_cast<unsigned*>(in->arrived.ptr);
   d.result = static_cast<double*>(in->result.ptr);
   d.left = in->d_left;
   d.right = in->d_right;
@@ -1024,7 +1031,7 @@ void codon_build_schedule(const std::vector<const EpochInstance*>& insts, int ta
   for (auto* in : insts) {
     n_levels = std::max(n_levels, in->plan.n_levels);
     max_tiles = std::max(max_tiles, (codon_chunk_patterns(in) + TILE - 1) / TILE);
-    max_pblocks = std::max(max_pblocks, (codon_chunk_patterns(in) + 255) / 256);
+    max_pblocks = std::max(max_pblocks, (codon_chunk_patterns(in) + kRootPatterns - 1) / kRootPatterns);
   }
   gslots.assign(nd, {});
   out.slot_total.assign(nd, 0);
@@ -1108,8 +1115,9 @@ void pre_levels(const CodonSchedule& sc, const CodonProblem* d_probs, const int2
 }
 
 template <typename T, int NT>
-void root_launch(const CodonSchedule& sc, const CodonProblem* d_probs, hipStream_t st) {
-  hipLaunchKernelGGL((codon_root_kernel<T, NT>), dim3(sc.max_pattern_blocks, sc.n_problems), dim3(256), 0, st, d_probs);
+void root_launch(const CodonSchedule& sc, const CodonProblem* d_probs, hipStream_t st, double* host_logL) {
+  hipLaunchKernelGGL((codon_root_kernel<T, NT>), dim3(sc.max_pattern_blocks, sc.n_problems), dim3(256), 0, st, d_probs,
+                     host_logL);
 }
 
 template <typename T, int NT>
@@ -1144,9 +1152,8 @@ int codon_launch_post(const CodonSchedule& sc, const CodonProblem* d_probs, cons
   return hip_check(hipGetLastError(), "codon_post_level launch");
 }
 
-int codon_launch_root(const CodonSchedule& sc, const CodonProblem* d_probs, hipStream_t st) {
-  EPOCH_CODON_DISPATCH(sc, root_launch, sc, d_probs, st);
-  hipLaunchKernelGGL(codon_final_kernel, dim3(sc.n_problems), dim3(256), 0, st, d_probs);
+int codon_launch_root(const CodonSchedule& sc, const CodonProblem* d_probs, hipStream_t st, double* host_logL) {
+  EPOCH_CODON_DISPATCH(sc, root_launch, sc, d_probs, st, host_logL);
   return hip_check(hipGetLastError(), "codon_root launch");
 }
 
@@ -1244,9 +1251,9 @@ int launch_codon_post_schedule(EpochInstance* in, const CodonSchedule& sc, const
   return codon_launch_post(sc, dev_probs(in), d_items, in->stream);
 }
 
-int launch_codon_root(EpochInstance* in) {
+int launch_codon_root(EpochInstance* in, double* host_logL) {
   if (in->codon_nchunks > 1) return EPOCH_OK;  // formed with the chunks' partials
-  return codon_launch_root(in->codon_sched, dev_probs(in), in->stream);
+  return codon_launch_root(in->codon_sched, dev_probs(in), in->stream, host_logL);
 }
 
 // Pre-order pass and dlogL/dP.  In chunks, each chunk's partials are formed

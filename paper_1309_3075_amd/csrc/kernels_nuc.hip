@@ -18,6 +18,8 @@
 //                    dlogL/dP for the two child branches of each node.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "device_common.h"
 #include "instance.h"
 #include "nuc_common.h"
@@ -270,33 +272,37 @@ template <typename T, int CP>
 __global__ __launch_bounds__(256) void nuc_root_kernel(
     const V4<T>* __restrict__ rootp, const int32_t* __restrict__ scale_root, const double* __restrict__ pi,
     const double* __restrict__ cat, const double* __restrict__ weights, double* __restrict__ site,
-    double* __restrict__ block_out, int P, int C) {
-  __shared__ double sm[4];
+    double* __restrict__ block_out, unsigned* __restrict__ arrived, double* __restrict__ result,
+    double* __restrict__ host_logL, int P, int C) {
+  __shared__ double sm[256];
   constexpr int TPW = 64 / CP;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int cl = lane & (CP - 1);
   const bool cat_ok = cl < C;
   const int c = cat_ok ? cl : 0;
-  const int p = (blockIdx.x * 4 + wave) * TPW + lane / CP;
-  const int pc = p < P ? p : P - 1;
-  const V4<T> x = rootp[(size_t)c * P + pc];
-  double l = 0.0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) l += pi[i] * (double)x.v[i];
-  l = cat_ok ? cat[kMaxCategories + c] * l : 0.0;
-  const double L = group_sum_cp<CP>(l);
   double contrib = 0.0;
-  if (p < P && cl == 0) {
-    const double s = log(L) + (double)scale_root[p] * kLn2;
-    site[p] = s;
-    contrib = weights[p] * s;
+  for (int first = (blockIdx.x * 4 + wave) * TPW; first < P; first += gridDim.x * 4 * TPW) {
+    const int p = first + lane / CP;
+    const int pc = p < P ? p : P - 1;
+    const V4<T> x = rootp[(size_t)c * P + pc];
+    double l = 0.0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) l += pi[i] * (double)x.v[i];
+    l = cat_ok ? cat[kMaxCategories + c] * l : 0.0;
+    const double L = group_sum_cp<CP>(l);
+    if (p < P && cl == 0) {
+      const double s = log(L) + (double)scale_root[p] * kLn2;
+      site[p] = s;
+      contrib += weights[p] * s;
+    }
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) contrib += __shfl_xor(contrib, o, 64);
   if (lane == 0) sm[wave] = contrib;
   __syncthreads();
-  if (threadIdx.x == 0) block_out[blockIdx.x] = ((sm[0] + sm[1]) + sm[2]) + sm[3];
+  sum_blocks_in_last<256>(((sm[0] + sm[1]) + sm[2]) + sm[3], block_out, blockIdx.x, gridDim.x, arrived, result,
+                          host_logL, sm);
 }
 
 // ---------------------------------------------------------------------------
@@ -568,23 +574,22 @@ int post_dispatch_cp(EpochInstance* in, const int32_t* d_nodes, const int32_t* l
   return hip_check(hipGetLastError(), "nuc_post_level launch");
 }
 
+// Blocks of the root launch, at most: each adds its share through one atomic counter.
+constexpr int kRootBlocks = 256;
 template <typename T, int CP>
-int root_dispatch_cp(EpochInstance* in) {
-  const auto& pl = in->plan;
+int root_dispatch_cp(EpochInstance* in, double* host_logL) {
   constexpr int TPW = 64 / CP;
-  const int blocks = (in->P + 4 * TPW - 1) / (4 * TPW);
+  const int blocks = std::min((in->P + 4 * TPW - 1) / (4 * TPW), kRootBlocks);
   const V4<T>* part = static_cast<const V4<T>*>(in->partials.ptr);
   const int32_t* sc = static_cast<const int32_t*>(in->scales.ptr);
-  const size_t slot = in->root_slot;  // pl.root - N, or its compact slot under an HBM budget
-  (void)pl;
+  const size_t slot = in->root_slot;  // root - N, or its compact slot under an HBM budget
   hipLaunchKernelGGL((nuc_root_kernel<T, CP>), dim3(blocks), dim3(256), 0, in->stream,
                      part + slot * in->C * (size_t)in->P, sc + slot * (size_t)in->P,
                      static_cast<const double*>(in->pi.ptr), static_cast<const double*>(in->cat.ptr),
                      static_cast<const double*>(in->weights.ptr), static_cast<double*>(in->site.ptr),
-                     static_cast<double*>(in->blocksum.ptr), in->P, in->C);
-  int rc = hip_check(hipGetLastError(), "nuc_root launch");
-  if (rc) return rc;
-  return launch_final_sum(in, blocks);
+                     static_cast<double*>(in->blocksum.ptr), static_cast<unsigned*>(in->arrived.ptr),
+                     static_cast<double*>(in->result.ptr), host_logL, in->P, in->C);
+  return hip_check(hipGetLastError(), "nuc_root launch");
 }
 
 int pre_blocks(const EpochInstance* in, int n_l) {
@@ -707,12 +712,12 @@ int launch_nuc_post_nodes(EpochInstance* in, const int32_t* d_nodes, const int32
   }
 }
 
-int launch_nuc_root(EpochInstance* in) {
+int launch_nuc_root(EpochInstance* in, double* host_logL) {
   switch (cp_of(in->C)) {
-    case 1: return in->fp64 ? root_dispatch_cp<double, 1>(in) : root_dispatch_cp<float, 1>(in);
-    case 2: return in->fp64 ? root_dispatch_cp<double, 2>(in) : root_dispatch_cp<float, 2>(in);
-    case 4: return in->fp64 ? root_dispatch_cp<double, 4>(in) : root_dispatch_cp<float, 4>(in);
-    default: return in->fp64 ? root_dispatch_cp<double, 8>(in) : root_dispatch_cp<float, 8>(in);
+    case 1: return in->fp64 ? root_dispatch_cp<double, 1>(in, host_logL) : root_dispatch_cp<float, 1>(in, host_logL);
+    case 2: return in->fp64 ? root_dispatch_cp<double, 2>(in, host_logL) : root_dispatch_cp<float, 2>(in, host_logL);
+    case 4: return in->fp64 ? root_dispatch_cp<double, 4>(in, host_logL) : root_dispatch_cp<float, 4>(in, host_logL);
+    default: return in->fp64 ? root_dispatch_cp<double, 8>(in, host_logL) : root_dispatch_cp<float, 8>(in, host_logL);
   }
 }
 

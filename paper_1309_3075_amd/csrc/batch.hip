@@ -534,6 +534,13 @@ int epoch_batch_evaluate(EpochBatch* b, uint32_t what, double* logL) {
     if (rc) return rc;
     b->tuned = true;
   }
+  // a member's setters may have left copies or launches on its own stream
+  for (EpochInstance* in : b->insts)
+    if (in->async_pending) {
+      rc = hip_check(hipStreamSynchronize(in->stream), "batch member sync");
+      if (rc) return rc;
+      in->async_pending = false;
+    }
   rc = replay(b, what);
   if (rc) return rc;
   const size_t n = b->insts.size();

@@ -291,6 +291,15 @@ int stage_reserve(EpochInstance* in, size_t bytes) {
 
 }  // namespace
 
+int epochlik::stage_upload(EpochInstance* in, void* dst, const void* src, size_t bytes) {
+  EPOCH_TRY(stage_reserve(in, bytes));
+  memcpy(in->stage_host, src, bytes);
+  EPOCH_TRY(hip_check(hipMemcpyAsync(dst, in->stage_host, bytes, hipMemcpyHostToDevice, in->stream), "staged upload"));
+  EPOCH_TRY(hip_check(hipEventRecord(in->stage_event, in->stream), "staged upload event"));
+  in->stage_pending = in->async_pending = true;
+  return EPOCH_OK;
+}
+
 extern "C" {
 
 const char* epoch_last_error(void) { return g_error.c_str(); }
@@ -757,7 +766,7 @@ int set_epoch_eigensystems(EpochInstance* in, int32_t s, const double* V, const 
     return st.rc;
   }
   EPOCH_TRY(hip_check(hipEventRecord(in->stage_event, in->stream), "eigensystem upload event"));
-  in->stage_pending = true;
+  in->stage_pending = in->async_pending = true;
   in->have_eig[s] = 1;
   invalidate_downstream(in);
   int ret = EPOCH_OK;

@@ -10,7 +10,8 @@
 // alone).  The instance therefore remembers which branches changed since the
 // last complete post-order pass and re-forms exactly those matrices and the
 // partials on their paths to the root, as the usual level launches restricted
-// to the dirty nodes.  The root reduction always runs in full; the gradient
+// to the dirty nodes (4-state: a short list of nodes as one launch).  The root
+// reduction always runs in full; the gradient
 // passes, when requested, run in full over the updated partials.
 //
 // The restricted launches use the same kernels on the same inputs, so the
@@ -60,6 +61,20 @@ bool incremental_eligible(const EpochInstance* in) {
 }
 
 namespace {
+
+// A proposal's few rates travel in the launch's arguments: no upload, and nothing waits.
+struct RateArgs {
+  int n;
+  int32_t node[kInlineRates];
+  double rate[kInlineRates];
+};
+__global__ __launch_bounds__(kInlineRates) void set_rates_kernel(const RateArgs a, double* __restrict__ d_rate) {
+  const int k = threadIdx.x;
+  if (k >= a.n) return;
+  for (int j = k + 1; j < a.n; ++j)
+    if (a.node[j] == a.node[k]) return;  // a node listed twice keeps its last rate
+  d_rate[a.node[k]] = a.rate[k];
+}
 
 size_t align16(size_t b) { return (b + 15) / 16 * 16; }
 
@@ -116,12 +131,7 @@ int build_lists(EpochInstance* in) {
   if (!L.chain_items.empty()) memcpy(h.data() + L.off_chain, L.chain_items.data(), L.chain_items.size() * sizeof(int4));
   if (!L.post_nodes.empty()) memcpy(h.data() + L.off_post, L.post_nodes.data(), L.post_nodes.size() * sizeof(int32_t));
   if (!citems.empty()) memcpy(h.data() + L.off_codon, citems.data(), citems.size() * sizeof(int2));
-  if (bytes) {
-    rc = hip_check(hipMemcpyAsync(in->inc_dev.ptr, h.data(), bytes, hipMemcpyHostToDevice, in->stream),
-                   "incremental list upload");
-    if (!rc) rc = hip_check(hipStreamSynchronize(in->stream), "incremental list sync");  // h is a local copy
-  }
-  return rc;
+  return bytes ? stage_upload(in, in->inc_dev.ptr, h.data(), bytes) : EPOCH_OK;
 }
 
 }  // namespace
@@ -150,10 +160,23 @@ int launch_post_incremental(EpochInstance* in) {
   in->work_partials = formed;
   if (L.post_nodes.empty()) return EPOCH_OK;
   switch (in->path) {
-    case 1: return launch_nuc_post_nodes(in, d_post, L.post_level_off.data());
+    case 1: return launch_nuc_post_nodes(in, d_post, L.post_level_off.data(), L.post_nodes.data());
     case 2: return launch_codon_post_schedule(in, L.codon, reinterpret_cast<const int2*>(base + L.off_codon));
     default: return launch_post_generic_nodes(in, d_post, L.post_level_off.data());
   }
+}
+
+int launch_set_rates(EpochInstance* in, int n, const int32_t* nodes, const double* rates) {
+  RateArgs a{};
+  for (int k = 0; k < n; ++k) {
+    if (nodes[k] == in->plan.root) continue;
+    a.node[a.n] = nodes[k];
+    a.rate[a.n++] = rates[k];
+  }
+  if (a.n == 0) return EPOCH_OK;
+  in->async_pending = true;
+  hipLaunchKernelGGL(set_rates_kernel, dim3(1), dim3(kInlineRates), 0, in->stream, a, in->d_rate);
+  return hip_check(hipGetLastError(), "branch rate launch");
 }
 
 void incremental_done(EpochInstance* in) {
@@ -186,9 +209,9 @@ int epoch_set_branch_rates(EpochInstance* in, int32_t n, const int32_t* nodes, c
     in->plan.rate[v] = rates[k];
     in->dirty[v] = 1;
   }
-  int rc = hip_check(hipMemcpyAsync(in->d_rate, in->plan.rate.data(), in->plan.rate.size() * sizeof(double),
-                                    hipMemcpyHostToDevice, in->stream), "branch rate upload");
-  if (!rc) rc = hip_check(hipStreamSynchronize(in->stream), "branch rate sync");
+  const int rc = n <= kInlineRates ? launch_set_rates(in, n, nodes, rates)
+                                   : stage_upload(in, in->d_rate, in->plan.rate.data(),
+                                                  in->plan.rate.size() * sizeof(double));
   if (rc) return rc;
   in->P_valid = in->partials_valid = in->logL_valid = false;
   return EPOCH_OK;

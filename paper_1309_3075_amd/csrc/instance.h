@@ -235,6 +235,7 @@ struct EpochInstance {
   size_t stage_bytes = 0;
   hipEvent_t stage_event = nullptr;
   bool stage_pending = false;
+  bool async_pending = false;  // a setter's work may still be queued on the instance's stream
   double* host_out = nullptr;  // behind the staging area: the kernels write an evaluation's results here
   bool ev_pending[EPOCH_N_PHASES] = {};
   double phase_ms[EPOCH_N_PHASES] = {};
@@ -266,6 +267,11 @@ int hip_check(hipError_t e, const char* what);
 
 // grows a device buffer (contents not preserved); returns EPOCH_OK or an error code
 int ensure(DevBuf& b, size_t bytes);
+
+// copies host data to the device through the pinned staging buffer, on the instance's stream and
+// without waiting (src may be reused at once)
+int stage_upload(EpochInstance* in, void* dst, const void* src, size_t bytes);
+constexpr int kInlineRates = 64;  // branch rates epoch_set_branch_rates passes in a launch's arguments
 
 // kernel launchers (kernels_generic.hip); all return EPOCH_OK or an error code
 // FP64 eigensystem check (kernels_eigcheck.hip): d_out[0] receives the residual, scratch follows it
@@ -302,7 +308,8 @@ int launch_grad_reduce(EpochInstance* in, int n_chunks, const int32_t* chunks_pe
 
 // 4-state kernels (kernels_nuc.hip)
 int launch_nuc_post(EpochInstance* in);
-int launch_nuc_post_nodes(EpochInstance* in, const int32_t* d_nodes, const int32_t* level_off);
+int launch_nuc_post_nodes(EpochInstance* in, const int32_t* d_nodes, const int32_t* level_off, const int32_t* h_nodes);
+int launch_set_rates(EpochInstance* in, int n, const int32_t* nodes, const double* rates);  // n <= kInlineRates
 int launch_nuc_root(EpochInstance* in, double* host_logL = nullptr);
 int launch_nuc_pre_grad(EpochInstance* in);
 int nuc_slots(int P, int C, int rmin);

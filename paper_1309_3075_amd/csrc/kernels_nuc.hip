@@ -19,6 +19,8 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <utility>
+#include <vector>
 
 #include "device_common.h"
 #include "instance.h"
@@ -181,6 +183,21 @@ __device__ inline int kind_of(int v, int N, const int32_t* __restrict__ left, co
   return (left[v] < N && right[v] < N) ? kCherry : kInternal;
 }
 
+// M x with its multiply-adds written out, so that the two post-order kernels round a node alike:
+// terms in the order 1, 0, 2, 3, or (FIRST0) 0, 1, 2, 3 for the first of two stored children.
+template <bool FIRST0, typename T>
+__device__ inline V4<T> matvec_post(const M4<T>& M, const V4<T>& x) {
+  constexpr int p = FIRST0 ? 0 : 1;
+  V4<T> y;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    T s = mul_add(M.m[4 * i + 1 - p], x.v[1 - p], M.m[4 * i + p] * x.v[p]);
+    s = mul_add(M.m[4 * i + 2], x.v[2], s);
+    y.v[i] = mul_add(M.m[4 * i + 3], x.v[3], s);
+  }
+  return y;
+}
+
 // ---------------------------------------------------------------------------
 template <typename T, int CP, int KA, int KB>
 __device__ inline void post_tiles(const NucCtx<T>& x, int u, int a, int b, int first, int R, const M4<T>& Pa,
@@ -210,8 +227,8 @@ __device__ inline void post_tiles(const NucCtx<T>& x, int u, int a, int b, int f
     V4<T> xb = child_vec<T, KB>(cb, x, 2);
     const int sa = child_normalise<CP, T, KA>(xa, ca, x.cat_ok);
     const int sb = child_normalise<CP, T, KB>(xb, cb, x.cat_ok);
-    const V4<T> va = matvec(Pa, xa);
-    const V4<T> vb = matvec(Pb, xb);
+    const V4<T> va = matvec_post<KA == kInternal && KB == kInternal>(Pa, xa);
+    const V4<T> vb = matvec_post<false>(Pb, xb);
     V4<T> y;
 #pragma unroll
     for (int i = 0; i < 4; ++i) y.v[i] = va.v[i] * vb.v[i];
@@ -265,6 +282,174 @@ __global__ __launch_bounds__(256) void nuc_post_level_kernel(
   EPOCH_POST_CASE(kInternal, kCherry);
   EPOCH_POST_CASE(kCherry, kCherry);
 #undef EPOCH_POST_CASE
+}
+
+// ---------------------------------------------------------------------------
+// Post-order of a short list of nodes in one launch.  Felsenstein's recursion never mixes patterns
+// (Eq. 4), so a wavefront can carry its tile of patterns through the whole list without waiting for
+// any other: what it reads of another listed node it wrote itself.  The nodes above one changed
+// branch, or a small tree, are a chain of levels with one or a few nodes each, where a launch per
+// level costs 5 us plus the gap before the next one however little it computes.  Here a block
+// stages the matrices of kListChunk nodes at a time in LDS, the child partials and tip states are
+// loaded kListAhead nodes ahead, and a child that is the node just formed stays in registers.  The
+// arithmetic is post_tiles', term by term, so both give the same bits.
+struct ListOp {
+  int u, a, b;
+  int kinds;  // child kinds of a (bits 0-1) and b (bits 2-3), a <= b; bits 4 / 5: a / b is the node
+              // before; bits 6 / 7: a / b is a node so recent that it is read when it is needed
+};
+constexpr int kListOps = 224;   // operations carried in the kernel's arguments
+constexpr int kListAhead = 4;   // nodes between a load and its use
+constexpr int kListSlots = 6;   // matrices of a node: its two children's, and both tips' of each cherry child
+struct ListOps {
+  int n, chunk;
+  ListOp op[kListOps];
+};
+
+template <typename T>
+struct ListCtx {
+  int N, P, C, c;
+  bool cat_ok;
+  const uint8_t* tips;
+  const int32_t* left;
+  const int32_t* right;
+  V4<T>* part;  // the listed nodes' partials and exponents are read and written through the same pointers
+  int32_t* scales;
+};
+
+template <typename T>
+struct ListLoads {
+  V4<T> xa, xb;
+  int sa, sb;  // scale exponent of a stored child, the state of a tip, or those of a cherry's tips (8 bits each)
+};
+
+template <typename T>
+__device__ inline void list_stored(V4<T>& xv, int& sc, const ListCtx<T>& x, int child, int pc) {
+  xv = x.part[((size_t)(child - x.N) * x.C + x.c) * x.P + pc];
+  sc = x.scales[(size_t)(child - x.N) * x.P + pc];
+}
+template <typename T>
+__device__ inline void list_load(V4<T>& xv, int& st, const ListCtx<T>& x, int child, int kind, bool later, int pc) {
+  if (kind == kTip)
+    st = x.tips[(size_t)child * x.P + pc];
+  else if (kind == kCherry)
+    st = x.tips[(size_t)x.left[child] * x.P + pc] | (x.tips[(size_t)x.right[child] * x.P + pc] << 8);
+  else if (!later)
+    list_stored(xv, st, x, child, pc);
+}
+
+// A tip branch's matrix column for a state set, summed as stage_cherry_tips sums it.
+template <typename T>
+__device__ inline V4<T> set_column(const M4<T>& m, int set) {
+  V4<T> col;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const T m0 = (set & 1) ? m.m[4 * i] : T(0), m1 = (set & 2) ? m.m[4 * i + 1] : T(0);
+    const T m2 = (set & 4) ? m.m[4 * i + 2] : T(0), m3 = (set & 8) ? m.m[4 * i + 3] : T(0);
+    col.v[i] = (m0 + m1) + (m2 + m3);
+  }
+  return col;
+}
+
+// Child vector and its scale exponent (post_tiles: child_vec, child_normalise); tipm: the LDS
+// matrices of a cherry's two tips.
+template <int CP, typename T>
+__device__ inline int list_child(V4<T>& v, const ListCtx<T>& x, int child, int kind, bool kept, bool late,
+                                 const V4<T>& loaded, int st, const T* tipm, int stride, const V4<T>& last, int last_sc,
+                                 int pc) {
+  if (kind == kTip) {
+    v = onehot<T>(st);
+    return 0;
+  }
+  if (kind == kInternal) {
+    v = kept ? last : loaded;
+    int sc = kept ? last_sc : st;
+    if (late) list_stored(v, sc, x, child, pc);
+    return sc;
+  }
+  const V4<T> s1 = set_column(load_matrix(tipm), st & 255), s2 = set_column(load_matrix(tipm + stride), st >> 8);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v.v[i] = s1.v[i] * s2.v[i];
+  const int e = scale_exponent(group_max_cp<CP>(x.cat_ok ? max4(v) : T(0)));
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v.v[i] = scale_by_pow2(v.v[i], e);
+  return e;
+}
+
+template <typename T, int CP>
+__global__ __launch_bounds__(256) void nuc_post_list_kernel(const ListOps ops, const int32_t* __restrict__ left,
+                                                            const int32_t* __restrict__ right,
+                                                            const T* __restrict__ Pm, const uint8_t* __restrict__ tips,
+                                                            V4<T>* part, int32_t* scales, int N, int P, int C) {
+  constexpr int TPW = 64 / CP;
+  extern __shared__ __align__(16) unsigned char list_lds[];
+  T* const sM = reinterpret_cast<T*>(list_lds);  // [chunk][kListSlots][C][16]
+  const int stride = C * 16;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int cl = lane & (CP - 1);
+  const bool cat_ok = cl < C;
+  const int c = cat_ok ? cl : 0;
+  const int p = (blockIdx.x * 4 + wave) * TPW + lane / CP, pc = p < P ? p : P - 1;
+  const ListCtx<T> x{N, P, C, c, cat_ok, tips, left, right, part, scales};
+  V4<T> last{};
+  int last_sc = 0;
+  auto load = [&](ListLoads<T>& ld, const ListOp& op) {
+    list_load(ld.xa, ld.sa, x, op.a, op.kinds & 3, op.kinds & (16 | 64), pc);
+    list_load(ld.xb, ld.sb, x, op.b, (op.kinds >> 2) & 3, op.kinds & (32 | 128), pc);
+  };
+  auto step = [&](const ListOp& op, const ListLoads<T>& ld, const T* m) {
+    m += c * 16;
+    const int ka = op.kinds & 3, kb = (op.kinds >> 2) & 3;
+    V4<T> xa, xb;
+    const int sa = list_child<CP, T>(xa, x, op.a, ka, op.kinds & 16, op.kinds & 64, ld.xa, ld.sa, m + 2 * stride, stride,
+                                     last, last_sc, pc);
+    const int sb = list_child<CP, T>(xb, x, op.b, kb, op.kinds & 32, op.kinds & 128, ld.xb, ld.sb, m + 4 * stride,
+                                     stride, last, last_sc, pc);
+    const M4<T> Pa = load_matrix(m), Pb = load_matrix(m + stride);
+    const V4<T> va = ka == kInternal && kb == kInternal ? matvec_post<true>(Pa, xa) : matvec_post<false>(Pa, xa);
+    const V4<T> vb = matvec_post<false>(Pb, xb);
+    V4<T> y;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) y.v[i] = va.v[i] * vb.v[i];
+    const int e = scale_exponent(group_max_cp<CP>(cat_ok ? max4(y) : T(0)));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) y.v[i] = scale_by_pow2(y.v[i], e);
+    last = y;
+    last_sc = e + sa + sb;
+    if (p < P && cat_ok) {
+      part[((size_t)(op.u - N) * C + c) * P + p] = y;
+      if (cl == 0) scales[(size_t)(op.u - N) * P + p] = last_sc;
+    }
+  };
+  ListLoads<T> ld[kListAhead];
+#pragma unroll
+  for (int s = 0; s < kListAhead; ++s)
+    if (s < ops.n) load(ld[s], ops.op[s]);
+  for (int base = 0; base < ops.n; base += ops.chunk) {
+    const int end = min(ops.n, base + ops.chunk);
+    __syncthreads();  // the previous chunk's matrices are no longer read
+    for (int t = threadIdx.x; t < (end - base) * kListSlots * C * 4; t += 256) {
+      const int o = t / (kListSlots * C * 4), r = t % (kListSlots * C * 4);
+      const int slot = r / (C * 4);
+      const ListOp& op = ops.op[base + o];
+      int v = slot == 0 ? op.a : op.b;
+      if (slot >= 2) {
+        const int owner = slot < 4 ? op.a : op.b;
+        if (((slot < 4 ? op.kinds : op.kinds >> 2) & 3) != kCherry) continue;
+        v = (slot & 1) ? right[owner] : left[owner];
+      }
+      reinterpret_cast<V4<T>*>(sM)[t] = reinterpret_cast<const V4<T>*>(Pm + (size_t)v * stride)[r % (C * 4)];
+    }
+    __syncthreads();
+    for (int i = base; i < end; i += kListAhead) {  // the chunk is a multiple of kListAhead
+#pragma unroll
+      for (int s = 0; s < kListAhead; ++s) {
+        if (i + s >= end) break;
+        step(ops.op[i + s], ld[s], sM + (size_t)(i + s - base) * kListSlots * stride);
+        if (i + s + kListAhead < ops.n) load(ld[s], ops.op[i + s + kListAhead]);
+      }
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -551,10 +736,93 @@ int tiles_per_wave(int tiles, int n_l, int r_min, int r_max, long target_waves) 
   return (int)R;
 }
 
+// Whether n nodes on `levels` tree levels are formed faster by one launch over the list than by a
+// launch per level.  Model in microseconds, from timings of whole trees and of the paths above one
+// branch (16 to 190 taxa, 100 to 100,000 patterns, 4 categories): a level launch costs 5.5 plus 0.49
+// per MB of a node's vectors; a node of the list costs a wavefront 1.1 (FP32) or 1.3 (FP64), and
+// 0.65 or 1.25 times the wavefronts per SIMD once they share its arithmetic units.  Measured,
+// levels against list: FP32 16 taxa x 1,000 patterns 52 -> 39 us, 48 x 20,011 108 -> 72, 190 x 1,000
+// 99 -> 175; FP64 100 x 20,011 206 -> 139, 190 x 5,003 164 -> 218.
+bool list_serves(const EpochInstance* in, int n, int levels) {
+  const int TPW = 64 / cp_of(in->C);
+  const double waves = (in->P + TPW - 1) / TPW, simds = 1024.0;
+  const double mb = (double)in->C * in->P * 4 * in->real_size * 1e-6;
+  const double list = n * std::max(in->fp64 ? 1.3 : 1.1, (in->fp64 ? 1.25 : 0.65) * waves / simds);
+  return 1.15 * list < 5.5 * levels + 0.49 * mb * n;
+}
+
+// The listed nodes as one launch's operations, ordered so that a node soon follows its children;
+// false where a launch per level is the better form.
+bool list_ops(const EpochInstance* in, const int32_t* nodes, const int32_t* level_off, ListOps& out) {
+  const auto& pl = in->plan;
+  const int N = in->N, lowest = pl.n_levels == 1 ? 1 : 2;
+  int n = 0, levels = 0;
+  for (int l = lowest; l <= pl.n_levels; ++l) {
+    n += level_off[l + 1] - level_off[l];
+    levels += level_off[l + 1] > level_off[l] ? 1 : 0;
+  }
+  if (n == 0 || n > kListOps || !list_serves(in, n, levels)) return false;
+  std::vector<uint8_t> todo(in->n_nodes, 0);
+  for (int l = lowest; l <= pl.n_levels; ++l)
+    for (int k = level_off[l]; k < level_off[l + 1]; ++k) todo[nodes[k]] = 1;
+  // depth first from each listed node that has no listed parent (the root of the tree, as the
+  // ancestors of a listed node are listed too), a listed child last
+  out.n = 0;
+  std::vector<std::pair<int, int>> stack;     // node, state
+  std::vector<int> at(in->n_nodes, -1 << 20);  // place of each node in the list
+  for (int l = pl.n_levels; l >= lowest; --l)
+    for (int k = level_off[l]; k < level_off[l + 1]; ++k) {
+      if (!todo[nodes[k]]) continue;
+      stack.assign(1, {nodes[k], 0});
+      while (!stack.empty()) {
+        const int u = stack.back().first, state = stack.back().second++;
+        const int a = pl.left[u], b = pl.right[u];
+        if (state < 2) {
+          const int child = state == 0 ? a : b;
+          if (todo[child]) stack.push_back({child, 0});
+          continue;
+        }
+        stack.pop_back();
+        todo[u] = 0;
+        auto kind = [&](int v) { return v < N ? kTip : (pl.left[v] < N && pl.right[v] < N ? kCherry : kInternal); };
+        int x = a, y = b, kx = kind(a), ky = kind(b);
+        if (kx > ky) {
+          std::swap(x, y);
+          std::swap(kx, ky);
+        }
+        auto when = [&](int v, int bit) {  // a load is issued kListAhead nodes before its use
+          const int back = out.n - at[v];
+          return back == 1 ? bit : (back < kListAhead ? bit << 2 : 0);
+        };
+        out.op[out.n] = ListOp{u, x, y, kx | ky << 2 | when(x, 16) | when(y, 32)};
+        at[u] = out.n++;
+      }
+    }
+  // about 40 KB of matrices at a time, so that four blocks share a compute unit
+  const int per_op = kListSlots * in->C * 16 * (int)in->real_size;
+  out.chunk = std::max(kListAhead, 40 * 1024 / per_op / kListAhead * kListAhead);
+  return true;
+}
+
 template <typename T, int CP>
-int post_dispatch_cp(EpochInstance* in, const int32_t* d_nodes, const int32_t* level_off) {
+int post_list_launch(EpochInstance* in, const ListOps& ops) {
+  constexpr int TPW = 64 / CP;
+  const int tiles = (in->P + TPW - 1) / TPW;
+  const size_t per_op = (size_t)kListSlots * in->C * 16 * sizeof(T);
+  hipLaunchKernelGGL((nuc_post_list_kernel<T, CP>), dim3((tiles + 3) / 4), dim3(256),
+                     std::min(ops.chunk, ops.n) * per_op, in->stream, ops, in->d_left,
+                     in->d_right, static_cast<const T*>(in->Pm.ptr), static_cast<const uint8_t*>(in->tips.ptr),
+                     static_cast<V4<T>*>(in->partials.ptr), static_cast<int32_t*>(in->scales.ptr), in->N, in->P,
+                     in->C);
+  return hip_check(hipGetLastError(), "nuc_post_list launch");
+}
+
+template <typename T, int CP>
+int post_dispatch_cp(EpochInstance* in, const int32_t* d_nodes, const int32_t* level_off, const int32_t* h_nodes) {
   const auto& pl = in->plan;
   constexpr int TPW = 64 / CP;
+  ListOps ops;
+  if (list_ops(in, h_nodes, level_off, ops)) return post_list_launch<T, CP>(in, ops);
   const int tiles = (in->P + TPW - 1) / TPW;
   const T* Pm = static_cast<const T*>(in->Pm.ptr);
   const uint8_t* tips = static_cast<const uint8_t*>(in->tips.ptr);
@@ -698,17 +966,17 @@ void nuc_pre_order_nodes(const EpochInstance* in, std::vector<int32_t>& nodes, s
 }
 
 int launch_nuc_post(EpochInstance* in) {
-  return launch_nuc_post_nodes(in, in->d_level_nodes, in->plan.level_offset.data());
+  return launch_nuc_post_nodes(in, in->d_level_nodes, in->plan.level_offset.data(), in->plan.level_nodes.data());
 }
 
 // Level l's nodes are d_nodes[level_off[l] .. level_off[l + 1]): the plan's level lists, or a
-// restricted list of the same layout (incremental re-evaluation).
-int launch_nuc_post_nodes(EpochInstance* in, const int32_t* d_nodes, const int32_t* level_off) {
+// restricted list of the same layout (incremental re-evaluation); h_nodes is the host's copy.
+int launch_nuc_post_nodes(EpochInstance* in, const int32_t* d_nodes, const int32_t* level_off, const int32_t* h_nodes) {
   switch (cp_of(in->C)) {
-    case 1: return in->fp64 ? post_dispatch_cp<double, 1>(in, d_nodes, level_off) : post_dispatch_cp<float, 1>(in, d_nodes, level_off);
-    case 2: return in->fp64 ? post_dispatch_cp<double, 2>(in, d_nodes, level_off) : post_dispatch_cp<float, 2>(in, d_nodes, level_off);
-    case 4: return in->fp64 ? post_dispatch_cp<double, 4>(in, d_nodes, level_off) : post_dispatch_cp<float, 4>(in, d_nodes, level_off);
-    default: return in->fp64 ? post_dispatch_cp<double, 8>(in, d_nodes, level_off) : post_dispatch_cp<float, 8>(in, d_nodes, level_off);
+    case 1: return in->fp64 ? post_dispatch_cp<double, 1>(in, d_nodes, level_off, h_nodes) : post_dispatch_cp<float, 1>(in, d_nodes, level_off, h_nodes);
+    case 2: return in->fp64 ? post_dispatch_cp<double, 2>(in, d_nodes, level_off, h_nodes) : post_dispatch_cp<float, 2>(in, d_nodes, level_off, h_nodes);
+    case 4: return in->fp64 ? post_dispatch_cp<double, 4>(in, d_nodes, level_off, h_nodes) : post_dispatch_cp<float, 4>(in, d_nodes, level_off, h_nodes);
+    default: return in->fp64 ? post_dispatch_cp<double, 8>(in, d_nodes, level_off, h_nodes) : post_dispatch_cp<float, 8>(in, d_nodes, level_off, h_nodes);
   }
 }
 

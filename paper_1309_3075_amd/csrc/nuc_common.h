@@ -43,6 +43,9 @@ __device__ inline V4<T> onehot(int mask) {
   return r;
 }
 
+__device__ inline float mul_add(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ inline double mul_add(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 template <typename T>
 __device__ inline V4<T> matvec(const M4<T>& M, const V4<T>& x) {
   V4<T> y;

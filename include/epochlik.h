@@ -384,8 +384,8 @@ typedef struct EpochBatch EpochBatch;
 int epoch_batch_create(EpochInstance* const* insts, int32_t n, const char* tune_cache_path, EpochBatch** out);
 
 /* Evaluate every member: logL: host [n] out.  what: EPOCH_EVAL_* bits (logL
- * is always computed).  Gradients stay on the device; read them with
- * epoch_batch_gradients.  Synchronises the batch's own stream.  As for one
+ * is always computed).  Read the gradients with epoch_batch_gradients (dlogL/dl
+ * comes to the host with logL, dlogL/dQ stays on the device until then).  Synchronises the batch's own stream.  As for one
  * instance (root_log_likelihood): a member whose logL is -inf makes the call
  * return EPOCH_WARN_UNDERFLOW (every logL written) and has no gradient; a NaN
  * or +inf logL returns EPOCH_ERR_NUMERIC. */

@@ -27,6 +27,14 @@
 
 using namespace epochlik;
 
+// Where one member's results lie on the device, and its gradient's place in the batch's host buffer.
+struct MemberResults {
+  const double* logL;
+  const double* dbranch;
+  int n_nodes;
+  int64_t offset;
+};
+
 struct EpochBatch {
   std::vector<EpochInstance*> insts;
   hipStream_t stream = nullptr;
@@ -39,7 +47,18 @@ struct EpochBatch {
   std::vector<DevBuf> gslots;  // per member
   DevBuf gpart;                // dlogL/dP slot partials of every member
   DevBuf dpart;                // per-chunk shares of dlogL/dl
-  DevBuf results;              // double [n]
+  DevBuf results;              // MemberResults [n]
+  double* host = nullptr;      // pinned: logL [n], then every member's dlogL/dl
+  bool host_grad = false;      // the last evaluation wrote the gradients there
+  std::vector<uint64_t> evaluated;  // each member's eval_gen after the last evaluation of this batch
+  std::vector<int64_t> grad_at;     // offset of each member's gradient in host
+  // members that run the FP32 tree walk: one launch per step for each group that can share it
+  struct WalkGroup {
+    std::vector<size_t> members;
+    WalkBatch walk;
+  };
+  std::vector<WalkGroup> walks;
+  std::vector<size_t> others;  // the members outside those groups
   // P-stage groups: members sharing Kp, precision, eigen arithmetic and gradient flag run in one launch
   struct PGroup {
     std::vector<size_t> members;
@@ -66,9 +85,14 @@ namespace {
 
 constexpr uint32_t kLogL = 1u, kGradBranch = 2u, kGradQ = 4u;
 
-__global__ __launch_bounds__(64) void gather_results(const double* const* __restrict__ src, int n,
-                                                     double* __restrict__ dst) {
-  for (int i = threadIdx.x; i < n; i += 64) dst[i] = *src[i];
+// Every member's logL, and with `grad` its dlogL/dl, into the batch's pinned host buffer (one block
+// per member).  Read one member at a time, 64 gradients cost 1.4 ms of copies that each wait.
+__global__ __launch_bounds__(256) void gather_results(const MemberResults* __restrict__ src, int grad,
+                                                      double* __restrict__ dst) {
+  const MemberResults m = src[blockIdx.x];
+  if (threadIdx.x == 0) dst[blockIdx.x] = *m.logL;
+  if (grad && m.dbranch)
+    for (int i = threadIdx.x; i < m.n_nodes; i += 256) dst[m.offset + i] = m.dbranch[i];
 }
 
 uint64_t member_signature(const EpochInstance* in) {
@@ -213,9 +237,50 @@ int fork_join(EpochBatch* b, const std::vector<size_t>& qs, F fn) {
   return rc;
 }
 
+// Group the members that share the launches of the FP32 tree walk (two or more of one kind).
+int build_walk_groups(EpochBatch* b) {
+  for (auto& g : b->walks) release_buf(g.walk.dev);
+  b->walks.clear();
+  b->others.clear();
+  std::vector<int> keys;
+  std::vector<std::vector<size_t>> members;
+  for (size_t q = 0; q < b->insts.size(); ++q) {
+    if (!walk_batch_member(b->insts[q])) continue;
+    const int k = walk_batch_key(b->insts[q]);
+    const size_t g = std::find(keys.begin(), keys.end(), k) - keys.begin();
+    if (g == keys.size()) {
+      keys.push_back(k);
+      members.emplace_back();
+    }
+    members[g].push_back(q);
+  }
+  std::vector<bool> grouped(b->insts.size(), false);
+  for (auto& m : members) {
+    if (m.size() < 2) continue;
+    b->walks.emplace_back();
+    b->walks.back().members = m;
+    std::vector<EpochInstance*> in;
+    for (size_t q : m) {
+      in.push_back(b->insts[q]);
+      grouped[q] = true;
+    }
+    const int rc = walk_batch_build(in, b->walks.back().walk);
+    if (rc) return rc;
+  }
+  for (size_t q = 0; q < b->insts.size(); ++q)
+    if (!grouped[q]) b->others.push_back(q);
+  return EPOCH_OK;
+}
+
 // Enqueue one evaluation of every member on b->stream (no host synchronisation).
-int enqueue(EpochBatch* b, uint32_t what, const double* const* d_result_ptrs) {
+int enqueue(EpochBatch* b, uint32_t what) {
   const size_t n = b->insts.size();
+  const bool gather_grad = (what & kGradBranch) != 0;
+  auto gather = [&] {
+    hipLaunchKernelGGL(gather_results, dim3((unsigned)n), dim3(256), 0, b->stream,
+                       static_cast<const MemberResults*>(b->results.ptr), gather_grad ? 1 : 0, b->host);
+    return hip_check(hipGetLastError(), "batch gather launch");
+  };
   for (const auto& g : b->pgroups) {
     int rc = launch_pstage_mfma_multi(b->insts[g.members[0]], static_cast<const PStageDesc*>(b->pdescs.ptr) + g.desc_offset,
                                       (int)g.members.size(), g.max_items, b->stream);
@@ -228,9 +293,17 @@ int enqueue(EpochBatch* b, uint32_t what, const double* const* d_result_ptrs) {
     // on one branch, the members spread over the branches
     std::vector<bool> single(n, false);
     for (size_t q : b->p_single) single[q] = true;
-    std::vector<size_t> all(n);
-    for (size_t q = 0; q < n; ++q) all[q] = q;
-    int rc = fork_join(b, all, [&](size_t q) {
+    std::vector<size_t> own = b->others;  // dlogL/dQ follows the level kernels' adjoints
+    if (what & kGradQ) {
+      own.resize(n);
+      for (size_t q = 0; q < n; ++q) own[q] = q;
+    } else {
+      for (const auto& g : b->walks) {
+        const int r = walk_batch_launch(g.walk, grad, b->stream);
+        if (r) return r;
+      }
+    }
+    int rc = fork_join(b, own, [&](size_t q) {
       EpochInstance* in = b->insts[q];
       int r = single[q] ? launch_pstage(in) : EPOCH_OK;
       if (!r && single[q]) r = fastpath_after_pstage(in);
@@ -240,9 +313,7 @@ int enqueue(EpochBatch* b, uint32_t what, const double* const* d_result_ptrs) {
       return r;
     });
     if (rc) return rc;
-    hipLaunchKernelGGL(gather_results, dim3(1), dim3(64), 0, b->stream, d_result_ptrs, (int)n,
-                       static_cast<double*>(b->results.ptr));
-    return hip_check(hipGetLastError(), "batch gather launch");
+    return gather();
   }
   {
     int rc = fork_join(b, b->p_single, [&](size_t q) {
@@ -275,9 +346,7 @@ int enqueue(EpochBatch* b, uint32_t what, const double* const* d_result_ptrs) {
     int rc = fork_join(b, all, [&](size_t q) { return launch_grad_Q(b->insts[q]); });
     if (rc) return rc;
   }
-  hipLaunchKernelGGL(gather_results, dim3(1), dim3(64), 0, b->stream, d_result_ptrs, (int)n,
-                     static_cast<double*>(b->results.ptr));
-  return hip_check(hipGetLastError(), "batch gather launch");
+  return gather();
 }
 
 int check_members(EpochBatch* b, uint32_t what) {
@@ -297,13 +366,24 @@ int check_members(EpochBatch* b, uint32_t what) {
 
 int capture(EpochBatch* b, uint32_t what) {
   const size_t n = b->insts.size();
-  // pointers to every member's result[0], kept after the results array
-  int rc = ensure(b->results, n * sizeof(double) + n * sizeof(double*));
+  int rc = ensure(b->results, n * sizeof(MemberResults));
   if (rc) return rc;
-  std::vector<const double*> ptrs(n);
-  for (size_t q = 0; q < n; ++q) ptrs[q] = static_cast<const double*>(b->insts[q]->result.ptr);
-  const double** d_ptrs = reinterpret_cast<const double**>(static_cast<char*>(b->results.ptr) + n * sizeof(double));
-  rc = hip_check(hipMemcpy(d_ptrs, ptrs.data(), n * sizeof(double*), hipMemcpyHostToDevice), "batch pointers");
+  std::vector<MemberResults> res(n);
+  b->grad_at.resize(n);
+  int64_t at = (int64_t)n;
+  for (size_t q = 0; q < n; ++q) {
+    const EpochInstance* in = b->insts[q];
+    b->grad_at[q] = at;
+    res[q] = MemberResults{static_cast<const double*>(in->result.ptr), static_cast<const double*>(in->dbranch.ptr),
+                           in->n_nodes, at};
+    at += in->n_nodes;
+  }
+  if (!b->host && hipHostMalloc(reinterpret_cast<void**>(&b->host), at * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    b->host = nullptr;
+    (void)hipGetLastError();
+    return set_error(EPOCH_ERR_OOM, "pinned batch results of %lld values", (long long)at);
+  }
+  rc = hip_check(hipMemcpy(b->results.ptr, res.data(), n * sizeof(MemberResults), hipMemcpyHostToDevice), "batch pointers");
   if (rc) return rc;
   // members launch on the batch stream while captured, without phase timing
   std::vector<hipStream_t> saved(n);
@@ -318,7 +398,7 @@ int capture(EpochBatch* b, uint32_t what) {
   if (rc) return rc;
   rc = hip_check(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal), "begin capture");
   if (!rc) {
-    int erc = enqueue(b, what, d_ptrs);
+    int erc = enqueue(b, what);
     hipGraph_t g = nullptr;
     int crc = hip_check(hipStreamEndCapture(b->stream, &g), "end capture");
     rc = erc ? erc : crc;
@@ -345,6 +425,9 @@ int replay(EpochBatch* b, uint32_t what) {
     if (rc) return rc;
     if (b->merged) {
       rc = build_schedule(b);
+      if (rc) return rc;
+    } else {
+      rc = build_walk_groups(b);
       if (rc) return rc;
     }
     b->signature = sig;
@@ -544,11 +627,15 @@ int epoch_batch_evaluate(EpochBatch* b, uint32_t what, double* logL) {
   rc = replay(b, what);
   if (rc) return rc;
   const size_t n = b->insts.size();
-  rc = hip_check(hipMemcpyAsync(logL, b->results.ptr, n * sizeof(double), hipMemcpyDeviceToHost, b->stream), "batch logL");
-  if (!rc) rc = hip_check(hipStreamSynchronize(b->stream), "batch sync");
+  rc = hip_check(hipStreamSynchronize(b->stream), "batch sync");
   if (rc) return rc;
+  std::copy(b->host, b->host + n, logL);
+  b->host_grad = (what & kGradBranch) != 0;
+  b->evaluated.resize(n);
   for (size_t q = 0; q < n; ++q) {
     EpochInstance* in = b->insts[q];
+    b->evaluated[q] = ++in->eval_gen;
+    if (what & (kGradBranch | kGradQ)) in->G_gen = in->eval_gen;  // formed in the same replay
     mark_dirty_all(in);  // the graph's launches are not tracked: the member's next single evaluation is full
     in->P_valid = in->partials_valid = true;
     const bool under = logL[q] == -std::numeric_limits<double>::infinity();
@@ -577,6 +664,12 @@ int epoch_batch_gradients(EpochBatch* b, int32_t i, double* d_branch, double* d_
   if (d_branch && !in->grad_ready) return set_error(EPOCH_ERR_STATE, "the last batch evaluation had no gradient");
   if (d_Q && !in->gradQ_ready) return set_error(EPOCH_ERR_STATE, "the last batch evaluation had no dlogL/dQ");
   int rc = EPOCH_OK;
+  // already on the host, unless something else evaluated the member since
+  if (d_branch && b->host_grad && b->evaluated[i] == in->eval_gen) {
+    std::copy(b->host + b->grad_at[i], b->host + b->grad_at[i] + in->n_nodes, d_branch);
+    if (!d_Q) return EPOCH_OK;
+    d_branch = nullptr;
+  }
   if (d_branch)
     rc = hip_check(hipMemcpyAsync(d_branch, in->dbranch.ptr, (size_t)in->n_nodes * sizeof(double), hipMemcpyDeviceToHost,
                                   b->stream), "batch gradient copy");
@@ -607,6 +700,8 @@ int epoch_batch_destroy(EpochBatch* b) {
   release_buf(b->dpart);
   release_buf(b->pdescs);
   release_buf(b->results);
+  for (auto& g : b->walks) release_buf(g.walk.dev);
+  if (b->host) (void)hipHostFree(b->host);
   for (auto& g : b->gslots) release_buf(g);
   for (int k = 0; k < EpochBatch::kBatchBranches; ++k) {
     if (b->branch[k]) (void)hipStreamDestroy(b->branch[k]);

@@ -73,6 +73,39 @@ struct PStageDesc {
   bool grad;
 };
 
+// Operands of the generic P stage (one instance, or one member of a batch).
+struct PStageGenericArgs {
+  int n_nodes;  // branches formed: all, or the length of node_list
+  const int32_t* node_list;
+  int Kp, C;
+  const void *V, *Vi, *lr, *li;  // eigensystems in the reconstruction's arithmetic
+  const int32_t *seg_offset, *seg_process;
+  const double *seg_time, *seg_frac, *rate, *cat_rates;
+  void *Pout, *dPout;
+  void* PTout;  // or null: the transposed matrices (4-state FP32 tree walk)
+};
+
+// Operands of the 4-state root reduction.
+struct NucRootArgs {
+  const void* rootp;
+  const int32_t* scale_root;
+  const double *pi, *cat, *weights;
+  double *site, *blocksum;
+  unsigned* arrived;
+  double *result, *host_logL;
+  int P, C;
+};
+
+// One launch per step for the FP32 tree walks of many instances (the members of a batch that share
+// the categories' lane group, tiles per wavefront, reconstruction arithmetic and gradient flag).
+struct WalkBatch {
+  DevBuf dev;  // PStageGenericArgs, NucRootArgs, and the walk's operands for each pass, [n] each
+  size_t off_root = 0, off_post = 0, off_pre = 0;
+  int n = 0, cp = 0, nt = 1;
+  bool wide = false, grad = false;
+  int max_items = 0, max_patterns = 0, max_groups = 0, max_nodes = 0, post_slots = 1, pre_slots = 1;
+};
+
 // Merged level schedule: work items (problem, internal node) grouped by level.
 struct CodonSchedule {
   std::vector<int2> items;         // level l (1-based) occupies [level_off[l-1], level_off[l])
@@ -287,6 +320,11 @@ int launch_eigen_check_n(hipStream_t st, int K, int n, int ld, long mat_stride, 
 int launch_pstage_generic(EpochInstance* in);
 int launch_pstage_generic_nodes(EpochInstance* in, const int32_t* d_nodes, int n);  // listed branches only
 int launch_post_generic_nodes(EpochInstance* in, const int32_t* d_nodes, const int32_t* level_off);
+PStageGenericArgs pstage_generic_args(const EpochInstance* in, const int32_t* d_nodes, int n_list);
+int launch_pstage_generic_multi(const PStageGenericArgs* d_args, int n, int max_items, bool wide, bool grad,
+                                hipStream_t st);
+NucRootArgs nuc_root_args(const EpochInstance* in);
+int launch_nuc_root_multi(const NucRootArgs* d_args, int n, int max_patterns, int cp, hipStream_t st);
 int launch_pstage_mfma_items(EpochInstance* in, const int4* d_items, int n_items);  // whole chains listed
 int launch_pstage_mfma(EpochInstance* in);
 bool pstage_mfma_supported(const EpochInstance* in);
@@ -322,6 +360,11 @@ int walk_prepare(EpochInstance* in);  // builds and uploads the programs (walk_o
 int walk_tiles(const EpochInstance* in);
 size_t walk_tcol_bytes(const EpochInstance* in);
 size_t walk_dpart_rows_bytes(const EpochInstance* in);
+// the walks of many instances in one launch per step (batches)
+bool walk_batch_member(const EpochInstance* in);
+int walk_batch_key(const EpochInstance* in);  // instances of one key may share the launches
+int walk_batch_build(const std::vector<EpochInstance*>& members, WalkBatch& out);
+int walk_batch_launch(const WalkBatch& b, bool grad, hipStream_t st);
 int launch_walk_tipcol(EpochInstance* in);
 int launch_walk_post(EpochInstance* in);
 int launch_walk_pre_grad(EpochInstance* in);

@@ -27,13 +27,22 @@ namespace {
 // share a block; otherwise one item per block and EPT elements per thread.
 // ---------------------------------------------------------------------------
 template <typename T, typename TO, bool GRAD, int EPT>
-__global__ __launch_bounds__(256) void pstage_generic_kernel(
-    int n_nodes, const int32_t* __restrict__ node_list, int Kp, int C, const T* __restrict__ eigV,
-    const T* __restrict__ eigVi,
-    const T* __restrict__ lre, const T* __restrict__ lim, const int32_t* __restrict__ seg_offset,
-    const int32_t* __restrict__ seg_process, const double* __restrict__ seg_time,
-    const double* __restrict__ seg_frac, const double* __restrict__ rate,
-    const double* __restrict__ cat_rates, TO* __restrict__ Pout, TO* __restrict__ dPout) {
+__device__ inline void pstage_generic_block(const PStageGenericArgs& A) {
+  const int n_nodes = A.n_nodes, Kp = A.Kp, C = A.C;
+  const int32_t* __restrict__ node_list = A.node_list;
+  const T* __restrict__ eigV = static_cast<const T*>(A.V);
+  const T* __restrict__ eigVi = static_cast<const T*>(A.Vi);
+  const T* __restrict__ lre = static_cast<const T*>(A.lr);
+  const T* __restrict__ lim = static_cast<const T*>(A.li);
+  const int32_t* __restrict__ seg_offset = A.seg_offset;
+  const int32_t* __restrict__ seg_process = A.seg_process;
+  const double* __restrict__ seg_time = A.seg_time;
+  const double* __restrict__ seg_frac = A.seg_frac;
+  const double* __restrict__ rate = A.rate;
+  const double* __restrict__ cat_rates = A.cat_rates;
+  TO* __restrict__ Pout = static_cast<TO*>(A.Pout);
+  TO* __restrict__ dPout = static_cast<TO*>(A.dPout);
+  TO* __restrict__ PTout = static_cast<TO*>(A.PTout);
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int KK = Kp * Kp;
   const int ipb = (EPT == 1) ? max(1, 256 / KK) : 1;
@@ -160,7 +169,20 @@ __global__ __launch_bounds__(256) void pstage_generic_kernel(
     if (eok[e]) {
       Pout[base + idx[e]] = TO(sX[idx[e]]);
       if (GRAD) dPout[base + idx[e]] = TO(sD[idx[e]]);
+      if (EPT == 1 && PTout) PTout[base + (idx[e] % Kp) * Kp + idx[e] / Kp] = TO(sX[idx[e]]);
     }
+}
+template <typename T, typename TO, bool GRAD, int EPT>
+__global__ __launch_bounds__(256) void pstage_generic_kernel(const PStageGenericArgs A) {
+  pstage_generic_block<T, TO, GRAD, EPT>(A);
+}
+// One launch for many instances (blockIdx.y), all of the same padded state count (Kp^2 <= 256).
+template <typename T, typename TO, bool GRAD>
+__global__ __launch_bounds__(256) void pstage_generic_multi_kernel(const PStageGenericArgs* __restrict__ args) {
+  const PStageGenericArgs A = args[blockIdx.y];
+  const int ipb = 256 / (A.Kp * A.Kp);
+  if ((int)blockIdx.x * ipb >= A.n_nodes * A.C) return;  // uniform
+  pstage_generic_block<T, TO, GRAD, 1>(A);
 }
 
 // ---------------------------------------------------------------------------
@@ -547,26 +569,15 @@ int lanes_per_pattern(int Kp) {
 // of the transition matrices handed to pruning.
 template <typename T, typename TO>
 int pstage_dispatch(EpochInstance* in, const int32_t* d_nodes, int n_list) {
-  const int Kp = in->Kp, KK = Kp * Kp, C = in->C, n = d_nodes ? n_list : in->n_nodes;
+  const PStageGenericArgs A = pstage_generic_args(in, d_nodes, n_list);
+  const int KK = A.Kp * A.Kp;
   const bool grad = (in->cfg.flags & (EPOCH_GRAD_BRANCH | EPOCH_GRAD_Q)) != 0;
   const int ept = KK <= 256 ? 1 : (KK + 255) / 256;
   const int ipb = ept == 1 ? std::max(1, 256 / KK) : 1;
-  const int items = n * C;
+  const int items = A.n_nodes * A.C;
   dim3 grid((items + ipb - 1) / ipb);
   const size_t shm = 2 * (size_t)ipb * KK * sizeof(T);
-  const T* base = static_cast<const T*>(sizeof(T) == 8 ? in->eig64.ptr : in->eigT.ptr);
-  const size_t S = in->S;
-  const T* V = base;
-  const T* Vi = base + S * KK;
-  const T* lr = base + 2 * S * KK;
-  const T* li = lr + S * Kp;
-  const double* cat = static_cast<const double*>(in->cat.ptr);
-  TO* Pout = static_cast<TO*>(in->Pm.ptr);
-  TO* dPout = static_cast<TO*>(in->dPm.ptr);
-#define EPOCH_PSTAGE(G, E)                                                                      \
-  hipLaunchKernelGGL((pstage_generic_kernel<T, TO, G, E>), grid, dim3(256), shm, in->stream, n, d_nodes, Kp, C, \
-                     V, Vi, lr, li, in->d_seg_offset, in->d_seg_process, in->d_seg_time,        \
-                     in->d_seg_frac, in->d_rate, cat, Pout, dPout)
+#define EPOCH_PSTAGE(G, E) hipLaunchKernelGGL((pstage_generic_kernel<T, TO, G, E>), grid, dim3(256), shm, in->stream, A)
   if (ept == 1) {
     if (grad) EPOCH_PSTAGE(true, 1); else EPOCH_PSTAGE(false, 1);
   } else if (ept <= 4) {
@@ -764,6 +775,52 @@ int launch_chunk_sum(EpochInstance* in, int n) {
 int launch_grad_reduce(EpochInstance* in, int n_slots, const int32_t* chunks_per_node) {
   return in->fp64 ? grad_reduce_dispatch<double>(in, n_slots, chunks_per_node)
                   : grad_reduce_dispatch<float>(in, n_slots, chunks_per_node);
+}
+
+// Operands of the generic P stage for every branch, or the n_list listed ones (d_nodes).  The 4-state
+// FP32 tree walk also reads the transposed matrices.
+PStageGenericArgs pstage_generic_args(const EpochInstance* in, const int32_t* d_nodes, int n_list) {
+  const bool wide = in->fp64 || in->eig_fp64;  // the arithmetic of the eigen reconstruction
+  const size_t S = in->S, Kp = in->Kp, KK = Kp * Kp, es = wide ? sizeof(double) : sizeof(float);
+  const char* base = static_cast<const char*>(wide ? in->eig64.ptr : in->eigT.ptr);
+  PStageGenericArgs A{};
+  A.n_nodes = d_nodes ? n_list : in->n_nodes;
+  A.node_list = d_nodes;
+  A.Kp = in->Kp;
+  A.C = in->C;
+  A.V = base;
+  A.Vi = base + S * KK * es;
+  A.lr = base + 2 * S * KK * es;
+  A.li = base + (2 * S * KK + S * Kp) * es;
+  A.seg_offset = in->d_seg_offset;
+  A.seg_process = in->d_seg_process;
+  A.seg_time = in->d_seg_time;
+  A.seg_frac = in->d_seg_frac;
+  A.rate = in->d_rate;
+  A.cat_rates = static_cast<const double*>(in->cat.ptr);
+  A.Pout = in->Pm.ptr;
+  A.dPout = in->dPm.ptr;
+  A.PTout = in->path == 1 && in->walk_ok && !in->fp64 ? in->walk_tcol.ptr : nullptr;
+  return A;
+}
+
+// The P stages of n 4-state FP32 instances that share the reconstruction's arithmetic and gradient flag.
+int launch_pstage_generic_multi(const PStageGenericArgs* d_args, int n, int max_items, bool wide, bool grad,
+                                hipStream_t st) {
+  constexpr int KK = 16, ipb = 256 / KK;
+  const dim3 grid((max_items + ipb - 1) / ipb, n);
+  const size_t shm = 2 * (size_t)ipb * KK * (wide ? sizeof(double) : sizeof(float));
+  if (wide) {
+    if (grad)
+      hipLaunchKernelGGL((pstage_generic_multi_kernel<double, float, true>), grid, dim3(256), shm, st, d_args);
+    else
+      hipLaunchKernelGGL((pstage_generic_multi_kernel<double, float, false>), grid, dim3(256), shm, st, d_args);
+  } else if (grad) {
+    hipLaunchKernelGGL((pstage_generic_multi_kernel<float, float, true>), grid, dim3(256), shm, st, d_args);
+  } else {
+    hipLaunchKernelGGL((pstage_generic_multi_kernel<float, float, false>), grid, dim3(256), shm, st, d_args);
+  }
+  return hip_check(hipGetLastError(), "pstage_generic_multi launch");
 }
 
 int launch_pstage_generic(EpochInstance* in) { return launch_pstage_generic_nodes(in, nullptr, 0); }

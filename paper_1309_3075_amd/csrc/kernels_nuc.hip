@@ -454,11 +454,14 @@ __global__ __launch_bounds__(256) void nuc_post_list_kernel(const ListOps ops, c
 
 // ---------------------------------------------------------------------------
 template <typename T, int CP>
-__global__ __launch_bounds__(256) void nuc_root_kernel(
-    const V4<T>* __restrict__ rootp, const int32_t* __restrict__ scale_root, const double* __restrict__ pi,
-    const double* __restrict__ cat, const double* __restrict__ weights, double* __restrict__ site,
-    double* __restrict__ block_out, unsigned* __restrict__ arrived, double* __restrict__ result,
-    double* __restrict__ host_logL, int P, int C) {
+__device__ inline void nuc_root_blocks(const NucRootArgs& A, int n_blocks) {
+  const V4<T>* __restrict__ rootp = static_cast<const V4<T>*>(A.rootp);
+  const int32_t* __restrict__ scale_root = A.scale_root;
+  const double* __restrict__ pi = A.pi;
+  const double* __restrict__ cat = A.cat;
+  const double* __restrict__ weights = A.weights;
+  double* __restrict__ site = A.site;
+  const int P = A.P, C = A.C;
   __shared__ double sm[256];
   constexpr int TPW = 64 / CP;
   const int lane = threadIdx.x & 63;
@@ -467,7 +470,7 @@ __global__ __launch_bounds__(256) void nuc_root_kernel(
   const bool cat_ok = cl < C;
   const int c = cat_ok ? cl : 0;
   double contrib = 0.0;
-  for (int first = (blockIdx.x * 4 + wave) * TPW; first < P; first += gridDim.x * 4 * TPW) {
+  for (int first = (blockIdx.x * 4 + wave) * TPW; first < P; first += n_blocks * 4 * TPW) {
     const int p = first + lane / CP;
     const int pc = p < P ? p : P - 1;
     const V4<T> x = rootp[(size_t)c * P + pc];
@@ -486,8 +489,25 @@ __global__ __launch_bounds__(256) void nuc_root_kernel(
   for (int o = 32; o > 0; o >>= 1) contrib += __shfl_xor(contrib, o, 64);
   if (lane == 0) sm[wave] = contrib;
   __syncthreads();
-  sum_blocks_in_last<256>(((sm[0] + sm[1]) + sm[2]) + sm[3], block_out, blockIdx.x, gridDim.x, arrived, result,
-                          host_logL, sm);
+  sum_blocks_in_last<256>(((sm[0] + sm[1]) + sm[2]) + sm[3], A.blocksum, blockIdx.x, n_blocks, A.arrived, A.result,
+                          A.host_logL, sm);
+}
+template <typename T, int CP>
+__global__ __launch_bounds__(256) void nuc_root_kernel(const NucRootArgs A) {
+  nuc_root_blocks<T, CP>(A, gridDim.x);
+}
+// Blocks of the root launch, at most: each adds its share through one atomic counter.
+constexpr int kRootBlocks = 256;
+__host__ __device__ inline int root_blocks(int P, int patterns_per_block) {
+  const int n = (P + patterns_per_block - 1) / patterns_per_block;
+  return n < kRootBlocks ? n : kRootBlocks;
+}
+// The root reductions of many instances (blockIdx.y) in one launch.
+template <typename T, int CP>
+__global__ __launch_bounds__(256) void nuc_root_multi_kernel(const NucRootArgs* __restrict__ args) {
+  const NucRootArgs A = args[blockIdx.y];
+  const int n_blocks = root_blocks(A.P, 4 * (64 / CP));
+  if ((int)blockIdx.x < n_blocks) nuc_root_blocks<T, CP>(A, n_blocks);
 }
 
 // ---------------------------------------------------------------------------
@@ -842,21 +862,11 @@ int post_dispatch_cp(EpochInstance* in, const int32_t* d_nodes, const int32_t* l
   return hip_check(hipGetLastError(), "nuc_post_level launch");
 }
 
-// Blocks of the root launch, at most: each adds its share through one atomic counter.
-constexpr int kRootBlocks = 256;
 template <typename T, int CP>
 int root_dispatch_cp(EpochInstance* in, double* host_logL) {
-  constexpr int TPW = 64 / CP;
-  const int blocks = std::min((in->P + 4 * TPW - 1) / (4 * TPW), kRootBlocks);
-  const V4<T>* part = static_cast<const V4<T>*>(in->partials.ptr);
-  const int32_t* sc = static_cast<const int32_t*>(in->scales.ptr);
-  const size_t slot = in->root_slot;  // root - N, or its compact slot under an HBM budget
-  hipLaunchKernelGGL((nuc_root_kernel<T, CP>), dim3(blocks), dim3(256), 0, in->stream,
-                     part + slot * in->C * (size_t)in->P, sc + slot * (size_t)in->P,
-                     static_cast<const double*>(in->pi.ptr), static_cast<const double*>(in->cat.ptr),
-                     static_cast<const double*>(in->weights.ptr), static_cast<double*>(in->site.ptr),
-                     static_cast<double*>(in->blocksum.ptr), static_cast<unsigned*>(in->arrived.ptr),
-                     static_cast<double*>(in->result.ptr), host_logL, in->P, in->C);
+  NucRootArgs A = nuc_root_args(in);
+  A.host_logL = host_logL;
+  hipLaunchKernelGGL((nuc_root_kernel<T, CP>), dim3(root_blocks(in->P, 4 * (64 / CP))), dim3(256), 0, in->stream, A);
   return hip_check(hipGetLastError(), "nuc_root launch");
 }
 
@@ -978,6 +988,36 @@ int launch_nuc_post_nodes(EpochInstance* in, const int32_t* d_nodes, const int32
     case 4: return in->fp64 ? post_dispatch_cp<double, 4>(in, d_nodes, level_off, h_nodes) : post_dispatch_cp<float, 4>(in, d_nodes, level_off, h_nodes);
     default: return in->fp64 ? post_dispatch_cp<double, 8>(in, d_nodes, level_off, h_nodes) : post_dispatch_cp<float, 8>(in, d_nodes, level_off, h_nodes);
   }
+}
+
+NucRootArgs nuc_root_args(const EpochInstance* in) {
+  // root - N, or the root's compact slot under an HBM budget
+  const size_t slot = in->root_slot, row = (size_t)in->C * in->P * 4 * in->real_size;
+  NucRootArgs A{};
+  A.rootp = static_cast<const char*>(in->partials.ptr) + slot * row;
+  A.scale_root = static_cast<const int32_t*>(in->scales.ptr) + slot * (size_t)in->P;
+  A.pi = static_cast<const double*>(in->pi.ptr);
+  A.cat = static_cast<const double*>(in->cat.ptr);
+  A.weights = static_cast<const double*>(in->weights.ptr);
+  A.site = static_cast<double*>(in->site.ptr);
+  A.blocksum = static_cast<double*>(in->blocksum.ptr);
+  A.arrived = static_cast<unsigned*>(in->arrived.ptr);
+  A.result = static_cast<double*>(in->result.ptr);
+  A.P = in->P;
+  A.C = in->C;
+  return A;
+}
+
+// Root reductions of n FP32 instances whose categories share a lane group of cp.
+int launch_nuc_root_multi(const NucRootArgs* d_args, int n, int max_patterns, int cp, hipStream_t st) {
+  const dim3 grid(root_blocks(max_patterns, 4 * (64 / cp)), n);
+  switch (cp) {
+    case 1: hipLaunchKernelGGL((nuc_root_multi_kernel<float, 1>), grid, dim3(256), 0, st, d_args); break;
+    case 2: hipLaunchKernelGGL((nuc_root_multi_kernel<float, 2>), grid, dim3(256), 0, st, d_args); break;
+    case 4: hipLaunchKernelGGL((nuc_root_multi_kernel<float, 4>), grid, dim3(256), 0, st, d_args); break;
+    default: hipLaunchKernelGGL((nuc_root_multi_kernel<float, 8>), grid, dim3(256), 0, st, d_args); break;
+  }
+  return hip_check(hipGetLastError(), "nuc_root_multi launch");
 }
 
 int launch_nuc_root(EpochInstance* in, double* host_logL) {

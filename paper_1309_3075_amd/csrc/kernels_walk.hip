@@ -54,6 +54,7 @@ struct WalkArgs {
   const double* cat;      // rates[8], weights[8]
   const T* weightsT;      // [P]
   T* dpart;               // [groups][n_nodes]: dlogL/dl shares of each group of tiles
+  double* dbranch;        // [n_nodes]: dlogL/dl
   V4<T>* dummy;           // [128]: read (first 64) and write (last 64) stand-ins
   int N, P, C, n_tiles, slots, n_nodes, root, n_groups;
 };
@@ -424,6 +425,26 @@ struct FetchM {
   int sta, stb;
 };
 
+// Rows of an operation's matrices (P of both children; pre-order also their columns and dP/dl),
+// loaded with the operation's other operands one operation ahead: read when needed, they put an L2
+// round trip into every operation of the program.
+struct MatsM {
+  f4v Ra, Rb, Ca, Cb, DRa, DRb;
+};
+template <bool PRE, int NT>
+__device__ inline void fetch_mats_m(const WalkArgs<float>& g, const LaneM<NT>& L, const Op& op, MatsM& m) {
+  const uint32_t mb = (uint32_t)g.C * 64;
+  const size_t oa = (size_t)op.a * g.C * 16, ob = (size_t)op.b * g.C * 16;
+  m.Ra = bload16(rsrc(g.Pm + oa, mb), L.voff_m);
+  m.Rb = bload16(rsrc(g.Pm + ob, mb), L.voff_m);
+  if constexpr (PRE) {
+    m.Ca = bload16(rsrc(g.PmT + oa, mb), L.voff_m);
+    m.Cb = bload16(rsrc(g.PmT + ob, mb), L.voff_m);
+    m.DRa = bload16(rsrc(g.dPm + oa, mb), L.voff_m);
+    m.DRb = bload16(rsrc(g.dPm + ob, mb), L.voff_m);
+  }
+}
+
 // Tip indicator: one-hot for an observed state, all ones for a missing one.
 __device__ inline V4<float> tip_vector(int mask) {  // the tip's state set as a 0/1 vector
   V4<float> x;
@@ -453,23 +474,15 @@ __device__ inline void fetch_op_m(const WalkArgs<float>& g, const LaneM<NT>& L, 
 
 template <int CP, bool PRE, int NT>
 __device__ inline void walk_step_m(const WalkArgs<float>& g, const LaneM<NT>& L, const Op& op,
-                                   const FetchM (&cur)[NT], bool has_next, const Op& nop, FetchM (&nxt)[NT],
-                                   int (&E)[NT]) {
+                                   const FetchM (&cur)[NT], const MatsM& mats, const Op& nop, FetchM (&nxt)[NT],
+                                   MatsM& nmats, int (&E)[NT]) {
   const int info = op.info, a = op.a, b = op.b, u = op.u;
   const int ka = (info >> 3) & 3, kb = (info >> 5) & 3;
   const int s_a = (info >> 8) & 63, s_b = (info >> 14) & 63, s_q = (info >> 20) & 63, s_qb = (info >> 26) & 63;
-  const uint32_t mb = (uint32_t)g.C * 64;
-  const auto rPa = rsrc(g.Pm + (size_t)a * g.C * 16, mb), rPb = rsrc(g.Pm + (size_t)b * g.C * 16, mb);
-  const f4v Ra = bload16(rPa, L.voff_m), Rb = bload16(rPb, L.voff_m);
-  f4v Ca, Cb, DRa, DRb;
-  if constexpr (PRE) {
-    Ca = bload16(rsrc(g.PmT + (size_t)a * g.C * 16, mb), L.voff_m);
-    Cb = bload16(rsrc(g.PmT + (size_t)b * g.C * 16, mb), L.voff_m);
-    DRa = bload16(rsrc(g.dPm + (size_t)a * g.C * 16, mb), L.voff_m);
-    DRb = bload16(rsrc(g.dPm + (size_t)b * g.C * 16, mb), L.voff_m);
-  }
+  const f4v Ra = mats.Ra, Rb = mats.Rb, Ca = mats.Ca, Cb = mats.Cb, DRa = mats.DRa, DRb = mats.DRb;
   __asm__ volatile("" ::: "memory");
-  if (has_next) fetch_op_m(g, L, nop, nxt);
+  fetch_op_m(g, L, nop, nxt);  // after the last operation: the first one's again, not used
+  fetch_mats_m<PRE>(g, L, nop, nmats);
 
   V4<float> xa[NT], xb[NT], q[NT];
 #pragma unroll
@@ -540,7 +553,7 @@ __device__ inline void walk_step_m(const WalkArgs<float>& g, const LaneM<NT>& L,
 }
 
 template <int CP, bool PRE, int NT>
-__global__ __launch_bounds__(256) void nuc_walk_mfma_kernel(const WalkArgs<float> g) {
+__device__ inline void walk_mfma_blocks(const WalkArgs<float>& g) {
   constexpr int TPW = 64 / CP;
   extern __shared__ __align__(16) unsigned char walk_lds[];
   const int lane = threadIdx.x & 63;
@@ -580,13 +593,15 @@ __global__ __launch_bounds__(256) void nuc_walk_mfma_kernel(const WalkArgs<float
     Op o0 = load_op(g.ops, 0);
     Op o1 = load_op(g.ops, n > 1 ? 1 : 0);
     FetchM f0[NT], f1[NT];
+    MatsM m0, m1;
     fetch_op_m(g, L, o0, f0);
+    fetch_mats_m<PRE>(g, L, o0, m0);
     for (int i = 0;;) {
       const Op o2 = load_op(g.ops, i + 2 < n ? i + 2 : 0);
-      walk_step_m<CP, PRE, NT>(g, L, o0, f0, i + 1 < n, o1, f1, E);
+      walk_step_m<CP, PRE, NT>(g, L, o0, f0, m0, o1, f1, m1, E);
       if (++i >= n) break;
       const Op o3 = load_op(g.ops, i + 2 < n ? i + 2 : 0);
-      walk_step_m<CP, PRE, NT>(g, L, o1, f1, i + 1 < n, o2, f0, E);
+      walk_step_m<CP, PRE, NT>(g, L, o1, f1, m1, o2, f0, m0, E);
       if (++i >= n) break;
       o0 = o2;
       o1 = o3;
@@ -601,13 +616,18 @@ __global__ __launch_bounds__(256) void nuc_walk_mfma_kernel(const WalkArgs<float
   }
 }
 
-// Transposed transition matrices (row i of PmT[v][c] = column i of Pm[v][c]).
-__global__ __launch_bounds__(256) void walk_transpose_kernel(const float* __restrict__ Pm, int n_mats,
-                                                             float* __restrict__ PmT) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n_mats * 16) return;
-  const int m = t / 16, i = (t / 4) % 4, j = t % 4;
-  PmT[(size_t)m * 16 + 4 * i + j] = Pm[(size_t)m * 16 + 4 * j + i];
+template <int CP, bool PRE, int NT>
+__global__ __launch_bounds__(256) void nuc_walk_mfma_kernel(const WalkArgs<float> g) {
+  walk_mfma_blocks<CP, PRE, NT>(g);
+}
+// The walks of many instances in one launch (blockIdx.y; blocks past an instance's tiles have none).
+// With launches of its own each small problem leaves the GPU to a handful of blocks: 64 problems of
+// 16-64 taxa and 300-3,000 patterns with gradients took 2.3 ms on 16 concurrent graph branches (3.8 ms
+// with the copies of the gradients), 0.43 ms in all in shared launches.
+template <int CP, bool PRE, int NT>
+__global__ __launch_bounds__(256) void nuc_walk_mfma_multi_kernel(const WalkArgs<float>* __restrict__ args) {
+  const WalkArgs<float> g = args[blockIdx.y];
+  walk_mfma_blocks<CP, PRE, NT>(g);
 }
 
 // Columns of P (and dP/dl) of every tip branch: tcol[m][v][c][j] for j < 4 is
@@ -632,25 +652,35 @@ __global__ __launch_bounds__(256) void walk_tipcol_kernel(const T* __restrict__ 
   tcol[t] = col;
 }
 
-// dlogL/dl of every branch: fixed-order FP64 sums of its per-tile shares, first
-// over strided row groups (grid.y), then over the groups.
-constexpr int kWalkRowGroups = 32;
+// dlogL/dl of every branch: fixed-order FP64 sums of its per-tile shares.  A block takes 16
+// branches; its 64 groups of threads each sum every 64th row (64-byte pieces of a row at a time).
+constexpr int kSumNodes = 16, kSumGroups = 64;
 template <typename T>
-__global__ __launch_bounds__(256) void walk_dbranch_rows_kernel(const T* __restrict__ dpart, int n_tiles, int n_nodes,
-                                                                double* __restrict__ part2) {
-  const int v = blockIdx.x * 256 + threadIdx.x;
-  if (v >= n_nodes) return;
+__device__ inline void walk_dbranch_block(const T* __restrict__ dpart, int n_rows, int n_nodes, double* __restrict__ dbranch) {
+  __shared__ double sm[kSumGroups][kSumNodes];
+  const int k = threadIdx.x % kSumNodes, grp = threadIdx.x / kSumNodes;
+  const int v = blockIdx.x * kSumNodes + k;
   double s = 0.0;
-  for (int t = blockIdx.y; t < n_tiles; t += kWalkRowGroups) s += (double)dpart[(size_t)t * n_nodes + v];
-  part2[(size_t)blockIdx.y * n_nodes + v] = s;
+  if (v < n_nodes) {
+#pragma unroll 4
+    for (int t = grp; t < n_rows; t += kSumGroups) s += (double)dpart[(size_t)t * n_nodes + v];
+  }
+  sm[grp][k] = s;
+  __syncthreads();
+  if (grp == 0 && v < n_nodes) {
+    double d = 0.0;
+    for (int r = 0; r < kSumGroups; ++r) d += sm[r][k];
+    dbranch[v] = d;
+  }
 }
-__global__ __launch_bounds__(256) void walk_dbranch_final_kernel(const double* __restrict__ part2, int n_nodes,
-                                                                 double* __restrict__ dbranch) {
-  const int v = blockIdx.x * 256 + threadIdx.x;
-  if (v >= n_nodes) return;
-  double s = 0.0;
-  for (int r = 0; r < kWalkRowGroups; ++r) s += part2[(size_t)r * n_nodes + v];
-  dbranch[v] = s;
+template <typename T>
+__global__ __launch_bounds__(kSumNodes* kSumGroups) void walk_dbranch_kernel(const T* __restrict__ dpart, int n_rows,
+                                                                             int n_nodes, double* __restrict__ dbranch) {
+  walk_dbranch_block(dpart, n_rows, n_nodes, dbranch);
+}
+__global__ __launch_bounds__(kSumNodes* kSumGroups) void walk_dbranch_multi_kernel(const WalkArgs<float>* __restrict__ args) {
+  const WalkArgs<float>& g = args[blockIdx.y];
+  if ((int)blockIdx.x * kSumNodes < g.n_nodes) walk_dbranch_block(g.dpart, g.n_groups, g.n_nodes, g.dbranch);
 }
 
 int cp_walk(int C) { return C <= 1 ? 1 : (C <= 2 ? 2 : (C <= 4 ? 4 : 8)); }
@@ -677,6 +707,7 @@ WalkArgs<T> walk_args(EpochInstance* in, bool pre) {
   g.cat = static_cast<const double*>(in->cat.ptr);
   g.weightsT = static_cast<const T*>(in->weightsT.ptr);
   g.dpart = static_cast<T*>(in->walk_dpart.ptr);
+  g.dbranch = static_cast<double*>(in->dbranch.ptr);
   g.dummy = static_cast<V4<T>*>(in->walk_dummy.ptr);
   g.N = in->N;
   g.P = in->P;
@@ -690,12 +721,18 @@ WalkArgs<T> walk_args(EpochInstance* in, bool pre) {
 }
 
 
+// Wavefronts per block, each with its own stacks.
+int walk_waves_per_block(size_t per_wave) {
+  int wpb = 4;
+  while (wpb > 1 && wpb * per_wave > kWalkMaxLds) wpb >>= 1;
+  return wpb;
+}
+
 template <typename T, int CP, int NT>
 int walk_launch(EpochInstance* in, bool pre) {
   const WalkArgs<T> g = walk_args<T>(in, pre);
   const size_t per_wave = walk_lds_per_wave<T>(g.slots, NT);
-  int wpb = 4;  // wavefronts per block, each with its own stacks
-  while (wpb > 1 && wpb * per_wave > kWalkMaxLds) wpb >>= 1;
+  const int wpb = walk_waves_per_block(per_wave);
   const size_t lds = wpb * per_wave;
   const int groups = (g.n_tiles + NT - 1) / NT;
   int blocks = (groups + wpb - 1) / wpb;
@@ -713,12 +750,8 @@ int walk_launch(EpochInstance* in, bool pre) {
   }
   int rc = hip_check(hipGetLastError(), pre ? "nuc_walk pre-order launch" : "nuc_walk post-order launch");
   if (rc || !pre) return rc;
-  double* part2 = reinterpret_cast<double*>(static_cast<char*>(in->walk_dpart.ptr) + walk_dpart_rows_bytes(in));
-  const int nb = (in->n_nodes + 255) / 256;
-  hipLaunchKernelGGL((walk_dbranch_rows_kernel<T>), dim3(nb, kWalkRowGroups), dim3(256), 0, in->stream, g.dpart,
-                     groups, in->n_nodes, part2);
-  hipLaunchKernelGGL(walk_dbranch_final_kernel, dim3(nb), dim3(256), 0, in->stream, part2, in->n_nodes,
-                     static_cast<double*>(in->dbranch.ptr));
+  hipLaunchKernelGGL((walk_dbranch_kernel<T>), dim3((in->n_nodes + kSumNodes - 1) / kSumNodes),
+                     dim3(kSumNodes * kSumGroups), 0, in->stream, g.dpart, groups, in->n_nodes, g.dbranch);
   return hip_check(hipGetLastError(), "walk_dbranch launch");
 }
 
@@ -766,13 +799,17 @@ bool walk_fits(const EpochInstance* in, int slots) {
 // launch per level, each with fewer 16-pattern tiles than there are SIMDs).
 constexpr int kWalkAutoTiles = 1024;
 
+// FP64 values per node an HBM budget counts beyond what the walk stores, so that a budget keeps
+// choosing the partials it always chose.
+constexpr size_t kWalkBudgetSpare = 32;
+
 // Bytes an HBM budget must hold for a walk that stores n_stored partials: the
 // partials, the root's scale row and (with gradients) the rows of dlogL/dl shares.
 size_t walk_budget_bytes(const EpochInstance* in, size_t n_stored) {
   const size_t V = (size_t)in->C * in->P * in->Kp * in->real_size;
   size_t b = n_stored * V + (size_t)in->P * sizeof(int32_t);
   if (in->cfg.flags & (EPOCH_GRAD_BRANCH | EPOCH_GRAD_Q))
-    b += walk_dpart_rows_bytes(in) + (size_t)kWalkRowGroups * in->n_nodes * sizeof(double);
+    b += walk_dpart_rows_bytes(in) + kWalkBudgetSpare * in->n_nodes * sizeof(double);
   return b;
 }
 
@@ -856,7 +893,7 @@ int walk_prepare(EpochInstance* in) {
     if (!rc) rc = hip_check(hipMemsetAsync(in->walk_dummy.ptr, 0, kWalkDummyBytes, in->stream), "walk dummy clear");
   }
   if (!rc && (in->cfg.flags & (EPOCH_GRAD_BRANCH | EPOCH_GRAD_Q)))
-    rc = ensure(in->walk_dpart, walk_dpart_rows_bytes(in) + (size_t)kWalkRowGroups * in->n_nodes * sizeof(double));
+    rc = ensure(in->walk_dpart, walk_dpart_rows_bytes(in));
   if (!rc)
     rc = hip_check(hipMemcpyAsync(in->walk_ops.ptr, ops.data(), ops.size() * sizeof(int32_t), hipMemcpyHostToDevice,
                                   in->stream), "walk program upload");
@@ -871,24 +908,110 @@ int walk_prepare(EpochInstance* in) {
   return EPOCH_OK;
 }
 
-int launch_walk_tipcol(EpochInstance* in) {
-  if (!in->fp64) {
-    const int n_mats = in->n_nodes * in->C;
-    hipLaunchKernelGGL(walk_transpose_kernel, dim3((n_mats * 16 + 255) / 256), dim3(256), 0, in->stream,
-                       static_cast<const float*>(in->Pm.ptr), n_mats, static_cast<float*>(in->walk_tcol.ptr));
-    return hip_check(hipGetLastError(), "walk_transpose launch");
+namespace {
+template <int CP, int NT>
+int walk_batch_pass(const WalkBatch& b, bool pre, hipStream_t st) {
+  const auto* args = reinterpret_cast<const WalkArgs<float>*>(static_cast<const char*>(b.dev.ptr) +
+                                                             (pre ? b.off_pre : b.off_post));
+  const size_t per_wave = walk_lds_per_wave<float>(pre ? b.pre_slots : b.post_slots, NT);
+  const int wpb = walk_waves_per_block(per_wave);
+  const dim3 grid((b.max_groups + wpb - 1) / wpb, b.n);
+  if (pre) {
+    hipLaunchKernelGGL((nuc_walk_mfma_multi_kernel<CP, true, NT>), grid, dim3(64 * wpb), wpb * per_wave, st, args);
+    hipLaunchKernelGGL(walk_dbranch_multi_kernel, dim3((b.max_nodes + kSumNodes - 1) / kSumNodes, b.n),
+                       dim3(kSumNodes * kSumGroups), 0, st, args);
+  } else {
+    hipLaunchKernelGGL((nuc_walk_mfma_multi_kernel<CP, false, NT>), grid, dim3(64 * wpb), wpb * per_wave, st, args);
   }
+  return hip_check(hipGetLastError(), "nuc_walk batch launch");
+}
+int walk_batch_pass(const WalkBatch& b, bool pre, hipStream_t st) {
+  switch (4 * b.nt + (b.cp == 1 ? 0 : (b.cp == 2 ? 1 : (b.cp == 4 ? 2 : 3)))) {
+    case 4: return walk_batch_pass<1, 1>(b, pre, st);
+    case 5: return walk_batch_pass<2, 1>(b, pre, st);
+    case 6: return walk_batch_pass<4, 1>(b, pre, st);
+    case 7: return walk_batch_pass<8, 1>(b, pre, st);
+    case 8: return walk_batch_pass<1, 2>(b, pre, st);
+    case 9: return walk_batch_pass<2, 2>(b, pre, st);
+    case 10: return walk_batch_pass<4, 2>(b, pre, st);
+    default: return walk_batch_pass<8, 2>(b, pre, st);
+  }
+}
+}  // namespace
+
+// FP32 walks whose gradient the walk forms too, with no cap on their blocks.
+bool walk_batch_member(const EpochInstance* in) {
+  const bool grad = (in->cfg.flags & (EPOCH_GRAD_BRANCH | EPOCH_GRAD_Q)) != 0;
+  return in->path == 1 && !in->fp64 && in->walk_ok && (!grad || in->walk_pre_ok) && in->walk_blocks == 0;
+}
+int walk_batch_key(const EpochInstance* in) {
+  const bool grad = (in->cfg.flags & (EPOCH_GRAD_BRANCH | EPOCH_GRAD_Q)) != 0;
+  return cp_walk(in->C) * 16 + walk_nt_of(in) * 4 + (in->eig_fp64 ? 2 : 0) + (grad ? 1 : 0);
+}
+
+int walk_batch_build(const std::vector<EpochInstance*>& members, WalkBatch& b) {
+  const size_t n = members.size();
+  const EpochInstance* like = members[0];
+  b.n = (int)n;
+  b.cp = cp_walk(like->C);
+  b.nt = walk_nt_of(like);
+  b.wide = like->eig_fp64;
+  b.grad = (like->cfg.flags & (EPOCH_GRAD_BRANCH | EPOCH_GRAD_Q)) != 0;
+  b.max_items = b.max_patterns = b.max_groups = b.max_nodes = 0;
+  b.post_slots = b.pre_slots = 1;
+  std::vector<PStageGenericArgs> ps(n);
+  std::vector<NucRootArgs> root(n);
+  std::vector<WalkArgs<float>> post(n), pre(n);
+  // the longest programs first, so that they are not what the launch ends on
+  std::vector<EpochInstance*> order(members);
+  std::stable_sort(order.begin(), order.end(),
+                   [](const EpochInstance* x, const EpochInstance* y) { return x->n_nodes > y->n_nodes; });
+  for (size_t q = 0; q < n; ++q) {
+    EpochInstance* in = order[q];
+    ps[q] = pstage_generic_args(in, nullptr, 0);
+    root[q] = nuc_root_args(in);
+    post[q] = walk_args<float>(in, false);
+    pre[q] = walk_args<float>(in, true);
+    b.max_items = std::max(b.max_items, in->n_nodes * in->C);
+    b.max_patterns = std::max(b.max_patterns, in->P);
+    b.max_groups = std::max(b.max_groups, post[q].n_groups);
+    b.max_nodes = std::max(b.max_nodes, in->n_nodes);
+    b.post_slots = std::max(b.post_slots, post[q].slots);
+    b.pre_slots = std::max(b.pre_slots, pre[q].slots);
+  }
+  auto align = [](size_t x) { return (x + 255) / 256 * 256; };
+  b.off_root = align(n * sizeof(PStageGenericArgs));
+  b.off_post = b.off_root + align(n * sizeof(NucRootArgs));
+  b.off_pre = b.off_post + align(n * sizeof(WalkArgs<float>));
+  const size_t bytes = b.off_pre + n * sizeof(WalkArgs<float>);
+  int rc = ensure(b.dev, bytes);
+  if (rc) return rc;
+  std::vector<char> h(bytes);
+  std::copy(ps.begin(), ps.end(), reinterpret_cast<PStageGenericArgs*>(h.data()));
+  std::copy(root.begin(), root.end(), reinterpret_cast<NucRootArgs*>(h.data() + b.off_root));
+  std::copy(post.begin(), post.end(), reinterpret_cast<WalkArgs<float>*>(h.data() + b.off_post));
+  std::copy(pre.begin(), pre.end(), reinterpret_cast<WalkArgs<float>*>(h.data() + b.off_pre));
+  return hip_check(hipMemcpy(b.dev.ptr, h.data(), bytes, hipMemcpyHostToDevice), "walk batch descriptors");
+}
+
+int walk_batch_launch(const WalkBatch& b, bool grad, hipStream_t st) {
+  const char* base = static_cast<const char*>(b.dev.ptr);
+  int rc = launch_pstage_generic_multi(reinterpret_cast<const PStageGenericArgs*>(base), b.n, b.max_items, b.wide,
+                                       b.grad, st);
+  if (!rc) rc = walk_batch_pass(b, false, st);
+  if (!rc) rc = launch_nuc_root_multi(reinterpret_cast<const NucRootArgs*>(base + b.off_root), b.n, b.max_patterns, b.cp, st);
+  if (!rc && grad) rc = walk_batch_pass(b, true, st);
+  return rc;
+}
+
+int launch_walk_tipcol(EpochInstance* in) {
+  if (!in->fp64) return EPOCH_OK;  // the P stage writes the transposed matrices itself
   const bool grad = in->dPm.ptr != nullptr && (in->cfg.flags & (EPOCH_GRAD_BRANCH | EPOCH_GRAD_Q));
   const int n = (grad ? 2 : 1) * in->N * in->C * 16;
   const int blocks = (n + 255) / 256;
-  if (in->fp64)
-    hipLaunchKernelGGL((walk_tipcol_kernel<double>), dim3(blocks), dim3(256), 0, in->stream,
-                       static_cast<const double*>(in->Pm.ptr), grad ? static_cast<const double*>(in->dPm.ptr) : nullptr,
-                       in->N, in->C, static_cast<V4<double>*>(in->walk_tcol.ptr));
-  else
-    hipLaunchKernelGGL((walk_tipcol_kernel<float>), dim3(blocks), dim3(256), 0, in->stream,
-                       static_cast<const float*>(in->Pm.ptr), grad ? static_cast<const float*>(in->dPm.ptr) : nullptr,
-                       in->N, in->C, static_cast<V4<float>*>(in->walk_tcol.ptr));
+  hipLaunchKernelGGL((walk_tipcol_kernel<double>), dim3(blocks), dim3(256), 0, in->stream,
+                     static_cast<const double*>(in->Pm.ptr), grad ? static_cast<const double*>(in->dPm.ptr) : nullptr,
+                     in->N, in->C, static_cast<V4<double>*>(in->walk_tcol.ptr));
   return hip_check(hipGetLastError(), "walk_tipcol launch");
 }
 

@@ -36,6 +36,7 @@ void fastpath_release(EpochInstance*) {}
 int fastpath_tips_changed(EpochInstance*) { return EPOCH_OK; }
 int fastpath_tree_changed(EpochInstance* in) {
   if (codon(in)) return codon_prepare(in);
+  if (!nuc(in)) return few_prepare(in);
   if (nuc(in)) {
     int rc = walk_prepare(in);
     if (rc) return rc;
@@ -117,6 +118,7 @@ void set_view(EpochInstance* in, int j, bool accumulate) {
 // logL follows its partials (the next chunk overwrites them), then the shares
 // are summed in order.
 int launch_post_generic_chunks(EpochInstance* in) {
+  if (in->few) return launch_few_post(in, in->few_plan, static_cast<const int32_t*>(in->few_dev.ptr));
   if (in->gen_nchunks == 1) return launch_post_generic(in);
   for (int j = 0; j < in->gen_nchunks; ++j) {
     set_view(in, j, false);
@@ -185,6 +187,9 @@ int fastpath_gradient(EpochInstance* in, bool want_Q) {
     EPOCH_PHASE(4, launch_grad_reduce(in, in->nuc_slots, static_cast<const int32_t*>(in->gslots.ptr)));
   } else if (codon(in)) {
     EPOCH_PHASE(3, launch_codon_pre_grad(in));
+  } else if (in->few) {
+    EPOCH_PHASE(3, launch_few_pre(in));
+    EPOCH_PHASE(4, launch_few_grad(in));
   } else if (in->gen_nchunks > 1) {
     EPOCH_PHASE(3, launch_pre_grad_generic_chunks(in));
   } else {

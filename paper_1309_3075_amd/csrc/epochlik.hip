@@ -520,7 +520,7 @@ int epoch_destroy(EpochInstance* in) {
                     &in->cat, &in->tree_i, &in->tree_d, &in->Pm, &in->dPm, &in->partials, &in->scales,
                     &in->pre, &in->site, &in->blocksum, &in->result, &in->Gpart, &in->G, &in->dbranch,
                     &in->qseg, &in->qscratch, &in->chain_items, &in->chain_scratch, &in->dQ, &in->seglist, &in->gslots, &in->codon_dev, &in->codon_aux,
-                    &in->eigTT, &in->eig64T, &in->qtau, &in->nuc_nodes, &in->walk_ops,
+                    &in->eigTT, &in->eig64T, &in->qtau, &in->nuc_nodes, &in->few_dev, &in->few_S, &in->walk_ops,
                     &in->walk_tcol, &in->walk_dpart, &in->walk_dummy, &in->walk_slots, &in->inc_dev, &in->tg_i,
                     &in->tg_d, &in->amb, &in->arrived})
     release(*b);

@@ -121,6 +121,18 @@ struct CodonSchedule {
   int nt = 4;            // 16-state tiles of the padded states: 4 (64 states) or 2 (32); every problem alike
 };
 
+// One launch of a pass of the few-pattern kernels: a level's items, or consecutive narrow levels as a
+// run of one block (kernels_few.hip gives the layout of the integers).
+struct FewStep {
+  bool run = false;
+  size_t at = 0;  // first integer in FewPlan::data
+  int n_ints = 0, n_levels = 0, n_nodes = 0, n_tips = 0, max_branches = 0;
+};
+struct FewPlan {
+  std::vector<FewStep> post, pre;
+  std::vector<int32_t> data;
+};
+
 // Incremental re-evaluation (MCMC proposals): the work of one restricted pass.
 struct IncrementalPlan {
   std::vector<int32_t> pnodes;          // branches (child nodes) whose transition matrices are formed again
@@ -128,7 +140,8 @@ struct IncrementalPlan {
   std::vector<int32_t> post_nodes;      // internal nodes whose partials are formed again, grouped by level
   std::vector<int32_t> post_level_off;  // [n_levels + 2]: level l occupies [off[l], off[l + 1])
   CodonSchedule codon;                  // the 64-state schedule restricted to post_nodes
-  size_t off_chain = 0, off_post = 0, off_codon = 0;  // byte offsets in the device copy
+  FewPlan few;                          // post_nodes as launches of the few-pattern kernels (generic path)
+  size_t off_chain = 0, off_post = 0, off_codon = 0, off_few = 0;  // byte offsets in the device copy
 };
 
 }  // namespace epochlik
@@ -227,6 +240,10 @@ struct EpochInstance {
   epochlik::DevBuf qtau;       // double [nseg][C] tau of each segment term of dlogL/dQ, then complex [nseg][C][Kp] e^{tau lambda}
   int q_chunks = 1;            // segment chunks per process of the dlogL/dQ sums
   int q_chunk_items = 32;      // segment terms per chunk
+  bool few = false;              // generic path, few patterns: the kernels of kernels_few.hip
+  epochlik::FewPlan few_plan;    // their launches for the current tree
+  epochlik::DevBuf few_dev;      // int32: the plan's item lists
+  epochlik::DevBuf few_S;        // T [n_nodes][C][P][Kp]: child vectors P_v L_v
   epochlik::DevBuf seglist;    // int32 segments grouped by process: offsets [S+1], items [nseg*C]
   epochlik::DevBuf gslots;     // int32 [n]: partial-sum slots written per branch (4-state / 64-state gradient)
   epochlik::DevBuf codon_dev;  // 64-state path: descriptor + work items
@@ -319,6 +336,12 @@ int launch_eigen_check_n(hipStream_t st, int K, int n, int ld, long mat_stride, 
                          double* out);
 int launch_pstage_generic(EpochInstance* in);
 int launch_pstage_generic_nodes(EpochInstance* in, const int32_t* d_nodes, int n);  // listed branches only
+// few patterns (kernels_few.hip)
+int few_prepare(EpochInstance* in);
+void few_plan(const EpochInstance* in, const int32_t* nodes, const int32_t* level_off, bool with_pre, FewPlan& out);
+int launch_few_post(EpochInstance* in, const FewPlan& plan, const int32_t* d_data);
+int launch_few_pre(EpochInstance* in);
+int launch_few_grad(EpochInstance* in);
 int launch_post_generic_nodes(EpochInstance* in, const int32_t* d_nodes, const int32_t* level_off);
 PStageGenericArgs pstage_generic_args(const EpochInstance* in, const int32_t* d_nodes, int n_list);
 int launch_pstage_generic_multi(const PStageGenericArgs* d_args, int n, int max_items, bool wide, bool grad,

@@ -184,13 +184,13 @@ int build_schedule(EpochBatch* b) {
                                region);
     off += sc.slot_total[q];
   }
-  const size_t bytes = sizeof(CodonProblem) * n + sizeof(int2) * (sc.items.size() + sc.reduce_items.size());
+  const size_t bytes = sizeof(CodonProblem) * n + sizeof(int4) * sc.items.size() + sizeof(int2) * sc.reduce_items.size();
   int rc = ensure(b->dev, bytes);
   if (rc) return rc;
   std::vector<char> h(bytes);
   memcpy(h.data(), desc.data(), sizeof(CodonProblem) * n);
-  memcpy(h.data() + sizeof(CodonProblem) * n, sc.items.data(), sizeof(int2) * sc.items.size());
-  memcpy(h.data() + sizeof(CodonProblem) * n + sizeof(int2) * sc.items.size(), sc.reduce_items.data(),
+  memcpy(h.data() + sizeof(CodonProblem) * n, sc.items.data(), sizeof(int4) * sc.items.size());
+  memcpy(h.data() + sizeof(CodonProblem) * n + sizeof(int4) * sc.items.size(), sc.reduce_items.data(),
          sizeof(int2) * sc.reduce_items.size());
   return hip_check(hipMemcpy(b->dev.ptr, h.data(), bytes, hipMemcpyHostToDevice), "batch schedule upload");
 }
@@ -332,9 +332,9 @@ int enqueue(EpochBatch* b, uint32_t what) {
   }
   if (b->merged) {
     const CodonProblem* probs = static_cast<const CodonProblem*>(b->dev.ptr);
-    const int2* items = reinterpret_cast<const int2*>(static_cast<const char*>(b->dev.ptr) +
+    const int4* items = reinterpret_cast<const int4*>(static_cast<const char*>(b->dev.ptr) +
                                                       sizeof(CodonProblem) * b->sched.n_problems);
-    const int2* red = items + b->sched.items.size();
+    const int2* red = reinterpret_cast<const int2*>(items + b->sched.items.size());
     int rc = codon_launch_post(b->sched, probs, items, b->stream);
     if (!rc) rc = codon_launch_root(b->sched, probs, b->stream);
     if (!rc && (what & (kGradBranch | kGradQ))) rc = codon_launch_pre_grad(b->sched, probs, items, red, static_cast<double*>(b->dpart.ptr), b->stream, false, true);

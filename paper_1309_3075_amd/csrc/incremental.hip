@@ -106,7 +106,7 @@ int build_lists(EpochInstance* in) {
   }
   L.post_level_off[pl.n_levels + 1] = (int32_t)L.post_nodes.size();
   // the 64-state schedule keeps its per-level tile shapes and drops the clean nodes
-  std::vector<int2> citems;
+  std::vector<int4> citems;
   if (in->path == 2) {
     const auto& sc = in->codon_sched;
     L.codon = sc;
@@ -123,7 +123,7 @@ int build_lists(EpochInstance* in) {
   L.off_chain = align16(L.pnodes.size() * sizeof(int32_t));
   L.off_post = L.off_chain + align16(L.chain_items.size() * sizeof(int4));
   L.off_codon = L.off_post + align16(L.post_nodes.size() * sizeof(int32_t));
-  L.off_few = L.off_codon + align16(citems.size() * sizeof(int2));
+  L.off_few = L.off_codon + align16(citems.size() * sizeof(int4));
   if (in->few) few_plan(in, L.post_nodes.data(), L.post_level_off.data(), false, L.few);
   const size_t bytes = L.off_few + (in->few ? L.few.data.size() * sizeof(int32_t) : 0);
   int rc = ensure(in->inc_dev, std::max<size_t>(bytes, 256));
@@ -133,7 +133,7 @@ int build_lists(EpochInstance* in) {
   if (!L.chain_items.empty()) memcpy(h.data() + L.off_chain, L.chain_items.data(), L.chain_items.size() * sizeof(int4));
   if (!L.post_nodes.empty()) memcpy(h.data() + L.off_post, L.post_nodes.data(), L.post_nodes.size() * sizeof(int32_t));
   if (in->few && !L.few.data.empty()) memcpy(h.data() + L.off_few, L.few.data.data(), L.few.data.size() * sizeof(int32_t));
-  if (!citems.empty()) memcpy(h.data() + L.off_codon, citems.data(), citems.size() * sizeof(int2));
+  if (!citems.empty()) memcpy(h.data() + L.off_codon, citems.data(), citems.size() * sizeof(int4));
   return bytes ? stage_upload(in, in->inc_dev.ptr, h.data(), bytes) : EPOCH_OK;
 }
 
@@ -164,7 +164,7 @@ int launch_post_incremental(EpochInstance* in) {
   if (L.post_nodes.empty()) return EPOCH_OK;
   switch (in->path) {
     case 1: return launch_nuc_post_nodes(in, d_post, L.post_level_off.data(), L.post_nodes.data());
-    case 2: return launch_codon_post_schedule(in, L.codon, reinterpret_cast<const int2*>(base + L.off_codon));
+    case 2: return launch_codon_post_schedule(in, L.codon, reinterpret_cast<const int4*>(base + L.off_codon));
     default:
       if (in->few) return launch_few_post(in, L.few, reinterpret_cast<const int32_t*>(base + L.off_few));
       return launch_post_generic_nodes(in, d_post, L.post_level_off.data());

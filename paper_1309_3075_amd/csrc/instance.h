@@ -20,7 +20,7 @@ struct DevBuf {
 
 // Device-visible description of one problem for the 64-state kernels (one
 // instance, or one member of a batch).
-struct CodonProblem {
+struct alignas(16) CodonProblem {
   const float* Pm;
   const uint8_t* tips;
   float* part;
@@ -108,7 +108,7 @@ struct WalkBatch {
 
 // Merged level schedule: work items (problem, internal node) grouped by level.
 struct CodonSchedule {
-  std::vector<int2> items;         // level l (1-based) occupies [level_off[l-1], level_off[l])
+  std::vector<int4> items;         // (problem, node, its children); level l (1-based) occupies [level_off[l-1], level_off[l])
   std::vector<int> level_off;
   std::vector<int> level_R;        // 64-pattern tiles per block of the launches of each level
   std::vector<int2> reduce_items;  // every (problem, node)
@@ -394,7 +394,7 @@ int launch_walk_pre_grad(EpochInstance* in);
 
 // 64-state MFMA kernels (kernels_codon.hip)
 int launch_codon_post(EpochInstance* in);
-int launch_codon_post_schedule(EpochInstance* in, const CodonSchedule& sc, const int2* d_items);
+int launch_codon_post_schedule(EpochInstance* in, const CodonSchedule& sc, const int4* d_items);
 int launch_codon_root(EpochInstance* in, double* host_logL = nullptr);
 int launch_codon_pre_grad(EpochInstance* in);
 int codon_prepare(EpochInstance* in);
@@ -402,10 +402,10 @@ CodonProblem codon_descriptor(const EpochInstance* in, int c, const int32_t* gsl
 constexpr size_t kCodonSlotBytes = 64 * 64 * sizeof(float);  // one FP32 64x64 partial of dlogL/dP (FP64: twice)
 void codon_build_schedule(const std::vector<const EpochInstance*>& insts, int target_blocks, CodonSchedule& out,
                           std::vector<std::vector<int32_t>>& gslots);
-int codon_launch_post(const CodonSchedule& sc, const CodonProblem* d_probs, const int2* d_items, hipStream_t st);
+int codon_launch_post(const CodonSchedule& sc, const CodonProblem* d_probs, const int4* d_items, hipStream_t st);
 int codon_launch_root(const CodonSchedule& sc, const CodonProblem* d_probs, hipStream_t st, double* host_logL = nullptr);
 size_t codon_dpart_bytes(const CodonSchedule& sc);
-int codon_launch_pre_grad(const CodonSchedule& sc, const CodonProblem* d_probs, const int2* d_items,
+int codon_launch_pre_grad(const CodonSchedule& sc, const CodonProblem* d_probs, const int4* d_items,
                           const int2* d_reduce_items, double* dpart, hipStream_t st, bool accumulate, bool finish);
 
 }  // namespace epochlik

@@ -120,9 +120,25 @@ __device__ inline void stage_matrix(T* __restrict__ s, const T* __restrict__ g, 
     *reinterpret_cast<f4*>(reinterpret_cast<char*>(s + row * LDP) + 16 * c) = src[e];
   }
 }
+// Both matrices of a node by 256 threads, every load in flight before the first LDS write.
 template <int NT, typename T>
-__device__ inline void stage_matrix(T* __restrict__ s, const T* __restrict__ g) {
-  stage_matrix<NT>(s, g, threadIdx.x);
+__device__ inline void stage_matrices(T* __restrict__ sa, T* __restrict__ sb, const T* __restrict__ ga,
+                                      const T* __restrict__ gb) {
+  EPOCH_DIMS(NT);
+  constexpr int PER_ROW = KP * sizeof(T) / 16, PIECES = (KP * PER_ROW + 255) / 256;
+  f4 va[PIECES], vb[PIECES];
+#pragma unroll
+  for (int k = 0; k < PIECES; ++k) {
+    const int e = threadIdx.x + 256 * k;
+    va[k] = gptr(reinterpret_cast<const f4*>(ga))[e];
+    vb[k] = gptr(reinterpret_cast<const f4*>(gb))[e];
+  }
+#pragma unroll
+  for (int k = 0; k < PIECES; ++k) {
+    const int e = threadIdx.x + 256 * k, row = e / PER_ROW, c = e % PER_ROW;
+    *reinterpret_cast<f4*>(reinterpret_cast<char*>(sa + row * LDP) + 16 * c) = va[k];
+    *reinterpret_cast<f4*>(reinterpret_cast<char*>(sb + row * LDP) + 16 * c) = vb[k];
+  }
 }
 // Row sums over the first K columns into column KP (needs the staged matrix;
 // 256 threads, t = 0 .. 255: TPR threads per row, CPT columns each).
@@ -138,8 +154,6 @@ __device__ inline void stage_row_sums(T* __restrict__ s, int K, int t) {
   for (int o = 1; o < TPR; o <<= 1) acc += __shfl_xor(acc, o, TPR);
   if (q == 0) s[row * LDP + KP] = acc;
 }
-template <int NT, typename T>
-__device__ inline void stage_row_sums(T* __restrict__ s, int K) { stage_row_sums<NT>(s, K, threadIdx.x); }
 
 // Row-max / row-sum over the 16 lanes of a DPP row (lanes sharing g).
 __device__ inline float row16_max(float v) {
@@ -439,15 +453,14 @@ __device__ inline void zero_unused_slot(const CodonProblem& pr, int child, int n
 template <typename T, int NT>
 struct PreTileLoads {
   v4<T> La[NT], Lb[NT];  // rows of 4 states of internal children's partials (child product A operand)
-  v4<T> Q[NT];           // q_u in the D layout
   int cola[4], colb[4];
 };
 
 template <int NT, typename T>
-__device__ inline void pre_load_tile(PreTileLoads<T, NT>& ld, const CodonProblem& pr, const T* La, const T* Lb,
-                                     const T* Qu, int a, int b, int p0, int g, int r) {
+__device__ inline void pre_load_tile(PreTileLoads<T, NT>& ld, const CodonProblem& pr, const T* La, const T* Lb, int a,
+                                     int b, int p0, int g, int r) {
   EPOCH_DIMS(NT);
-  const int P = pr.P, K = pr.K, N = pr.N;
+  const int P = pr.P, K = pr.K;
   const int pa = min(p0 + r, P - 1);
   if (La) {
     const EPOCH_GLOBAL v4<T>* row = gptr(reinterpret_cast<const v4<T>*>(La + (size_t)pa * KP)) + g;
@@ -463,8 +476,6 @@ __device__ inline void pre_load_tile(PreTileLoads<T, NT>& ld, const CodonProblem
   } else {
     tip_columns<NT, T>(ld.colb, pr.tips + (size_t)b * pr.tip_stride, P, p0, K, g);
   }
-  if (Qu) load_dlayout<NT, T>(ld.Q, Qu, P, p0, g, r);
-  (void)N;
 }
 
 // S[nt] (D layout) from 16-byte A-operand rows already in registers.
@@ -488,18 +499,17 @@ __device__ inline void child_gemm_regs(v4<T> (&S)[NT], const v4<T> (&a)[NT], con
 // ---------------------------------------------------------------------------
 template <typename T, int NT, bool AMB>
 __global__ __launch_bounds__(256) void codon_post_level_kernel(const CodonProblem* __restrict__ probs,
-                                                                const int2* __restrict__ items, int R) {
+                                                                const int4* __restrict__ items, int R) {
   EPOCH_DIMS(NT);
   __shared__ __align__(16) T sPa[KP * LDP];
   __shared__ __align__(16) T sPb[KP * LDP];
-  const int2 it = items[blockIdx.y];
+  const int4 it = items[blockIdx.y];
   const CodonProblem& pr = probs[it.x];
   const int N = pr.N, P = pr.P, K = pr.K;
   const int base = blockIdx.x * R * TILE;
   if (base >= P) return;  // uniform: this problem has fewer tiles
   const int end = min(P, base + R * TILE);
-  const int u = it.y;
-  const int a = pr.left[u], b = pr.right[u];
+  const int u = it.y, a = it.z, b = it.w;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, r = lane & 15;
   T* part = reinterpret_cast<T*>(pr.part);
   const T* La = a >= N ? part + (size_t)(a - N) * P * KP : nullptr;
@@ -512,7 +522,7 @@ __global__ __launch_bounds__(256) void codon_post_level_kernel(const CodonProble
   // go out before the matrices are staged, so the two memory round trips overlap; each later tile's
   // at the end of the tile before it
   auto load = [&](PreTileLoads<T, NT>& ld, int (&csc)[4], int p0) {
-    pre_load_tile<NT, T>(ld, pr, La, Lb, nullptr, a, b, p0, g, r);
+    pre_load_tile<NT, T>(ld, pr, La, Lb, a, b, p0, g, r);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int pc = min(p0 + drow<T>(g, v), P - 1);
@@ -523,12 +533,13 @@ __global__ __launch_bounds__(256) void codon_post_level_kernel(const CodonProble
   int csc[4];
   load(cur, csc, base + WT * w);
   const T* Pm = reinterpret_cast<const T*>(pr.Pm);
-  stage_matrix<NT>(sPa, Pm + (size_t)a * pr.pm_stride);
-  stage_matrix<NT>(sPb, Pm + (size_t)b * pr.pm_stride);
+  stage_matrices<NT>(sPa, sPb, Pm + (size_t)a * pr.pm_stride, Pm + (size_t)b * pr.pm_stride);
   __syncthreads();
-  stage_row_sums<NT>(sPa, K);
-  stage_row_sums<NT>(sPb, K);
-  __syncthreads();
+  if (!La || !Lb) {  // only a tip reads the row sums (a missing state)
+    if (!La) stage_row_sums<NT>(sPa, K, threadIdx.x);
+    if (!Lb) stage_row_sums<NT>(sPb, K, threadIdx.x);
+    __syncthreads();
+  }
   for (int p0 = base + WT * w; p0 < end; p0 += 4 * WT) {
     v4<T> Sa[NT], Sb[NT];
     if (La)
@@ -566,7 +577,7 @@ __global__ __launch_bounds__(256) void codon_post_level_kernel(const CodonProble
 
 template <typename T, int NT, bool AMB>
 __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void codon_pre_level_kernel(
-    const CodonProblem* __restrict__ probs, const int2* __restrict__ items, int R) {
+    const CodonProblem* __restrict__ probs, const int4* __restrict__ items, int R) {
   EPOCH_DIMS(NT);
   constexpr int NCT = Dim<NT>::NCT;
   __shared__ __align__(16) T sPa[KP * LDP];
@@ -575,18 +586,18 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void codon_pre_level_k
   __shared__ __align__(16) T sL[TILE * LDP];  // that side's child partials for the block tile
   __shared__ __align__(16) T sCF[TILE];         // w_p / L_p of the block tile
   __shared__ __align__(16) int sCol[2][TILE];   // tip columns of the block tile
-  const int2 it = items[blockIdx.y];
+  const int4 it = items[blockIdx.y];
   const CodonProblem& pr = probs[it.x];
   const int N = pr.N, P = pr.P, K = pr.K;
   const int base = blockIdx.x * R * TILE;
-  const int u = it.y;
-  const int a = pr.left[u], b = pr.right[u];
+  const int u = it.y, a = it.z, b = it.w;
   if (base >= P) {  // uniform: this problem (or pattern chunk) has fewer tiles
     zero_unused_slot<T, NT>(pr, a, 256);
     zero_unused_slot<T, NT>(pr, b, 256);
     return;
   }
   const int n_tiles = min(R, (P - base + TILE - 1) / TILE);  // uniform over the block
+  const int slot_a = pr.gslots[pr.n_nodes + a], slot_b = pr.gslots[pr.n_nodes + b];  // read now, used at the end
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, r = lane & 15;
   const T* part = reinterpret_cast<const T*>(pr.part);
   T* pre = reinterpret_cast<T*>(pr.pre);
@@ -595,14 +606,15 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void codon_pre_level_k
   const T* Qu = u == pr.root ? nullptr : pre + (size_t)(u - N) * P * KP;
   // the first tile's loads go out before the matrices are staged, so the two wait together
   PreTileLoads<T, NT> cur, nxt;
-  pre_load_tile<NT, T>(cur, pr, La, Lb, Qu, a, b, base + WT * w, g, r);
+  pre_load_tile<NT, T>(cur, pr, La, Lb, a, b, base + WT * w, g, r);
   const T* Pm = reinterpret_cast<const T*>(pr.Pm);
-  stage_matrix<NT>(sPa, Pm + (size_t)a * pr.pm_stride);
-  stage_matrix<NT>(sPb, Pm + (size_t)b * pr.pm_stride);
+  stage_matrices<NT>(sPa, sPb, Pm + (size_t)a * pr.pm_stride, Pm + (size_t)b * pr.pm_stride);
   __syncthreads();
-  stage_row_sums<NT>(sPa, K);
-  stage_row_sums<NT>(sPb, K);
-  __syncthreads();
+  if (!La || !Lb) {  // only a tip reads the row sums (a missing state)
+    if (!La) stage_row_sums<NT>(sPa, K, threadIdx.x);
+    if (!Lb) stage_row_sums<NT>(sPb, K, threadIdx.x);
+    __syncthreads();
+  }
   T piv[NT];
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) piv[nt] = 16 * nt + r < K ? (T)pr.pi[16 * nt + r] : T(0);
@@ -618,7 +630,18 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void codon_pre_level_k
   T* lrows = sL + (WT * w) * LDP;
   for (int bt = 0; bt < n_tiles; ++bt) {
     const int p0 = base + bt * TILE + WT * w;  // first pattern of this wavefront's part
-    T wts[4];  // pattern weights of this wavefront's rows, in flight during the child products
+    // q_u and the pattern weights of this wavefront's rows, in flight during the child products.
+    // Loaded with the next tile's rows, q_u took the kernel past its 256 registers: a pointer that
+    // is reloaded from scratch waits for every store in flight, 9,000 to 13,000 of the 42,000 to
+    // 47,000 cycles of a tile.
+    v4<T> Q[NT];
+    if (Qu) {
+      load_dlayout<NT, T>(Q, Qu, P, p0, g, r);
+    } else {
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) Q[nt] = v4<T>{piv[nt], piv[nt], piv[nt], piv[nt]};
+    }
+    T wts[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) wts[v] = gptr(reinterpret_cast<const T*>(pr.weightsT))[min(p0 + drow<T>(g, v), P - 1)];
     // ---- this wavefront's 16 patterns: child vectors, q_u, w_p / L_p
@@ -631,9 +654,6 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void codon_pre_level_k
       child_gemm_regs<NT, T>(Sb, cur.Lb, sPb, g, r);
     else
       tip_lookup<NT, AMB, T>(Sb, cur.colb, sPb, r, pr.amb);
-    v4<T> Q[NT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) Q[nt] = Qu ? cur.Q[nt] : v4<T>{piv[nt], piv[nt], piv[nt], piv[nt]};
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       T sum = 0;
@@ -648,7 +668,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void codon_pre_level_k
       }
     }
     // loads of this wavefront's part of the next tile, in flight during the rest
-    if (bt + 1 < n_tiles) pre_load_tile<NT, T>(nxt, pr, La, Lb, Qu, a, b, p0 + TILE, g, r);
+    if (bt + 1 < n_tiles) pre_load_tile<NT, T>(nxt, pr, La, Lb, a, b, p0 + TILE, g, r);
 #pragma unroll
     for (int side = 0; side < 2; ++side) {
       const int child = side == 0 ? a : b;
@@ -713,9 +733,8 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void codon_pre_level_k
   // this wavefront's rows of the block's slot of each child branch
 #pragma unroll
   for (int side = 0; side < 2; ++side) {
-    const int child = side == 0 ? a : b;
     const v4<T>* G = side == 0 ? Ga : Gb;
-    EPOCH_GLOBAL T* dst = gptr(reinterpret_cast<T*>(pr.Gpart) + ((size_t)pr.gslots[pr.n_nodes + child] + blockIdx.x) * KK);
+    EPOCH_GLOBAL T* dst = gptr(reinterpret_cast<T*>(pr.Gpart) + ((size_t)(side == 0 ? slot_a : slot_b) + blockIdx.x) * KK);
 #pragma unroll
     for (int c = 0; c < NCT; ++c)
 #pragma unroll
@@ -762,14 +781,13 @@ __device__ inline void split_load_tile(SplitTileLoads& ld, const CodonProblem& p
 
 template <bool AMB>
 __global__ __launch_bounds__(512, 1) void codon_pre_split_kernel(const CodonProblem* __restrict__ probs,
-                                                                const int2* __restrict__ items, int R) {
+                                                                const int4* __restrict__ items, int R) {
   __shared__ PreSplitShared sh;
-  const int2 it = items[blockIdx.y];
+  const int4 it = items[blockIdx.y];
   const CodonProblem& pr = probs[it.x];
   const int N = pr.N, P = pr.P, K = pr.K;
   const int base = blockIdx.x * R * TILE;
-  const int u = it.y;
-  const int a = pr.left[u], b = pr.right[u];
+  const int u = it.y, a = it.z, b = it.w;
   if (base >= P) {  // uniform: this problem (or pattern chunk) has fewer tiles
     zero_unused_slot<float, 4>(pr, a, 512);
     zero_unused_slot<float, 4>(pr, b, 512);
@@ -1041,7 +1059,10 @@ void codon_build_schedule(const std::vector<const EpochInstance*>& insts, int ta
     for (size_t q = 0; q < nd; ++q) {
       const auto& pl = inst(q)->plan;
       if (l > pl.n_levels) continue;
-      for (int k = pl.level_offset[l]; k < pl.level_offset[l + 1]; ++k) out.items.push_back(make_int2((int)q, pl.level_nodes[k]));
+      for (int k = pl.level_offset[l]; k < pl.level_offset[l + 1]; ++k) {
+        const int u = pl.level_nodes[k];
+        out.items.push_back(make_int4((int)q, u, pl.left[u], pl.right[u]));
+      }
     }
     const int n_items = (int)(out.items.size() - begin);
     const int R = codon_tiles_per_block(max_tiles, std::max(1, n_items), target_blocks, max_tiles);
@@ -1074,7 +1095,7 @@ void codon_build_schedule(const std::vector<const EpochInstance*>& insts, int ta
 
 namespace {
 template <typename T, int NT>
-void post_levels(const CodonSchedule& sc, const CodonProblem* d_probs, const int2* d_items, hipStream_t st) {
+void post_levels(const CodonSchedule& sc, const CodonProblem* d_probs, const int4* d_items, hipStream_t st) {
   for (int l = 1; l <= sc.n_levels; ++l) {
     const int b = sc.level_off[l - 1], n = sc.level_off[l] - b;
     if (!n) continue;
@@ -1093,7 +1114,7 @@ void post_levels(const CodonSchedule& sc, const CodonProblem* d_probs, const int
 // kernel.  FP64 (the split kernel's LDS would not hold doubles) and 32 states:
 // the level kernel throughout.
 template <typename T, int NT>
-void pre_levels(const CodonSchedule& sc, const CodonProblem* d_probs, const int2* d_items, hipStream_t st) {
+void pre_levels(const CodonSchedule& sc, const CodonProblem* d_probs, const int4* d_items, hipStream_t st) {
   for (int l = sc.n_levels; l >= 1; --l) {
     const int b = sc.level_off[l - 1], n = sc.level_off[l] - b;
     if (!n) continue;
@@ -1147,7 +1168,7 @@ void reduce_launch(const CodonSchedule& sc, const CodonProblem* d_probs, const i
     }                                          \
   } while (0)
 
-int codon_launch_post(const CodonSchedule& sc, const CodonProblem* d_probs, const int2* d_items, hipStream_t st) {
+int codon_launch_post(const CodonSchedule& sc, const CodonProblem* d_probs, const int4* d_items, hipStream_t st) {
   EPOCH_CODON_DISPATCH(sc, post_levels, sc, d_probs, d_items, st);
   return hip_check(hipGetLastError(), "codon_post_level launch");
 }
@@ -1161,7 +1182,7 @@ size_t codon_dpart_bytes(const CodonSchedule& sc) {
   return sc.reduce_items.size() * (sc.nt == 2 ? reduce_chunks<2>() : reduce_chunks<4>()) * sizeof(double);
 }
 
-int codon_launch_pre_grad(const CodonSchedule& sc, const CodonProblem* d_probs, const int2* d_items,
+int codon_launch_pre_grad(const CodonSchedule& sc, const CodonProblem* d_probs, const int4* d_items,
                           const int2* d_reduce_items, double* dpart, hipStream_t st, bool accumulate, bool finish) {
   EPOCH_CODON_DISPATCH(sc, pre_levels, sc, d_probs, d_items, st);
   int rc = hip_check(hipGetLastError(), "codon_pre_level launch");
@@ -1206,13 +1227,13 @@ int codon_prepare(EpochInstance* in) {
     }
   }
   const size_t dbytes = sizeof(CodonProblem) * desc.size();
-  const size_t bytes = dbytes + sizeof(int2) * (sc.items.size() + sc.reduce_items.size());
+  const size_t bytes = dbytes + sizeof(int4) * sc.items.size() + sizeof(int2) * sc.reduce_items.size();
   rc = ensure(in->codon_dev, bytes);
   if (rc) return rc;
   std::vector<char> h(bytes);
   memcpy(h.data(), desc.data(), dbytes);
-  memcpy(h.data() + dbytes, sc.items.data(), sizeof(int2) * sc.items.size());
-  memcpy(h.data() + dbytes + sizeof(int2) * sc.items.size(), sc.reduce_items.data(),
+  memcpy(h.data() + dbytes, sc.items.data(), sizeof(int4) * sc.items.size());
+  memcpy(h.data() + dbytes + sizeof(int4) * sc.items.size(), sc.reduce_items.data(),
          sizeof(int2) * sc.reduce_items.size());
   std::vector<int32_t> hg(C * gs);
   for (int c = 0; c < C; ++c) std::copy(gslots[c].begin(), gslots[c].end(), hg.begin() + c * gs);
@@ -1226,11 +1247,13 @@ int codon_prepare(EpochInstance* in) {
 
 namespace {
 const CodonProblem* dev_probs(EpochInstance* in) { return static_cast<const CodonProblem*>(in->codon_dev.ptr); }
-const int2* dev_items(EpochInstance* in) {
-  return reinterpret_cast<const int2*>(static_cast<const char*>(in->codon_dev.ptr) +
+const int4* dev_items(EpochInstance* in) {
+  return reinterpret_cast<const int4*>(static_cast<const char*>(in->codon_dev.ptr) +
                                        sizeof(CodonProblem) * in->codon_nchunks * in->C);
 }
-const int2* dev_reduce_items(EpochInstance* in) { return dev_items(in) + in->codon_sched.items.size(); }
+const int2* dev_reduce_items(EpochInstance* in) {
+  return reinterpret_cast<const int2*>(dev_items(in) + in->codon_sched.items.size());
+}
 }  // namespace
 
 // Post-order pass.  In chunks, each chunk's root reduction follows its partials
@@ -1247,7 +1270,7 @@ int launch_codon_post(EpochInstance* in) {
   return launch_chunk_sum(in, nc);
 }
 
-int launch_codon_post_schedule(EpochInstance* in, const CodonSchedule& sc, const int2* d_items) {
+int launch_codon_post_schedule(EpochInstance* in, const CodonSchedule& sc, const int4* d_items) {
   return codon_launch_post(sc, dev_probs(in), d_items, in->stream);
 }
 

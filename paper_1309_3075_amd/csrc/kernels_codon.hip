@@ -197,14 +197,18 @@ __device__ inline double row16_sum(double v) {
 // state is its column, a missing one column KP (the row sums), and the
 // caller's ambiguity set a is KP + 1 + a (text after Eq. 4: tips are 0/1
 // indicators of the possible states).
+// The states are loaded a tile ahead and turned into columns where they are used, so that the load
+// is not waited for when it is issued.
 template <int NT, typename T>
-__device__ inline void tip_columns(int (&col)[4], const uint8_t* __restrict__ tipst, int P, int p0, int K, int g) {
+__device__ inline void tip_states(int (&st)[4], const uint8_t* __restrict__ tipst, int P, int p0, int g) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) st[v] = gptr(tipst)[min(p0 + drow<T>(g, v), P - 1)];
+}
+template <int NT>
+__device__ inline void tip_columns(int (&col)[4], const int (&st)[4], int K) {
   EPOCH_DIMS(NT);
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int st = gptr(tipst)[min(p0 + drow<T>(g, v), P - 1)];
-    col[v] = st < K ? st : KP + (st - K);
-  }
+  for (int v = 0; v < 4; ++v) col[v] = st[v] < K ? st[v] : KP + (st[v] - K);
 }
 // Sum of row entries over an ambiguity set (rare: kept off the common path).
 template <typename T>
@@ -299,11 +303,23 @@ __global__ __launch_bounds__(256) void codon_root_kernel(const CodonProblem* __r
     } else {
       double l[kMaxCategories];
       int e[kMaxCategories], emax = INT_MIN;
-      for (int c = 0; c < pr.n_cats; ++c) {
-        const CodonProblem& q = probs[blockIdx.y + c];
-        l[c] = pr.cat[kMaxCategories + c] * pi_dot(q, pc);
-        e[c] = q.scales[slot * P + pc];
-        if (l[c] > 0.0) emax = max(emax, e[c]);
+      for (int c0 = 0; c0 < pr.n_cats; c0 += 4) {  // four categories' rows in flight
+        double d[4];
+        int x[4];
+#pragma unroll
+        for (int cc = 0; cc < 4; ++cc) {
+          const CodonProblem& q = probs[blockIdx.y + min(c0 + cc, pr.n_cats - 1)];
+          d[cc] = pi_dot(q, pc);
+          x[cc] = q.scales[slot * P + pc];
+        }
+#pragma unroll
+        for (int cc = 0; cc < 4; ++cc) {
+          const int c = c0 + cc;
+          if (c >= pr.n_cats) break;
+          l[c] = pr.cat[kMaxCategories + c] * d[cc];
+          e[c] = x[cc];
+          if (l[c] > 0.0) emax = max(emax, e[c]);
+        }
       }
       double L = 0.0;
       for (int c = 0; c < pr.n_cats; ++c) {
@@ -369,11 +385,31 @@ __device__ inline void grad_rows_internal(v4<T>* G, const T* __restrict__ tcol, 
 // give dlogL/dP to FP32 rounding, as the FP32 product would.  Lane (g, r)
 // supplies patterns 8 g .. 8 g + 7 of each 32-pattern block for row r of A
 // and column r of B; D has the FP32 layout.
+// The indicator is the same for the four wavefronts, so it is laid out once in the LDS buffer an
+// internal child's partials would take ([column][pattern], each wavefront the 16 patterns it owns)
+// instead of being built from the states in every wavefront's registers, 320 of the 850 vector
+// instructions of a tile.
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
-typedef int i4 __attribute__((ext_vector_type(4)));
+constexpr int kHotStride = 2 * TILE + 16;  // bytes from one column's row of the indicator to the next
+__device__ inline void stage_tip_indicator(void* buf, const int (&col)[4], int K, int w, int lane) {
+  char* const hot = static_cast<char*>(buf);
+  const int g = lane >> 4, r = lane & 15;
+  f4* const mine = reinterpret_cast<f4*>(hot + lane * kHotStride + 2 * WT * w);  // column `lane`, this wavefront's patterns
+  mine[0] = f4{0.f, 0.f, 0.f, 0.f};
+  mine[1] = f4{0.f, 0.f, 0.f, 0.f};
+  wave_lds_sync();
+  const int c = r == 0 ? col[0] : (r == 1 ? col[1] : (r == 2 ? col[2] : col[3]));
+  const int p = WT * w + 4 * g + r;
+  if (r < 4 && c < KP) *reinterpret_cast<__bf16*>(hot + c * kHotStride + 2 * p) = (__bf16)1.0f;
+  // a missing state is every observable column
+  for (unsigned long long m = __ballot(r < 4 && c == KP); m; m &= m - 1) {
+    const int l = __builtin_ctzll(m);
+    if (lane < K) *reinterpret_cast<__bf16*>(hot + lane * kHotStride + 2 * (WT * w + 4 * (l >> 4) + (l & 15))) = (__bf16)1.0f;
+  }
+}
 template <int NT>
 __device__ inline void grad_rows_tip_bf16(f4* G, const float* __restrict__ tcol, const float* __restrict__ sCF,
-                                          const int* __restrict__ sCol, int K, int ct0, int g, int r) {
+                                          const void* __restrict__ buf, int ct0, int g, int r) {
   EPOCH_DIMS(NT);
   constexpr int NCT = Dim<NT>::NCT;
 #pragma unroll
@@ -392,14 +428,9 @@ __device__ inline void grad_rows_tip_bf16(f4* G, const float* __restrict__ tcol,
       am[e] = m;
       al[e] = (__bf16)(r1 - (float)m);
     }
-    const i4 cl0 = *reinterpret_cast<const i4*>(sCol + p0), cl1 = *reinterpret_cast<const i4*>(sCol + p0 + 4);
-    const int col[8] = {cl0.x, cl0.y, cl0.z, cl0.w, cl1.x, cl1.y, cl1.z, cl1.w};
 #pragma unroll
     for (int c = 0; c < NCT; ++c) {
-      const int j = 16 * (ct0 + c) + r;
-      bf8 B;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) B[e] = (col[e] == j || (col[e] == KP && j < K)) ? (__bf16)1.0f : (__bf16)0.0f;
+      const bf8 B = *reinterpret_cast<const bf8*>(static_cast<const char*>(buf) + (16 * (ct0 + c) + r) * kHotStride + 2 * p0);
       G[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, B, G[c], 0, 0, 0);
       G[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am, B, G[c], 0, 0, 0);
       G[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, B, G[c], 0, 0, 0);
@@ -408,13 +439,17 @@ __device__ inline void grad_rows_tip_bf16(f4* G, const float* __restrict__ tcol,
 }
 
 template <int NT, bool AMB, typename T>
+constexpr bool tip_bf16() {  // the split pays off over four column tiles, not one
+  return sizeof(T) == 4 && !AMB && Dim<NT>::NCT >= 4;
+}
+template <int NT, bool AMB, typename T>
 __device__ inline void grad_rows_tip(v4<T>* G, const T* __restrict__ tcol, const T* __restrict__ sCF,
-                                     const int* __restrict__ sCol, int K, int ct0, int g, int r,
+                                     const int* __restrict__ sCol, const T* __restrict__ sL, int K, int ct0, int g, int r,
                                      const uint64_t* __restrict__ amb) {
   EPOCH_DIMS(NT);
   constexpr int NCT = Dim<NT>::NCT;
-  if constexpr (sizeof(T) == 4 && !AMB && NCT >= 4) {  // the split pays off over four column tiles, not one
-    grad_rows_tip_bf16<NT>(G, tcol, sCF, sCol, K, ct0, g, r);
+  if constexpr (tip_bf16<NT, AMB, T>()) {
+    grad_rows_tip_bf16<NT>(G, tcol, sCF, sL, ct0, g, r);
     return;
   }
 #pragma unroll 8
@@ -453,28 +488,28 @@ __device__ inline void zero_unused_slot(const CodonProblem& pr, int child, int n
 template <typename T, int NT>
 struct PreTileLoads {
   v4<T> La[NT], Lb[NT];  // rows of 4 states of internal children's partials (child product A operand)
-  int cola[4], colb[4];
+  int sta[4], stb[4];    // tip states
 };
 
 template <int NT, typename T>
 __device__ inline void pre_load_tile(PreTileLoads<T, NT>& ld, const CodonProblem& pr, const T* La, const T* Lb, int a,
                                      int b, int p0, int g, int r) {
   EPOCH_DIMS(NT);
-  const int P = pr.P, K = pr.K;
+  const int P = pr.P;
   const int pa = min(p0 + r, P - 1);
   if (La) {
     const EPOCH_GLOBAL v4<T>* row = gptr(reinterpret_cast<const v4<T>*>(La + (size_t)pa * KP)) + g;
 #pragma unroll
     for (int t = 0; t < NT; ++t) ld.La[t] = row[4 * t];
   } else {
-    tip_columns<NT, T>(ld.cola, pr.tips + (size_t)a * pr.tip_stride, P, p0, K, g);
+    tip_states<NT, T>(ld.sta, pr.tips + (size_t)a * pr.tip_stride, P, p0, g);
   }
   if (Lb) {
     const EPOCH_GLOBAL v4<T>* row = gptr(reinterpret_cast<const v4<T>*>(Lb + (size_t)pa * KP)) + g;
 #pragma unroll
     for (int t = 0; t < NT; ++t) ld.Lb[t] = row[4 * t];
   } else {
-    tip_columns<NT, T>(ld.colb, pr.tips + (size_t)b * pr.tip_stride, P, p0, K, g);
+    tip_states<NT, T>(ld.stb, pr.tips + (size_t)b * pr.tip_stride, P, p0, g);
   }
 }
 
@@ -542,14 +577,17 @@ __global__ __launch_bounds__(256) void codon_post_level_kernel(const CodonProble
   }
   for (int p0 = base + WT * w; p0 < end; p0 += 4 * WT) {
     v4<T> Sa[NT], Sb[NT];
+    int cola[4], colb[4];
+    if (!La) tip_columns<NT>(cola, cur.sta, K);
+    if (!Lb) tip_columns<NT>(colb, cur.stb, K);
     if (La)
       child_gemm_regs<NT, T>(Sa, cur.La, sPa, g, r);
     else
-      tip_lookup<NT, AMB, T>(Sa, cur.cola, sPa, r, pr.amb);
+      tip_lookup<NT, AMB, T>(Sa, cola, sPa, r, pr.amb);
     if (Lb)
       child_gemm_regs<NT, T>(Sb, cur.Lb, sPb, g, r);
     else
-      tip_lookup<NT, AMB, T>(Sb, cur.colb, sPb, r, pr.amb);
+      tip_lookup<NT, AMB, T>(Sb, colb, sPb, r, pr.amb);
     int e[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -576,7 +614,7 @@ __global__ __launch_bounds__(256) void codon_post_level_kernel(const CodonProble
 
 
 template <typename T, int NT, bool AMB>
-__global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void codon_pre_level_kernel(
+__global__ __launch_bounds__(256, sizeof(T) == 4 || NT == 2 ? 2 : 1) void codon_pre_level_kernel(
     const CodonProblem* __restrict__ probs, const int4* __restrict__ items, int R) {
   EPOCH_DIMS(NT);
   constexpr int NCT = Dim<NT>::NCT;
@@ -646,14 +684,17 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void codon_pre_level_k
     for (int v = 0; v < 4; ++v) wts[v] = gptr(reinterpret_cast<const T*>(pr.weightsT))[min(p0 + drow<T>(g, v), P - 1)];
     // ---- this wavefront's 16 patterns: child vectors, q_u, w_p / L_p
     v4<T> Sa[NT], Sb[NT];
+    int cola[4], colb[4];
+    if (!La) tip_columns<NT>(cola, cur.sta, K);
+    if (!Lb) tip_columns<NT>(colb, cur.stb, K);
     if (La)
       child_gemm_regs<NT, T>(Sa, cur.La, sPa, g, r);
     else
-      tip_lookup<NT, AMB, T>(Sa, cur.cola, sPa, r, pr.amb);
+      tip_lookup<NT, AMB, T>(Sa, cola, sPa, r, pr.amb);
     if (Lb)
       child_gemm_regs<NT, T>(Sb, cur.Lb, sPb, g, r);
     else
-      tip_lookup<NT, AMB, T>(Sb, cur.colb, sPb, r, pr.amb);
+      tip_lookup<NT, AMB, T>(Sb, colb, sPb, r, pr.amb);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       T sum = 0;
@@ -663,8 +704,8 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void codon_pre_level_k
       const int p = p0 + drow<T>(g, v);
       if (r == 0) {
         sCF[WT * w + drow<T>(g, v)] = (p < P && sum > T(0)) ? wts[v] / sum : T(0);
-        if (!La) sCol[0][WT * w + drow<T>(g, v)] = cur.cola[v];
-        if (!Lb) sCol[1][WT * w + drow<T>(g, v)] = cur.colb[v];
+        if (!La) sCol[0][WT * w + drow<T>(g, v)] = cola[v];
+        if (!Lb) sCol[1][WT * w + drow<T>(g, v)] = colb[v];
       }
     }
     // loads of this wavefront's part of the next tile, in flight during the rest
@@ -686,6 +727,8 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void codon_pre_level_k
         const v4<T>* lr = side == 0 ? cur.La : cur.Lb;
 #pragma unroll
         for (int t = 0; t < NT; ++t) *reinterpret_cast<v4<T>*>(lrows + r * LDP + 16 * t + 4 * g) = lr[t];
+      } else if constexpr (tip_bf16<NT, AMB, T>()) {
+        stage_tip_indicator(sL, side == 0 ? cola : colb, K, w, lane);
       }
       wave_lds_sync();
       if (Lc) {
@@ -725,7 +768,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void codon_pre_level_k
       if (Lc)
         grad_rows_internal<NT, T>(G, tcol, sCF, sL, ct0, g, r);
       else
-        grad_rows_tip<NT, AMB, T>(G, tcol, sCF, sCol[side], K, ct0, g, r, pr.amb);
+        grad_rows_tip<NT, AMB, T>(G, tcol, sCF, sCol[side], sL, K, ct0, g, r, pr.amb);
     }
     __syncthreads();  // the next tile overwrites t, L, w_p / L_p and tip columns
     if (bt + 1 < n_tiles) cur = nxt;
@@ -763,7 +806,7 @@ struct PreSplitShared {
 struct SplitTileLoads {
   f4 L[4];  // 16-byte rows of this side's child partials (internal child)
   f4 Q[4];  // q_u in the D layout
-  int col[4];
+  int st[4];
 };
 
 __device__ inline void split_load_tile(SplitTileLoads& ld, const CodonProblem& pr, const float* Lc, const float* Qu,
@@ -774,7 +817,7 @@ __device__ inline void split_load_tile(SplitTileLoads& ld, const CodonProblem& p
 #pragma unroll
     for (int t = 0; t < 4; ++t) ld.L[t] = row[4 * t];
   } else {
-    tip_columns<4, float>(ld.col, pr.tips + (size_t)c * pr.tip_stride, P, p0, pr.K, g);
+    tip_states<4, float>(ld.st, pr.tips + (size_t)c * pr.tip_stride, P, p0, g);
   }
   if (Qu) load_dlayout<4, float>(ld.Q, Qu, P, p0, g, r);
 }
@@ -822,10 +865,12 @@ __global__ __launch_bounds__(512, 1) void codon_pre_split_kernel(const CodonProb
   for (int bt = 0; bt < n_tiles; ++bt) {
     const int p0 = base + bt * TILE + WT * w;
     f4 S[4];
+    int col[4];
+    if (!Lc) tip_columns<4>(col, cur.st, K);
     if (Lc)
       child_gemm_regs<4, float>(S, cur.L, sPc, g, r);
     else
-      tip_lookup<4, AMB, float>(S, cur.col, sPc, r, pr.amb);
+      tip_lookup<4, AMB, float>(S, col, sPc, r, pr.amb);
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
@@ -850,7 +895,7 @@ __global__ __launch_bounds__(512, 1) void codon_pre_split_kernel(const CodonProb
         const int p = p0 + 4 * g + v;
         if (r == 0) sh.sCF[WT * w + 4 * g + v] = (p < P && sum > 0.f) ? gptr(pr.weightsT)[p] / sum : 0.f;
       }
-      if (r == 0 && !Lc) sh.sCol[s][WT * w + 4 * g + v] = cur.col[v];
+      if (r == 0 && !Lc) sh.sCol[s][WT * w + 4 * g + v] = col[v];
     }
     if (bt + 1 < n_tiles) split_load_tile(nxt, pr, Lc, Qu, c, p0 + TILE, g, r);
 #pragma unroll
@@ -860,6 +905,8 @@ __global__ __launch_bounds__(512, 1) void codon_pre_split_kernel(const CodonProb
     if (Lc) {
 #pragma unroll
       for (int t = 0; t < 4; ++t) *reinterpret_cast<f4*>(lrows + r * LDP + 16 * t + 4 * g) = cur.L[t];
+    } else if constexpr (tip_bf16<4, AMB, float>()) {
+      stage_tip_indicator(sh.sL[s], col, K, w, lane);
     }
     wave_lds_sync();
     if (Lc) {
@@ -897,7 +944,7 @@ __global__ __launch_bounds__(512, 1) void codon_pre_split_kernel(const CodonProb
     if (Lc)
       grad_rows_internal<4, float>(G, tcol, sh.sCF, sh.sL[s], 0, g, r);
     else
-      grad_rows_tip<4, AMB, float>(G, tcol, sh.sCF, sh.sCol[s], K, 0, g, r, pr.amb);
+      grad_rows_tip<4, AMB, float>(G, tcol, sh.sCF, sh.sCol[s], sh.sL[s], K, 0, g, r, pr.amb);
     if (bt + 1 < n_tiles) cur = nxt;
   }
   EPOCH_GLOBAL float* dst = gptr(pr.Gpart + ((size_t)pr.gslots[pr.n_nodes + c] + blockIdx.x) * KK);

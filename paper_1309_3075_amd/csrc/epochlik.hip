@@ -250,23 +250,8 @@ void invalidate_downstream(EpochInstance* in) {
   in->logL_valid = false;
 }
 
-// Host-to-device copies of one set_epoch_eigensystems call, staged in the
-// instance's pinned host buffer and enqueued on its stream without waiting; the
-// next call waits for them (stage_event) before it reuses the buffer.
-struct EigStage {
-  EpochInstance* in;
-  size_t off = 0;
-  int rc = EPOCH_OK;
-  template <typename D>
-  void put(void* dst, const double* src, size_t n) {  // n doubles, copied as D
-    if (rc) return;
-    off = (off + 15) / 16 * 16;
-    D* h = reinterpret_cast<D*>(static_cast<char*>(in->stage_host) + off);
-    for (size_t i = 0; i < n; ++i) h[i] = (D)src[i];
-    rc = hip_check(hipMemcpyAsync(dst, h, n * sizeof(D), hipMemcpyHostToDevice, in->stream), "eigensystem upload");
-    off += n * sizeof(D);
-  }
-};
+// The instance's pinned staging buffer: what a setter hands over is copied there and read by work
+// enqueued on the instance's stream without waiting; the next use waits (stage_event) first.
 int stage_reserve(EpochInstance* in, size_t bytes) {
   if (in->stage_pending) {
     EPOCH_TRY(hip_check(hipEventSynchronize(in->stage_event), "eigensystem staging wait"));
@@ -403,7 +388,7 @@ int epoch_create(const EpochConfig* cfg, EpochInstance** out) {
   A(in->eig64, (2 * S * KK + 2 * S * Kp) * sizeof(double));
   A(in->eigTT, 2 * S * KK * R);
   A(in->eig64T, 2 * S * KK * sizeof(double));
-  A(in->check, (KK + 1 + 3 * (size_t)eigen_check_tiles(in->K)) * sizeof(double));  // Q, residual, tile maxima
+  A(in->check, (KK + 3 * (size_t)eigen_check_tiles(in->K)) * sizeof(double));  // Q, tile maxima
   A(in->tips, N * P);
   A(in->amb, 256 * sizeof(uint64_t));
   A(in->weights, P * sizeof(double));
@@ -718,63 +703,26 @@ int set_epoch_eigensystems(EpochInstance* in, int32_t s, const double* V, const 
     if (choose_eig_precision(in) || !in->have_eig[s]) mark_dirty_all(in);
     else mark_dirty_process(in, s);
   }
-  // this process's slices in double and in the compute type, and the transposed
-  // copies (rows of V^T and V^-T feed the adjoint chain), staged in pinned host
-  // memory and copied without waiting
-  const size_t R = in->real_size;
-  const size_t need = (2 * KK + 2 * Kp) * (8 + R) + 2 * KK * (8 + R) + (size_t)K * K * 8 + 16 * 16;
-  EPOCH_TRY(stage_reserve(in, need));
-  EigStage st{in};
-  auto slice = [&](DevBuf& buf, bool as_float) {
-    const size_t es = as_float ? sizeof(float) : sizeof(double);
-    char* base = static_cast<char*>(buf.ptr);
-    const double* src[4] = {hV, hVi, hr, hi};
-    const size_t off[4] = {s * KK, S * KK + s * KK, 2 * S * KK + (size_t)s * Kp, 2 * S * KK + S * Kp + (size_t)s * Kp};
-    const size_t cnt[4] = {KK, KK, (size_t)Kp, (size_t)Kp};
-    for (int k = 0; k < 4; ++k) {
-      if (as_float)
-        st.put<float>(base + off[k] * es, src[k], cnt[k]);
-      else
-        st.put<double>(base + off[k] * es, src[k], cnt[k]);
-    }
-  };
-  slice(in->eig64, false);
-  slice(in->eigT, !in->fp64);
-  {
-    std::vector<double> tV(KK), tVi(KK);
-    for (int i = 0; i < Kp; ++i)
-      for (int j = 0; j < Kp; ++j) {
-        tV[(size_t)j * Kp + i] = hV[(size_t)i * Kp + j];
-        tVi[(size_t)j * Kp + i] = hVi[(size_t)i * Kp + j];
-      }
-    char* b64 = static_cast<char*>(in->eig64T.ptr);
-    st.put<double>(b64 + s * KK * sizeof(double), tV.data(), KK);
-    st.put<double>(b64 + (S * KK + s * KK) * sizeof(double), tVi.data(), KK);
-    char* bT = static_cast<char*>(in->eigTT.ptr);
-    if (in->fp64) {
-      st.put<double>(bT + s * KK * 8, tV.data(), KK);
-      st.put<double>(bT + (S * KK + s * KK) * 8, tVi.data(), KK);
-    } else {
-      st.put<float>(bT + s * KK * 4, tV.data(), KK);
-      st.put<float>(bT + (S * KK + s * KK) * 4, tVi.data(), KK);
-    }
-  }
-  double* dQ = static_cast<double*>(in->check.ptr);
-  if (Q) st.put<double>(dQ, Q, (size_t)K * K);
-  if (st.rc) {  // copies enqueued before the failure may still read the staging buffer
-    (void)hipStreamSynchronize(in->stream);
-    return st.rc;
-  }
+  // staged as [V][V^-1][lambda_re][lambda_im][Q] in pinned host memory; one launch reads it there and
+  // writes this process's slices of every device copy, and the check's result comes back the same way
+  const size_t nq = Q ? (size_t)K * K : 0;
+  EPOCH_TRY(stage_reserve(in, (2 * KK + 2 * Kp + (size_t)K * K) * sizeof(double)));
+  double* h = static_cast<double*>(in->stage_host);
+  std::copy(hV, hV + KK, h);
+  std::copy(hVi, hVi + KK, h + KK);
+  std::copy(hr, hr + Kp, h + 2 * KK);
+  std::copy(hi, hi + Kp, h + 2 * KK + Kp);
+  if (Q) std::copy(Q, Q + nq, h + 2 * KK + 2 * Kp);
+  EPOCH_TRY(launch_eigen_store(in, s, h, nq));
   EPOCH_TRY(hip_check(hipEventRecord(in->stage_event, in->stream), "eigensystem upload event"));
   in->stage_pending = in->async_pending = true;
   in->have_eig[s] = 1;
   invalidate_downstream(in);
   int ret = EPOCH_OK;
   if (Q) {
-    double* dout = dQ + (size_t)Kp * Kp;
-    EPOCH_TRY(launch_eigen_check(in, s, dQ, dout));
-    double res = 0.0;
-    EPOCH_TRY(download(in, &res, dout, sizeof(res)));
+    EPOCH_TRY(launch_eigen_check(in, s, static_cast<const double*>(in->check.ptr), in->host_out));
+    EPOCH_TRY(hip_check(hipStreamSynchronize(in->stream), "eigensystem check sync"));
+    const double res = in->host_out[0];
     if (residual_out) *residual_out = res;
     if (!(res <= 1e-8)) {
       set_error(EPOCH_WARN_EIGEN_RESIDUAL, "eigensystem %d reconstruction residual %.3g", s, res);

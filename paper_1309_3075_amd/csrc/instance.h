@@ -280,7 +280,7 @@ struct EpochInstance {
   // per-phase timing (epoch_set_timing)
   bool timing = false;
   hipEvent_t ev[EPOCH_N_PHASES][2] = {};
-  // pinned staging of set_epoch_eigensystems' copies (enqueued without waiting)
+  // pinned staging of what the setters hand over (read by work enqueued without waiting)
   void* stage_host = nullptr;
   size_t stage_bytes = 0;
   hipEvent_t stage_event = nullptr;
@@ -324,8 +324,12 @@ int stage_upload(EpochInstance* in, void* dst, const void* src, size_t bytes);
 constexpr int kInlineRates = 64;  // branch rates epoch_set_branch_rates passes in a launch's arguments
 
 // kernel launchers (kernels_generic.hip); all return EPOCH_OK or an error code
-// FP64 eigensystem check (kernels_eigcheck.hip): d_out[0] receives the residual, scratch follows it
-int launch_eigen_check(EpochInstance* in, int s, const double* dQ, double* d_out);
+// every device copy of process s's eigensystem (and Q, n_q doubles) from the staged
+// [V][V^-1][lambda_re][lambda_im][Q] (kernels_eigcheck.hip)
+int launch_eigen_store(EpochInstance* in, int s, const double* staged, size_t n_q);
+// FP64 eigensystem check (kernels_eigcheck.hip): out[0], device or pinned host memory, receives the
+// residual; the tile maxima lie behind Q in the check buffer
+int launch_eigen_check(EpochInstance* in, int s, const double* dQ, double* out);
 int eigen_check_tiles(int K);  // scratch rows (3 doubles each) per system
 int launch_q_reconstruct(EpochInstance* in, double* d_Q, double* part);  // Q_s = V B V^-1, FP64 [S][Kp][Kp]
 // node-height and boundary gradients (kernels_tgrad.hip)

@@ -9,7 +9,7 @@
 // A block forms one 16 x 16 tile of R and E for one system from LDS-staged
 // tiles of V B, V and V^-1 (the contraction runs over the states in order)
 // and writes the tile's three maxima to a scratch row; a second launch folds
-// each system's tiles.  Maxima do not round, so the result does not depend on
+// each system's tiles, a wavefront to a system.  Maxima do not round, so the result does not depend on
 // the tiling.
 #include <hip/hip_runtime.h>
 
@@ -96,17 +96,56 @@ __global__ __launch_bounds__(256) void eigen_check_tile_kernel(const double* __r
   }
 }
 
-__global__ __launch_bounds__(256) void eigen_check_finish_kernel(const double* __restrict__ part, int tiles, int n,
-                                                                 double* __restrict__ out) {
-  for (int s = blockIdx.x * 256 + threadIdx.x; s < n; s += 256 * gridDim.x) {
-    double r1 = 0.0, r2 = 0.0, qm = 0.0;
-    for (int t = 0; t < tiles; ++t) {
-      const double* p = part + ((long)s * tiles + t) * 3;
-      r1 = fmax(r1, p[0]);
-      r2 = fmax(r2, p[1]);
-      qm = fmax(qm, p[2]);
-    }
-    out[s] = fmax(qm > 0.0 ? r1 / qm : r1, r2);
+// A wavefront per system; its lanes share the tiles.
+__global__ __launch_bounds__(64) void eigen_check_finish_kernel(const double* __restrict__ part, int tiles,
+                                                                double* __restrict__ out) {
+  const int s = blockIdx.x;
+  double m[3] = {0.0, 0.0, 0.0};
+  for (int t = threadIdx.x; t < tiles; t += 64)
+    for (int q = 0; q < 3; ++q) m[q] = fmax(m[q], part[((long)s * tiles + t) * 3 + q]);
+  for (int off = 32; off > 0; off >>= 1)
+    for (int q = 0; q < 3; ++q) m[q] = fmax(m[q], __shfl_xor(m[q], off, 64));
+  if (threadIdx.x == 0) out[s] = fmax(m[2] > 0.0 ? m[0] / m[2] : m[0], m[1]);
+}
+
+// Process s's eigensystem into the device copies: FP64 and compute type, as handed over and
+// transposed (rows of V^T and V^-T feed the adjoint chain).  The source is the pinned host buffer
+// it was staged in: some 100 KB at 64 states, read over the bus by all threads at once in one
+// round trip, where a copy per destination (12 of them) cost a call and a transfer each.  With the
+// check's result written to host memory, handing over a checked 61-state eigensystem takes
+// 55 instead of 185 us.
+struct EigenStoreArgs {
+  const double* src;          // [V][V^-1][lambda_re][lambda_im][Q]
+  double *v64, *l64, *t64;    // process s's slices: V (V^-1 at +SKK), lambda_re (lambda_im at +SKp), V^T
+  void *vT, *lT, *tT;         // the same in the compute type
+  double* q;                  // Q, n_q doubles
+  long SKK;
+  int Kp, SKp, n_q;
+};
+template <typename T>
+__global__ __launch_bounds__(256) void eigen_store_kernel(const EigenStoreArgs a) {
+  const int KK = a.Kp * a.Kp;
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  if (e < a.n_q) a.q[e] = a.src[2 * KK + 2 * a.Kp + e];
+  if (e >= KK) return;
+  const double v = a.src[e], vi = a.src[KK + e];
+  const int i = e / a.Kp, j = e % a.Kp, t = j * a.Kp + i;
+  a.v64[e] = v;
+  a.v64[a.SKK + e] = vi;
+  a.t64[t] = v;
+  a.t64[a.SKK + t] = vi;
+  T* vT = static_cast<T*>(a.vT);
+  T* tT = static_cast<T*>(a.tT);
+  vT[e] = T(v);
+  vT[a.SKK + e] = T(vi);
+  tT[t] = T(v);
+  tT[a.SKK + t] = T(vi);
+  if (e < a.Kp) {
+    const double lr = a.src[2 * KK + e], li = a.src[2 * KK + a.Kp + e];
+    a.l64[e] = lr;
+    a.l64[a.SKp + e] = li;
+    static_cast<T*>(a.lT)[e] = T(lr);
+    static_cast<T*>(a.lT)[a.SKp + e] = T(li);
   }
 }
 
@@ -125,7 +164,7 @@ int launch_eigen_check_n(hipStream_t st, int K, int n, int ld, long mat_stride, 
                      vec_stride, part, nullptr);
   int rc = hip_check(hipGetLastError(), "eigen check launch");
   if (rc) return rc;
-  hipLaunchKernelGGL(eigen_check_finish_kernel, dim3((n + 255) / 256), dim3(256), 0, st, part, tiles, n, out);
+  hipLaunchKernelGGL(eigen_check_finish_kernel, dim3(n), dim3(64), 0, st, part, tiles, out);
   return hip_check(hipGetLastError(), "eigen check finish launch");
 }
 
@@ -140,15 +179,39 @@ int launch_q_reconstruct(EpochInstance* in, double* d_Q, double* part) {
   return hip_check(hipGetLastError(), "Q reconstruction launch");
 }
 
-int launch_eigen_check(EpochInstance* in, int s, const double* dQ, double* d_out) {
-  // the instance's FP64 eigensystem slices (padded, device column order); scratch follows the output
+int launch_eigen_store(EpochInstance* in, int s, const double* staged, size_t n_q) {
+  const size_t KK = (size_t)in->Kp * in->Kp, Kp = in->Kp, S = in->S, R = in->real_size;
+  EigenStoreArgs a{};
+  a.src = staged;
+  a.SKK = (long)(S * KK);
+  a.Kp = in->Kp;
+  a.SKp = (int)(S * Kp);
+  a.n_q = (int)n_q;
+  a.q = static_cast<double*>(in->check.ptr);
+  a.v64 = static_cast<double*>(in->eig64.ptr) + s * KK;
+  a.l64 = static_cast<double*>(in->eig64.ptr) + 2 * S * KK + s * Kp;
+  a.t64 = static_cast<double*>(in->eig64T.ptr) + s * KK;
+  a.vT = static_cast<char*>(in->eigT.ptr) + s * KK * R;
+  a.lT = static_cast<char*>(in->eigT.ptr) + (2 * S * KK + s * Kp) * R;
+  a.tT = static_cast<char*>(in->eigTT.ptr) + s * KK * R;
+  const dim3 grid((unsigned)((KK + 255) / 256)), block(256);
+  if (in->fp64)
+    hipLaunchKernelGGL(eigen_store_kernel<double>, grid, block, 0, in->stream, a);
+  else
+    hipLaunchKernelGGL(eigen_store_kernel<float>, grid, block, 0, in->stream, a);
+  return hip_check(hipGetLastError(), "eigensystem store launch");
+}
+
+int launch_eigen_check(EpochInstance* in, int s, const double* dQ, double* out) {
+  // the instance's FP64 eigensystem slices (padded, device column order); scratch behind Q
   const size_t KK = (size_t)in->Kp * in->Kp;
   const double* base = static_cast<const double*>(in->eig64.ptr);
   const double* V = base + s * KK;
   const double* Vi = base + in->S * KK + s * KK;
   const double* lr = base + 2 * in->S * KK + (size_t)s * in->Kp;
   const double* li = base + 2 * in->S * KK + (size_t)in->S * in->Kp + (size_t)s * in->Kp;
-  return launch_eigen_check_n(in->stream, in->K, 1, in->Kp, (long)KK, in->Kp, V, Vi, lr, li, dQ, d_out + 1, d_out);
+  return launch_eigen_check_n(in->stream, in->K, 1, in->Kp, (long)KK, in->Kp, V, Vi, lr, li, dQ,
+                              static_cast<double*>(in->check.ptr) + KK, out);
 }
 
 // ---- The check without allocation (epoch_eigen_residual_noalloc) ---------------------------

@@ -40,7 +40,9 @@ def eigensystem(Q: np.ndarray, pi: Optional[np.ndarray] = None) -> Eigensystem:
         lam, U = linalg.eigh(S)
         V = U / d[:, None]
         Vinv = U.T * d[None, :]
-        return Eigensystem(V, Vinv, lam, np.zeros(K), float(np.linalg.cond(V)))
+        # U is orthogonal, so V = D^-1/2 U has the singular values 1/sqrt(pi): no decomposition
+        # (an SVD of V took 130 of the 440 us of a 61-state call)
+        return Eigensystem(V, Vinv, lam, np.zeros(K), float(d.max() / d.min()))
     wr, vr = linalg.eig(Q)
     lam_re = np.empty(K)
     lam_im = np.zeros(K)

@@ -389,11 +389,12 @@ __global__ __launch_bounds__(256) void qgrad_chain_kernel(
 
   // tau and e^{tau lambda} of every segment term, for the divided differences of the sums;
   // the forward products A_k V were stored by the P stage
-  for (int k = k0; k < k1; ++k) {
+  // (the wavefronts take the segments in turn: exp, cos and sin in FP64 are some hundred instructions)
+  for (int k = k0 + w; k < k1; k += NT) {
     const int s = seg_process[seg0 + k];
     const double tau_d = scale * seg_time[seg0 + k];
-    if (threadIdx.x == 0) qtau[(size_t)(seg0 + k) * C + c] = tau_d;
-    if (w == 0 && lane < Kp) {
+    if (lane == 0) qtau[(size_t)(seg0 + k) * C + c] = tau_d;
+    if (lane < Kp) {
       const double ea = exp(tau_d * lr64[(size_t)s * Kp + lane]);
       const double th = tau_d * li64[(size_t)s * Kp + lane];
       reinterpret_cast<double2*>(qexp)[((size_t)(seg0 + k) * C + c) * Kp + lane] = make_double2(ea * cos(th), ea * sin(th));
@@ -505,27 +506,117 @@ __global__ __launch_bounds__(256) void qgrad_chain_kernel(
 
 // (e^{x_a} - e^{x_b}) / (x_a - x_b) from E_a = e^{x_a}, E_b = e^{x_b} and
 // d = x_a - x_b: the quotient where |d| is large, E_b (e^d - 1)/d by its Taylor
-// series where it is small (no cancellation; exact limit E_b at d = 0).
+// series where it is small (no cancellation; exact limit E_b at d = 0).  The
+// series sum_k d^k / (k+1)! runs through d^12 / 13!: the remainder is below
+// 0.25^13 / 14! ~ 2e-19.  At a complex d the polynomial, whose coefficients are
+// real, is divided by x^2 - 2 Re(d) x + |d|^2: two real FMAs a term where
+// Horner's rule takes four.
+constexpr int kSeriesTerms = 12;
+constexpr double series_coef(int k) {  // 1 / (k + 1)!
+  double f = 1.0;
+  for (int i = 2; i <= k + 1; ++i) f *= (double)i;
+  return 1.0 / f;
+}
+__device__ inline double divided_difference_from_exp(double Ea, double Eb, double d) {
+  if (fabs(d) > 0.25) return (Ea - Eb) / d;
+  double s = series_coef(kSeriesTerms);
+#pragma unroll
+  for (int k = kSeriesTerms - 1; k >= 0; --k) s = __builtin_fma(s, d, series_coef(k));
+  return Eb * s;
+}
 __device__ inline cplx divided_difference_from_exp(cplx Ea, cplx Eb, cplx d) {
   const double ad = fabs(d.re) + fabs(d.im);
   if (ad > 0.25) return cdiv(cplx{Ea.re - Eb.re, Ea.im - Eb.im}, d);
-  // (e^d - 1)/d = sum_{k>=0} d^k / (k+1)! = 1 + d/2 (1 + d/3 (1 + ... (1 + d/15))),
-  // terms through d^14/15!: the remainder is below 0.25^15 / 16! ~ 4e-23.  Each
-  // step multiplies by the correctly rounded constant 1/k (no division).
-  cplx s = {1.0, 0.0};
+  const double r = 2.0 * d.re, m = -(d.re * d.re + d.im * d.im);
+  double b1 = 0.0, b2 = 0.0;  // the quotient's last two coefficients
 #pragma unroll
-  for (int k = 15; k >= 2; --k) {
-    constexpr double one = 1.0;
-    const double inv_k = one / (double)k;  // folded to a constant once the loop is unrolled
-    s = cmul(s, d);
-    s.re = 1.0 + s.re * inv_k;
-    s.im = s.im * inv_k;
+  for (int k = kSeriesTerms; k >= 1; --k) {
+    const double b = __builtin_fma(r, b1, __builtin_fma(m, b2, series_coef(k)));
+    b2 = b1;
+    b1 = b;
   }
-  return cmul(Eb, s);
+  // remainder: b1 d + (c_0 - |d|^2 b2)
+  const double q = __builtin_fma(b1, d.re, m * b2);  // small beside 1: one rounding at 1, as with Horner's rule
+  return cmul(Eb, cplx{1.0 + q, b1 * d.im});
 }
 
 // H_s partial sums: for every segment term of process s in this block's chunk,
 // tau Phi(tau lambda) o (T^T Y T^-T) in FP64 complex, one entry per thread.
+// FP64 arithmetic and the latency of a term's loads bound it: the loads of four
+// terms are in flight together (a pair's two rows and columns are read by every
+// thread, those of a real eigenvalue twice, so that no load sits in a branch),
+// and a system whose eigenvalues are all real (the pairs stand first) takes the
+// real forms: 61 states, 254 branches: 37 -> 10 us; 40 states, half of them pairs, 4,333 terms: 97 -> 54 us
+// (its 80 MB of Y take 20 us).
+template <bool CPLX>
+__device__ inline void h_accumulate(int Kp, int a, int b, const double* __restrict__ lr, const double* __restrict__ li,
+                                    const int32_t* __restrict__ list, int q0, int q1,
+                                    const double* __restrict__ Yseg, const double* __restrict__ qtau,
+                                    const double2* __restrict__ E, double& re, double& im) {
+  constexpr int U = 4, NY = CPLX ? 2 : 1;
+  const int KK = Kp * Kp;
+  int at[NY][NY];
+  cplx tt[NY][NY];
+  if constexpr (CPLX) {
+    const PairIdx pa = pair_of(li, a), pb = pair_of(li, b);
+#pragma unroll
+    for (int ci = 0; ci < 2; ++ci)
+#pragma unroll
+      for (int di = 0; di < 2; ++di) {
+        const int i = pa.pair ? pa.first + ci : a, j = pb.pair ? pb.first + di : b;
+        at[ci][di] = i * Kp + j;
+        tt[ci][di] = cmul(T_entry(i, a, pa.first, pa.pair), Tinv_entry(b, j, pb.first, pb.pair));
+        if ((ci && !pa.pair) || (di && !pb.pair)) tt[ci][di] = {0.0, 0.0};
+      }
+  } else {
+    at[0][0] = a * Kp + b;
+  }
+  const cplx dl = {lr[a] - lr[b], CPLX ? li[a] - li[b] : 0.0};
+  double tau[U], y[U][NY][NY];
+  double2 ea[U], eb[U];
+  auto load = [&](int u, int qi) {
+    const int item = list[qi];
+    const double* Y = Yseg + (size_t)item * KK;
+    tau[u] = qtau[item];
+    ea[u] = E[(size_t)item * Kp + a];
+    eb[u] = E[(size_t)item * Kp + b];
+#pragma unroll
+    for (int ci = 0; ci < NY; ++ci)
+#pragma unroll
+      for (int di = 0; di < NY; ++di) y[u][ci][di] = Y[at[ci][di]];
+  };
+  auto add = [&](int u) {
+    if constexpr (CPLX) {
+      cplx z = {0.0, 0.0};
+#pragma unroll
+      for (int ci = 0; ci < 2; ++ci)
+#pragma unroll
+        for (int di = 0; di < 2; ++di) {
+          z.re += tt[ci][di].re * y[u][ci][di];
+          z.im += tt[ci][di].im * y[u][ci][di];
+        }
+      const cplx phi = divided_difference_from_exp(cplx{ea[u].x, ea[u].y}, cplx{eb[u].x, eb[u].y},
+                                                   cplx{tau[u] * dl.re, tau[u] * dl.im});
+      const cplx wv = cmul(phi, z);
+      re += tau[u] * wv.re;
+      im += tau[u] * wv.im;
+    } else {
+      re += tau[u] * (divided_difference_from_exp(ea[u].x, eb[u].x, tau[u] * dl.re) * y[u][0][0]);
+    }
+  };
+  int qi = q0;
+  for (; qi + U <= q1; qi += U) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) load(u, qi + u);
+#pragma unroll
+    for (int u = 0; u < U; ++u) add(u);
+  }
+  for (; qi < q1; ++qi) {
+    load(0, qi);
+    add(0);
+  }
+}
+
 __global__ __launch_bounds__(256) void qgrad_h_kernel(int Kp, int n_chunks, int chunk,
                                                       const int32_t* __restrict__ list_off,
                                                       const int32_t* __restrict__ list, const double* __restrict__ Yseg,
@@ -539,35 +630,14 @@ __global__ __launch_bounds__(256) void qgrad_h_kernel(int Kp, int n_chunks, int 
   const int a = e / Kp, b = e - (e / Kp) * Kp;
   const double* lr = lr_all + (size_t)s * Kp;
   const double* li = li_all + (size_t)s * Kp;
-  const PairIdx pa = pair_of(li, a), pb = pair_of(li, b);
-  const int na = pa.pair ? 2 : 1, nb = pb.pair ? 2 : 1;
-  cplx tt[2][2];
-  for (int ci = 0; ci < na; ++ci)
-    for (int di = 0; di < nb; ++di)
-      tt[ci][di] = cmul(T_entry(pa.first + ci, a, pa.first, pa.pair), Tinv_entry(b, pb.first + di, pb.first, pb.pair));
-  const cplx dl = {lr[a] - lr[b], li[a] - li[b]};
   const int q0 = list_off[s] + ch * chunk;
   const int q1 = min(list_off[s + 1], q0 + chunk);
-  double re = 0.0, im = 0.0;
   const double2* E = reinterpret_cast<const double2*>(qexp);
-#pragma unroll 4
-  for (int qi = q0; qi < q1; ++qi) {
-    const int item = list[qi];
-    const double tau = qtau[item];
-    const double* Y = Yseg + (size_t)item * KK;
-    cplx z = {0.0, 0.0};
-    for (int ci = 0; ci < na; ++ci)
-      for (int di = 0; di < nb; ++di) {
-        const double yv = Y[(pa.first + ci) * Kp + pb.first + di];
-        z.re += tt[ci][di].re * yv;
-        z.im += tt[ci][di].im * yv;
-      }
-    const double2 ea = E[(size_t)item * Kp + a], eb = E[(size_t)item * Kp + b];
-    const cplx phi = divided_difference_from_exp(cplx{ea.x, ea.y}, cplx{eb.x, eb.y}, cplx{tau * dl.re, tau * dl.im});
-    const cplx wv = cmul(phi, z);
-    re += tau * wv.re;
-    im += tau * wv.im;
-  }
+  double re = 0.0, im = 0.0;
+  if (li[0] == 0.0)
+    h_accumulate<false>(Kp, a, b, lr, li, list, q0, q1, Yseg, qtau, E, re, im);
+  else
+    h_accumulate<true>(Kp, a, b, lr, li, list, q0, q1, Yseg, qtau, E, re, im);
   reinterpret_cast<double2*>(Hpart)[((size_t)s * n_chunks + ch) * KK + e] = make_double2(re, im);
 }
 

@@ -99,9 +99,18 @@ __device__ inline void pstage_stripe(const PStageDesc& pd, int gw, ColCoef<T>* c
     }
   };
   T av[2][4][NT], ai[2][4][NT];
+  // The first segment's X is I and its D is 0, so X V is V itself (this stripe's rows) and D V is 0:
+  // no first product.  Most branches lie within one interval, and half their arithmetic goes with it.
+  acc y[NB][NT];
   if (k1 > k0) {
+    const T* V0 = eigV + (size_t)seg_process[seg0 + k0] * KK + (size_t)row * Kp + 4 * g;
+#pragma unroll
+    for (int mt = 0; mt < NT; ++mt) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) y[0][mt][q] = V0[16 * mt + q];
+      if (GRAD) y[NB - 1][mt] = acc{0, 0, 0, 0};
+    }
     make_coef(k0, coef + 64 * (k0 & 1));
-    stripe_load<T, NT>(eigV + (size_t)seg_process[seg0 + k0] * KK, 0, g, arow, av[0]);
   }
   for (int k = k0; k < k1; ++k) {
     const int s = seg_process[seg0 + k];
@@ -109,20 +118,20 @@ __device__ inline void pstage_stripe(const PStageDesc& pd, int gw, ColCoef<T>* c
     wave_lds_sync();  // segment k's coefficients are in LDS
     stripe_load<T, NT>(eigVi + (size_t)s * KK, 0, g, arow, ai[0]);
 
-    // Y^T = V^T X^T (and V^T D^T)
-    acc y[NB][NT];
+    if (k > k0) {  // Y^T = V^T X^T (and V^T D^T)
 #pragma unroll
-    for (int b = 0; b < NB; ++b)
+      for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int mt = 0; mt < NT; ++mt) y[b][mt] = acc{0, 0, 0, 0};
-    stripe_gemm_from<T, NT, NB>(eigV + (size_t)s * KK, g, arow, av, xd, y);
+        for (int mt = 0; mt < NT; ++mt) y[b][mt] = acc{0, 0, 0, 0};
+      stripe_gemm_from<T, NT, NB>(eigV + (size_t)s * KK, g, arow, av, xd, y);
+    }
     if (k + 1 < k1) {
       make_coef(k + 1, coef + 64 * ((k + 1) & 1));
       stripe_load<T, NT>(eigV + (size_t)seg_process[seg0 + k + 1] * KK, 0, g, arow, av[0]);
     }
-    if (pd.Ubuf) {
+    if (pd.Ubuf && k > 0) {
       // A_k V (the running product times V before the column operator), the forward
-      // half of the dlogL/dQ adjoint chain
+      // half of the dlogL/dQ adjoint chain, which takes A_0 V from V itself
       T* U = static_cast<T*>(pd.Ubuf) + ((size_t)(seg0 + k) * C + c) * KK + (size_t)row * Kp + 4 * g;
 #pragma unroll
       for (int mt = 0; mt < NT; ++mt) store4<T, T>(U + 16 * mt, y[0][mt]);

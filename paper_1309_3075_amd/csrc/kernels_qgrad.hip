@@ -353,7 +353,7 @@ __global__ __launch_bounds__(256) void qgrad_reduce_kernel(
 //   Y_k = V_s^T G_k V_s^-T = U_k^T W_k.
 // One block per (branch, category), one wavefront per 16-row stripe.  The
 // forward chain is the P stage's: it stores U_k = A_k V (its first product of
-// each step) in a global scratch buffer.  The backward chain
+// each step past the first, where U_0 = V) in a global scratch buffer.  The backward chain
 // R_{k-1} = R_k + (W_k (E_k - I)^T) V^T keeps its stripes in registers (the
 // layout of the P-stage kernel); Y_k contracts over all rows, so U_k and W_k
 // meet in LDS and each wavefront writes 16 rows of Y_k.  The transposed factors V^T and
@@ -432,7 +432,9 @@ __global__ __launch_bounds__(256) void qgrad_chain_kernel(
     }
   };
   auto load_u = [&](int k, T (&u)[NT][4]) {
-    const T* U = Ubuf + ((size_t)(seg0 + k) * C + c) * KK + (size_t)row * Kp + 4 * g;
+    // A_0 V is V: the P stage stores the products from segment 1 on
+    const T* U = (k > 0 ? Ubuf + ((size_t)(seg0 + k) * C + c) * KK : eigV + (size_t)seg_process[seg0] * KK) +
+                 (size_t)row * Kp + 4 * g;
 #pragma unroll
     for (int mt = 0; mt < NT; ++mt)
 #pragma unroll

@@ -735,9 +735,26 @@ int set_epoch_eigensystems(EpochInstance* in, int32_t s, const double* V, const 
 }
 
 namespace {
+// The shortest chain that is cut, unless the caller chose one.  A chain's segments run one after the
+// other, so the longest uncut chain bounds the launch from below, some 5 us a segment at 40 states;
+// cutting costs the combination's products.  A launch whose wavefronts fill the SIMDs many times over
+// (NT = 4 kernels hold one wavefront each, the smaller ones two) hides a chain of about as many
+// segments as it has rounds, so the line is that number, between 8 and 16.  Measured in FP64 with dlogL/dQ,
+// 40 states, 48 intervals, 500 taxa (1 round): 425 us at 8 and 510 at 16; in an instance that formed the
+// products in FP64 for FP32, 2,000 taxa: 40 states (6 rounds) 558 and 608, 20 states (4) 484 and 529,
+// 56 states (17) 1,193 and 1,164.  An FP32 instance keeps 16 all the same: cutting rounds differently,
+// and the last bits of the FP32 P show it in the results.
+int chain_split_line(const EpochInstance* in, int64_t n_seg) {
+  if (in->chain_split_min >= 0) return in->chain_split_min;
+  if (!in->fp64) return 16;
+  const int nt = in->Kp / 16;
+  const int64_t rounds = n_seg * in->C * nt / (1024 * (nt >= 4 ? 1 : 2));
+  return (int)std::min<int64_t>(16, std::max<int64_t>(8, rounds));
+}
+
 // Work items of the matrix-core chain kernels (P stage, dlogL/dQ chain): one per
 // node, longest segment chain first; and the same with every chain of at least
-// chain_split_min segments cut into J parts of about max(4, chain_split_min / 2)
+// chain_split_line segments cut into J parts of about max(4, half of that)
 // segments (at most kChainMaxParts), which run in parallel and are combined
 // afterwards.
 int build_chain_items(EpochInstance* in, const std::vector<int32_t>& off) {  // off: the tree's segment offsets
@@ -748,12 +765,13 @@ int build_chain_items(EpochInstance* in, const std::vector<int32_t>& off) {  // 
                    [&](int32_t a, int32_t b) { return off[a + 1] - off[a] > off[b + 1] - off[b]; });
   std::vector<int4> whole, split, info;
   int max_tail = 0;
-  const int part_len = std::max(4, in->chain_split_min / 2);
+  const int line = chain_split_line(in, off[n]);
+  const int part_len = std::max(4, line / 2);
   for (int v : order) {
     const int m = off[v + 1] - off[v];
     whole.push_back(make_int4(v, 0, m, 0));
     const int J = std::min(kChainMaxParts, (m + part_len - 1) / part_len);
-    if (in->chain_split_min > 0 && m >= in->chain_split_min && J >= 2) {
+    if (line > 0 && m >= line && J >= 2) {
       // J parts [j m / J, (j + 1) m / J); info word: kind 1 | part << 2 | parts << 5 | slot << 9
       const int slot = (int)info.size();
       for (int p = 0; p < J; ++p)

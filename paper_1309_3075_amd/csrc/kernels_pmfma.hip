@@ -305,7 +305,7 @@ __global__ __launch_bounds__(256) void pstage_tail_fix_kernel(PStageDesc pd, con
 
 // One problem (descriptor passed by value).
 template <typename T, typename TO, bool GRAD, int NT>
-__global__ __launch_bounds__(256) void pstage_mfma_kernel(PStageDesc pd) {
+__global__ __launch_bounds__(256, (GRAD && NT == 4 && sizeof(T) == 8 ? 1 : 2)) void pstage_mfma_kernel(PStageDesc pd) {
   __shared__ ColCoef<T> s_coef[4][2 * 64];
   const int wave = threadIdx.x >> 6;
   pstage_stripe<T, TO, GRAD, NT>(pd, blockIdx.x * 4 + wave, s_coef[wave]);
@@ -313,7 +313,7 @@ __global__ __launch_bounds__(256) void pstage_mfma_kernel(PStageDesc pd) {
 
 // Several problems of one batch in one launch: blockIdx.y selects the problem.
 template <typename T, typename TO, bool GRAD, int NT>
-__global__ __launch_bounds__(256) void pstage_mfma_multi_kernel(const PStageDesc* __restrict__ descs) {
+__global__ __launch_bounds__(256, (GRAD && NT == 4 && sizeof(T) == 8 ? 1 : 2)) void pstage_mfma_multi_kernel(const PStageDesc* __restrict__ descs) {
   __shared__ ColCoef<T> s_coef[4][2 * 64];
   const int wave = threadIdx.x >> 6;
   const PStageDesc pd = descs[blockIdx.y];

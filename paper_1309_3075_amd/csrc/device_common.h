@@ -99,4 +99,12 @@ __device__ inline void sum_blocks_in_last(double block_total, double* slots, int
   }
 }
 
+// Barrier of a run between its levels: what its wavefronts exchange is in LDS, so the loads ahead and
+// the stores of results stay in flight (a __syncthreads waits for them).
+__device__ inline void lds_barrier() {
+  __asm__ volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  __asm__ volatile("" ::: "memory");
+}
+
 }  // namespace epochlik

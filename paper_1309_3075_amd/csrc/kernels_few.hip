@@ -40,14 +40,6 @@ __device__ inline void wave_lds_order() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Barrier of a run between its levels: what its wavefronts exchange is in LDS, so the loads ahead and
-// the stores of results stay in flight (a __syncthreads waits for them).
-__device__ inline void lds_barrier() {
-  __asm__ volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  __asm__ volatile("" ::: "memory");
-}
-
 // One matrix of an item, loaded a level ahead.  Up to 32 states a lane holds its own row or column;
 // from 33 on (an item is a whole wavefront) the wavefront loads the matrix in consecutive 16-byte
 // pieces and passes it through an LDS buffer with padded rows, because a row per lane touches 64

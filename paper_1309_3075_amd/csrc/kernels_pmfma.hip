@@ -8,9 +8,9 @@
 //   X <- X + ((X V)(E_k - I)) V^-1,
 //   D <- D + ((D V)(E_k - I) + (X V) dE_k) V^-1,   dE_k = dtau_k/dl * dE/dtau.
 // Rows of P are independent through the whole chain, so one wavefront carries
-// a 16-row stripe of one (branch, category) product from the identity to the
-// end, entirely in registers: the kernel has no barriers and no LDS traffic
-// apart from a per-wave table of column coefficients.
+// a 16-row stripe of one (branch, category) product, and of its derivative, from
+// the identity to the end in registers; LDS holds a per-wave table of column
+// coefficients (and what a derivative carried apart reads).
 //
 // Layout.  The wave holds the stripe transposed, X^T (Kp x 16), as Kp/16
 // accumulator tiles of v_mfma_*_16x16x4: lane (g = lane / 16, n = lane % 16)
@@ -42,16 +42,34 @@ __device__ inline T* chain_mat(void* scratch, int slot, int C, int c, int part, 
   return static_cast<T*>(scratch) + ((((size_t)slot * C + c) * kChainMaxParts + part) * 5 + which) * KK;
 }
 
-// One wavefront = one 16-row stripe of one (work item, category) of one
-// problem.  A work item is a node's whole chain, or the head or tail half of a
-// long one (written to scratch for pstage_combine_kernel).
-template <typename T, typename TO, bool GRAD, int NT>
-__device__ inline void pstage_stripe(const PStageDesc& pd, int gw, ColCoef<T>* coef) {
+// A unit is one 16-row stripe of one (work item, category) of one problem.  A
+// work item is a node's whole chain, or a part of a long one (written to scratch
+// for pstage_combine_kernel).  With GRAD one wavefront carries both X and D (each
+// operand of V and V^-1 then feeds two products), or, with APART, a block has a
+// wavefront for X and one for D, which takes the X V that its step reads from
+// LDS.  A chain's products are serial, each 4 NT^2 matrix instructions of 64
+// cycles in FP64, so a launch that does not fill the chip lasts as long as its
+// longest chain, and the two wavefronts, on SIMDs of their own, halve that; a
+// full one is bound by the operands.  61 states, 254 branches of up to 4
+// segments (1,016 units): 40 us together, 28 apart; 16 such problems (some
+// 16,000): 206 and 274; 40 states, 3,998 branches (12,000): 95 and 91.
+constexpr int kApartUnits = 4096;
+
+template <typename T, bool GRAD, bool APART, int NT>
+struct PStageShared {
+  ColCoef<T> coef[APART ? 2 : 4][2 * 64];  // per wavefront, double-buffered by segment parity
+  alignas(16) T xv[APART ? 2 : 1][APART ? NT : 1][APART ? 64 : 1][4];  // X V of a segment, by parity: tile, lane
+};
+
+template <typename T, typename TO, bool GRAD, bool APART, int NT>
+__device__ inline void pstage_stripe(const PStageDesc& pd, int unit, PStageShared<T, GRAD, APART, NT>& sh) {
   using acc = typename Mfma<T>::acc;
   constexpr int Kp = 16 * NT;
   constexpr int KK = Kp * Kp;
-  const int item = gw / NT, stripe = gw - item * NT;
-  if (item >= pd.n_items) return;  // whole wavefronts only: no barrier follows
+  const int item = unit / NT, stripe = unit - item * NT;
+  if (item >= pd.n_items) return;  // whole wavefronts, and with APART (the only form with a barrier) whole blocks
+  const int wave = threadIdx.x >> 6;
+  const bool is_d = APART && wave == 1;  // this wavefront carries D alone
   const int C = pd.C;
   const int4 wi = pd.items[item / C];
   const int k0 = wi.y, k1 = wi.z, kind = wi.w & 3, part = (wi.w >> 2) & 7, slot = wi.w >> 9;
@@ -65,22 +83,21 @@ __device__ inline void pstage_stripe(const PStageDesc& pd, int gw, ColCoef<T>* c
   const double* __restrict__ seg_frac = pd.seg_frac;
   const double* __restrict__ rate = pd.rate;
   const double* __restrict__ cat_rates = pd.cat_rates;
-  TO* __restrict__ Pout = static_cast<TO*>(pd.Pout);
-  TO* __restrict__ dPout = static_cast<TO*>(pd.dPout);
   const int lane = threadIdx.x & 63;
   const int v = wi.x, c = item - (item / C) * C;
   const int g = lane >> 4, n = lane & 15;
   const int row = 16 * stripe + n;  // row of P this lane's column of X^T belongs to
   const int arow = Mfma<T>::a_row(n);
+  ColCoef<T>* coef = sh.coef[wave];
 
-  constexpr int NB = GRAD ? 2 : 1;  // the running product X and, with GRAD, its derivative D
-  acc xd[NB][NT];
+  constexpr int NB = GRAD && !APART ? 2 : 1;
+  acc xd[NB][NT];  // the running product X and its derivative D, or the one this wavefront carries
 #pragma unroll
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      xd[0][t][q] = (16 * t + 4 * g + q == row) ? T(1) : T(0);
-      if (GRAD) xd[NB - 1][t][q] = T(0);
+      xd[0][t][q] = (!is_d && 16 * t + 4 * g + q == row) ? T(1) : T(0);
+      if (NB == 2) xd[NB - 1][t][q] = T(0);
     }
 
   const int seg0 = seg_offset[v];
@@ -101,14 +118,18 @@ __device__ inline void pstage_stripe(const PStageDesc& pd, int gw, ColCoef<T>* c
   T av[2][4][NT], ai[2][4][NT];
   // The first segment's X is I and its D is 0, so X V is V itself (this stripe's rows) and D V is 0:
   // no first product.  Most branches lie within one interval, and half their arithmetic goes with it.
-  acc y[NB][NT];
+  acc y[NB][NT], xv[APART ? NT : 1];
   if (k1 > k0) {
     const T* V0 = eigV + (size_t)seg_process[seg0 + k0] * KK + (size_t)row * Kp + 4 * g;
 #pragma unroll
     for (int mt = 0; mt < NT; ++mt) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) y[0][mt][q] = V0[16 * mt + q];
-      if (GRAD) y[NB - 1][mt] = acc{0, 0, 0, 0};
+      for (int q = 0; q < 4; ++q) {
+        const T v0 = V0[16 * mt + q];
+        y[0][mt][q] = is_d ? T(0) : v0;
+        if constexpr (APART) xv[mt][q] = v0;
+      }
+      if (NB == 2) y[NB - 1][mt] = acc{0, 0, 0, 0};
     }
     make_coef(k0, coef + 64 * (k0 & 1));
   }
@@ -118,7 +139,7 @@ __device__ inline void pstage_stripe(const PStageDesc& pd, int gw, ColCoef<T>* c
     wave_lds_sync();  // segment k's coefficients are in LDS
     stripe_load<T, NT>(eigVi + (size_t)s * KK, 0, g, arow, ai[0]);
 
-    if (k > k0) {  // Y^T = V^T X^T (and V^T D^T)
+    if (k > k0) {  // Y^T = V^T X^T, V^T D^T
 #pragma unroll
       for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -129,7 +150,21 @@ __device__ inline void pstage_stripe(const PStageDesc& pd, int gw, ColCoef<T>* c
       make_coef(k + 1, coef + 64 * ((k + 1) & 1));
       stripe_load<T, NT>(eigV + (size_t)seg_process[seg0 + k + 1] * KK, 0, g, arow, av[0]);
     }
-    if (pd.Ubuf && k > 0) {
+    if constexpr (APART) {
+      if (k > k0) {  // X V handed over; the next segment writes the other buffer, and the one after it follows a barrier
+        T(*slot_xv)[64][4] = sh.xv[k & 1];
+        if (!is_d)
+#pragma unroll
+          for (int mt = 0; mt < NT; ++mt) store4<T, T>(slot_xv[mt][lane], y[0][mt]);
+        lds_barrier();
+        if (is_d)
+#pragma unroll
+          for (int mt = 0; mt < NT; ++mt)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) xv[mt][q] = slot_xv[mt][lane][q];
+      }
+    }
+    if (pd.Ubuf && k > 0 && !is_d) {
       // A_k V (the running product times V before the column operator), the forward
       // half of the dlogL/dQ adjoint chain, which takes A_0 V from V itself
       T* U = static_cast<T*>(pd.Ubuf) + ((size_t)(seg0 + k) * C + c) * KK + (size_t)row * Kp + 4 * g;
@@ -145,34 +180,37 @@ __device__ inline void pstage_stripe(const PStageDesc& pd, int gw, ColCoef<T>* c
         const ColCoef<T> c0 = ck[16 * mt + 4 * g + q];
         const ColCoef<T> c1 = ck[16 * mt + 4 * g + q + 1];
         const T y0 = y[0][mt][q], y1 = y[0][mt][q + 1];
-        y[0][mt][q] = c0.ms * y0 + c0.mo * y1;
-        y[0][mt][q + 1] = c1.ms * y1 + c1.mo * y0;
-        if (GRAD) {
+        if constexpr (NB == 2) {
           const T d0 = y[NB - 1][mt][q], d1 = y[NB - 1][mt][q + 1];
           y[NB - 1][mt][q] = c0.ms * d0 + c0.mo * d1 + c0.dms * y0 + c0.dmo * y1;
           y[NB - 1][mt][q + 1] = c1.ms * d1 + c1.mo * d0 + c1.dms * y1 + c1.dmo * y0;
         }
+        if (!is_d) {
+          y[0][mt][q] = c0.ms * y0 + c0.mo * y1;
+          y[0][mt][q + 1] = c1.ms * y1 + c1.mo * y0;
+        } else if constexpr (APART) {
+          const T x0 = xv[mt][q], x1 = xv[mt][q + 1];
+          y[0][mt][q] = c0.ms * y0 + c0.mo * y1 + c0.dms * x0 + c0.dmo * x1;
+          y[0][mt][q + 1] = c1.ms * y1 + c1.mo * y0 + c1.dms * x1 + c1.dmo * x0;
+        }
       }
 
-    // X^T += V^-T Y'^T (and D^T += V^-T YD'^T)
+    // X^T += V^-T Y'^T, D^T += V^-T YD'^T
     stripe_gemm_from<T, NT, NB>(eigVi + (size_t)s * KK, g, arow, ai, y, xd);
   }
 
-  if (kind == 0) {
-    const size_t base = ((size_t)v * C + c) * KK + (size_t)row * Kp + 4 * g;
 #pragma unroll
-    for (int mt = 0; mt < NT; ++mt) {
-      store4<T, TO>(Pout + base + 16 * mt, xd[0][mt]);
-      if (GRAD) store4<T, TO>(dPout + base + 16 * mt, xd[NB - 1][mt]);
+  for (int b = 0; b < NB; ++b) {
+    const bool d = is_d || b == 1;
+    if (kind == 0) {
+      TO* out = static_cast<TO*>(d ? pd.dPout : pd.Pout) + ((size_t)v * C + c) * KK + (size_t)row * Kp + 4 * g;
+#pragma unroll
+      for (int mt = 0; mt < NT; ++mt) store4<T, TO>(out + 16 * mt, xd[b][mt]);
+    } else {  // one part of a split chain: its product X_j and dX_j/dl
+      T* X = chain_mat<T, KK>(pd.scratch, slot, C, c, part, d ? 1 : 0) + (size_t)row * Kp + 4 * g;
+#pragma unroll
+      for (int mt = 0; mt < NT; ++mt) store4<T, T>(X + 16 * mt, xd[b][mt]);
     }
-    return;
-  }
-  // one part of a split chain: its product X_j and dX_j/dl
-  T* X = chain_mat<T, KK>(pd.scratch, slot, C, c, part, 0);
-#pragma unroll
-  for (int mt = 0; mt < NT; ++mt) {
-    store4<T, T>(X + (size_t)row * Kp + 4 * g + 16 * mt, xd[0][mt]);
-    if (GRAD) store4<T, T>(X + KK + (size_t)row * Kp + 4 * g + 16 * mt, xd[NB - 1][mt]);
   }
 }
 
@@ -304,20 +342,20 @@ __global__ __launch_bounds__(256) void pstage_tail_fix_kernel(PStageDesc pd, con
 }
 
 // One problem (descriptor passed by value).
-template <typename T, typename TO, bool GRAD, int NT>
-__global__ __launch_bounds__(256, (GRAD && NT == 4 && sizeof(T) == 8 ? 1 : 2)) void pstage_mfma_kernel(PStageDesc pd) {
-  __shared__ ColCoef<T> s_coef[4][2 * 64];
-  const int wave = threadIdx.x >> 6;
-  pstage_stripe<T, TO, GRAD, NT>(pd, blockIdx.x * 4 + wave, s_coef[wave]);
+template <typename T, typename TO, bool GRAD, bool APART, int NT>
+__global__ __launch_bounds__(APART ? 128 : 256, (GRAD && NT == 4 && sizeof(T) == 8 && !APART ? 1 : 2)) void
+pstage_mfma_kernel(PStageDesc pd) {
+  __shared__ PStageShared<T, GRAD, APART, NT> sh;
+  pstage_stripe<T, TO, GRAD, APART, NT>(pd, APART ? blockIdx.x : blockIdx.x * 4 + (threadIdx.x >> 6), sh);
 }
 
 // Several problems of one batch in one launch: blockIdx.y selects the problem.
 template <typename T, typename TO, bool GRAD, int NT>
-__global__ __launch_bounds__(256, (GRAD && NT == 4 && sizeof(T) == 8 ? 1 : 2)) void pstage_mfma_multi_kernel(const PStageDesc* __restrict__ descs) {
-  __shared__ ColCoef<T> s_coef[4][2 * 64];
-  const int wave = threadIdx.x >> 6;
+__global__ __launch_bounds__(256, (GRAD && NT == 4 && sizeof(T) == 8 ? 1 : 2)) void pstage_mfma_multi_kernel(
+    const PStageDesc* __restrict__ descs) {
+  __shared__ PStageShared<T, GRAD, false, NT> sh;
   const PStageDesc pd = descs[blockIdx.y];
-  pstage_stripe<T, TO, GRAD, NT>(pd, blockIdx.x * 4 + wave, s_coef[wave]);
+  pstage_stripe<T, TO, GRAD, false, NT>(pd, blockIdx.x * 4 + (threadIdx.x >> 6), sh);
 }
 
 template <typename T, typename TO, int NT>
@@ -331,12 +369,14 @@ int pstage_mfma_launch(EpochInstance* in, const int4* d_items, int n_items) {
     pd.items = static_cast<const int4*>(in->chain_items.ptr) + in->n_nodes;
     pd.n_items = in->n_chain_split_items * in->C;
   }
-  const long waves = (long)pd.n_items * NT;
-  dim3 grid((unsigned)((waves + 3) / 4));
-  if (pd.grad)
-    hipLaunchKernelGGL((pstage_mfma_kernel<T, TO, true, NT>), grid, dim3(256), 0, in->stream, pd);
+  const long units = (long)pd.n_items * NT;
+  const dim3 grid((unsigned)((units + 3) / 4));
+  if (pd.grad && units <= kApartUnits)
+    hipLaunchKernelGGL((pstage_mfma_kernel<T, TO, true, true, NT>), dim3((unsigned)units), dim3(128), 0, in->stream, pd);
+  else if (pd.grad)
+    hipLaunchKernelGGL((pstage_mfma_kernel<T, TO, true, false, NT>), grid, dim3(256), 0, in->stream, pd);
   else
-    hipLaunchKernelGGL((pstage_mfma_kernel<T, TO, false, NT>), grid, dim3(256), 0, in->stream, pd);
+    hipLaunchKernelGGL((pstage_mfma_kernel<T, TO, false, false, NT>), grid, dim3(256), 0, in->stream, pd);
   if (split) {
     const int4* splits = static_cast<const int4*>(in->chain_items.ptr) + in->n_nodes + in->n_chain_split_items;
     dim3 cgrid((unsigned)(in->n_chain_splits * in->C));

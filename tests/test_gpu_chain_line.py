@@ -29,3 +29,14 @@ def test_default_line(K, n_intervals, precision):
         assert rel(logL, whole[0]) <= TOL_LOGL[precision]
         assert_grad(db, whole[2], TOL_GRAD[precision], "dlogL/dl, uncut")
         assert_grad(dq, whole[3], TOL_GRAD[precision], "dlogL/dQ, uncut")
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("n_tips", [1020, 1030])  # 4,078 and 4,118 stripes: either side of the P stage's two forms
+def test_derivative_apart(n_tips, precision):
+    prob = W.random_problem(np.random.default_rng(n_tips), n_tips, 17, 2, n_categories=1, n_intervals=3,
+                            reversible=False)
+    with from_problem(prob, precision, grad_branch=True) as lik:
+        logL, _, db, _ = lik.evaluate(branch=True)
+    assert rel(logL, O.log_likelihood(prob)) <= TOL_LOGL[precision]
+    assert_grad(db, O.gradient(prob)[0], TOL_GRAD[precision], "dlogL/dl")

@@ -421,7 +421,7 @@ int epoch_create(const EpochConfig* cfg, EpochInstance** out) {
     if (grad) A(in->pre, (N - 1) * C * P * Kp * R);
   }
   A(in->site, P * sizeof(double));
-  A(in->blocksum, ((P + 31) / 32 + 1) * sizeof(double));  // a root block serves 32 patterns at least (4-state, 8 categories)
+  A(in->blocksum, ((P + 15) / 16 + 1) * sizeof(double));  // a root block serves 16 patterns at least
   A(in->arrived, sizeof(unsigned));
   A(in->result, std::max<size_t>(8, std::max(in->codon_nchunks, in->gen_nchunks) + 1) * sizeof(double));
   if (grad) {

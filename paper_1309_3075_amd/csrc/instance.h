@@ -218,7 +218,7 @@ struct EpochInstance {
   epochlik::DevBuf scales;     // int32 [N-1][P]
   epochlik::DevBuf pre;        // T [N-1][C][P][Kp]
   epochlik::DevBuf site;       // double [P]
-  epochlik::DevBuf blocksum;   // double [ceil(P/32)+1], one per block of the root reduction
+  epochlik::DevBuf blocksum;   // double [ceil(P/16)+1], one per block of the root reduction
   epochlik::DevBuf arrived;    // uint32: blocks of the root launch that have delivered their share (0 between launches)
   epochlik::DevBuf result;     // double [4]
   epochlik::DevBuf Gpart;      // double [chunks][n][C][Kp][Kp]

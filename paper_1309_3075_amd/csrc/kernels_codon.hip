@@ -260,24 +260,26 @@ __device__ inline double dmax(double a, double b) { return fmax(a, b); }
 // wavefront reads four whole rows at once), in FP64; block partial sums of w_p log L_p per
 // instance (blockIdx.y runs over descriptors; those of categories above 0 have
 // nothing to do), added up by the instance's last block.  One thread per pattern, walking its
-// row alone, took 14 us on 10,000 codon patterns and 21 us on 2,003 patterns of four categories.  One category: L_p = sum_i pi_i x_root(p, i) 2^E_p.  Several
+// row alone, took 14 us on 10,000 codon patterns and 21 us on 2,003 patterns of four categories.  A
+// group walks one pattern where those blocks are at most one per CU, else four: 2,003 patterns of four
+// categories 20 -> 8.3 us, 3,001 FP64 codon patterns 10.6 -> 7.7; 10,000 patterns take 11 either way.  One category: L_p = sum_i pi_i x_root(p, i) 2^E_p.  Several
 // (text after Eq. 4, rate categories): each category c has its own scale
 // exponent E_c, so L_p = 2^Emax sum_c w_c l_c 2^(E_c - Emax) with
 // l_c = sum_i pi_i x_c(p, i); the pre-order pass of category c then weighs
 // pattern p by w_p w_c l_c 2^E_c / L_p (its posterior share), written to that
 // category's weightsT.
-constexpr int kRootPatterns = 64;  // patterns per block
+__host__ __device__ inline int root_steps(int P) { return P <= 16 * 256 ? 1 : 4; }  // patterns per sixteen-lane group
+__host__ __device__ inline int root_blocks(int P) { return (P + 16 * root_steps(P) - 1) / (16 * root_steps(P)); }
 template <typename T, int NT>
 __global__ __launch_bounds__(256) void codon_root_kernel(const CodonProblem* __restrict__ probs,
                                                          double* __restrict__ host_logL) {
   EPOCH_DIMS(NT);
   constexpr int PER = NT;                   // states per lane
-  constexpr int STEPS = kRootPatterns / 16;  // patterns per sixteen-lane group
   __shared__ double sm[256];
   const CodonProblem& pr = probs[blockIdx.y];
   if (pr.cat_index != 0) return;  // uniform
   const int P = pr.P, K = pr.K;
-  const int n_blocks = (P + kRootPatterns - 1) / kRootPatterns;
+  const int steps = root_steps(P), n_blocks = root_blocks(P);
   if ((int)blockIdx.x >= n_blocks) return;  // uniform
   const int grp = threadIdx.x >> 4, r = threadIdx.x & 15;
   const size_t slot = pr.root - pr.N;
@@ -293,9 +295,8 @@ __global__ __launch_bounds__(256) void codon_root_kernel(const CodonProblem* __r
     return row16_sum(acc);
   };
   double contrib = 0.0;
-#pragma unroll
-  for (int k = 0; k < STEPS; ++k) {
-    const int p = blockIdx.x * kRootPatterns + 16 * k + grp;
+  for (int k = 0; k < steps; ++k) {
+    const int p = blockIdx.x * 16 * steps + 16 * k + grp;
     const int pc = min(p, P - 1);
     double s;
     if (pr.n_cats == 1) {
@@ -303,7 +304,9 @@ __global__ __launch_bounds__(256) void codon_root_kernel(const CodonProblem* __r
     } else {
       double l[kMaxCategories];
       int e[kMaxCategories], emax = INT_MIN;
-      for (int c0 = 0; c0 < pr.n_cats; c0 += 4) {  // four categories' rows in flight
+#pragma unroll
+      for (int c0 = 0; c0 < kMaxCategories; c0 += 4) {  // four categories' rows in flight
+        if (c0 >= pr.n_cats) break;
         double d[4];
         int x[4];
 #pragma unroll
@@ -314,22 +317,24 @@ __global__ __launch_bounds__(256) void codon_root_kernel(const CodonProblem* __r
         }
 #pragma unroll
         for (int cc = 0; cc < 4; ++cc) {
-          const int c = c0 + cc;
-          if (c >= pr.n_cats) break;
-          l[c] = pr.cat[kMaxCategories + c] * d[cc];
-          e[c] = x[cc];
-          if (l[c] > 0.0) emax = max(emax, e[c]);
+          l[c0 + cc] = c0 + cc < pr.n_cats ? pr.cat[kMaxCategories + c0 + cc] * d[cc] : 0.0;
+          e[c0 + cc] = x[cc];
+          if (l[c0 + cc] > 0.0) emax = max(emax, x[cc]);
         }
       }
       double L = 0.0;
-      for (int c = 0; c < pr.n_cats; ++c) {
-        l[c] = l[c] > 0.0 ? ldexp(l[c], e[c] - emax) : 0.0;
-        L += l[c];
-      }
+#pragma unroll
+      for (int c = 0; c < kMaxCategories; ++c)
+        if (c < pr.n_cats) {
+          l[c] = l[c] > 0.0 ? ldexp(l[c], e[c] - emax) : 0.0;
+          L += l[c];
+        }
       s = L > 0.0 ? log(L) + (double)emax * kLn2 : -INFINITY;
       if (p < P && r == 0)
-        for (int c = 0; c < pr.n_cats; ++c)
-          reinterpret_cast<T*>(probs[blockIdx.y + c].weightsT)[p] = L > 0.0 ? (T)(pr.weights[p] * (l[c] / L)) : T(0);
+#pragma unroll
+        for (int c = 0; c < kMaxCategories; ++c)
+          if (c < pr.n_cats)
+            reinterpret_cast<T*>(probs[blockIdx.y + c].weightsT)[p] = L > 0.0 ? (T)(pr.weights[p] * (l[c] / L)) : T(0);
     }
     if (p < P && r == 0) {
       pr.site[p] = s;
@@ -1096,7 +1101,8 @@ void codon_build_schedule(const std::vector<const EpochInstance*>& insts, int ta
   for (auto* in : insts) {
     n_levels = std::max(n_levels, in->plan.n_levels);
     max_tiles = std::max(max_tiles, (codon_chunk_patterns(in) + TILE - 1) / TILE);
-    max_pblocks = std::max(max_pblocks, (codon_chunk_patterns(in) + kRootPatterns - 1) / kRootPatterns);
+    const int pc = codon_chunk_patterns(in);
+    max_pblocks = std::max({max_pblocks, root_blocks(pc), root_blocks((in->P - 1) % pc + 1)});  // the last chunk may take more
   }
   gslots.assign(nd, {});
   out.slot_total.assign(nd, 0);

@@ -677,6 +677,7 @@ __global__ __launch_bounds__(256) void qgrad_hsum_kernel(int KK, int n_chunks, c
 // blocks: every block forms the whole X, but the two products, serial per
 // thread, are 4 times shorter than with bands of 16.
 constexpr int kFinalRows = 4;
+constexpr int kFinalV = 64 * 64 / 256;  // entries of V per thread, at most
 __global__ __launch_bounds__(256) void qgrad_final_kernel(int K, int Kp, const double* __restrict__ Hsum,
                                                           const double* __restrict__ V, const double* __restrict__ Vi,
                                                           const double* __restrict__ li_all, double* __restrict__ dQ) {
@@ -691,38 +692,74 @@ __global__ __launch_bounds__(256) void qgrad_final_kernel(int K, int Kp, const d
   const double2* H = reinterpret_cast<const double2*>(Hsum) + (size_t)s * KK;
   const double* Vis = Vi + (size_t)s * KK;
   for (int e = threadIdx.x; e < BR * Kp; e += 256) sVi[e] = Vis[(e / BR) * Kp + r0 + e % BR];
-  for (int e = threadIdx.x; e < KK; e += 256) {
-    const int a = e / Kp, b = e % Kp;
-    const PairIdx pa = pair_of(li, a), pb = pair_of(li, b);
-    const int na = pa.pair ? 2 : 1, nb = pb.pair ? 2 : 1;
-    double re = 0.0;
-    for (int ci = 0; ci < na; ++ci) {
-      const int cc = pa.first + ci;
-      const cplx t1 = Tinv_entry(cc, a, pa.first, pa.pair);
-      for (int di = 0; di < nb; ++di) {
-        const int dd = pb.first + di;
-        const cplx t2 = T_entry(b, dd, pb.first, pb.pair);
-        const double2 h = H[cc * Kp + dd];
-        re += cmul(cmul(t1, cplx{h.x, h.y}), t2).re;
+  // V waits in registers until its place in LDS is free; H's loads of four entries are in flight together
+  constexpr int U = 4;
+  double v[kFinalV];
+#pragma unroll
+  for (int k = 0; k < kFinalV; ++k) {
+    const int e = threadIdx.x + 256 * k;
+    v[k] = e < KK ? V[(size_t)s * KK + e] : 0.0;
+  }
+  if (li[0] == 0.0) {  // pairs stand first: every eigenvalue is real, T = I
+    for (int e0 = threadIdx.x; e0 < KK; e0 += 256 * U) {
+      double h[U];
+#pragma unroll
+      for (int k = 0; k < U; ++k) h[k] = H[min(e0 + 256 * k, KK - 1)].x;
+#pragma unroll
+      for (int k = 0; k < U; ++k)
+        if (e0 + 256 * k < KK) sX[e0 + 256 * k] = h[k];
+    }
+  } else {
+    for (int e0 = threadIdx.x; e0 < KK; e0 += 256 * U) {
+      double2 h[U][2][2];
+      cplx t[U][2][2];
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const int e = min(e0 + 256 * k, KK - 1), a = e / Kp, b = e - (e / Kp) * Kp;
+        const PairIdx pa = pair_of(li, a), pb = pair_of(li, b);
+#pragma unroll
+        for (int ci = 0; ci < 2; ++ci)
+#pragma unroll
+          for (int di = 0; di < 2; ++di) {  // a real eigenvalue's entry is read twice and counted once
+            const int i = pa.pair ? pa.first + ci : a, j = pb.pair ? pb.first + di : b;
+            h[k][ci][di] = H[i * Kp + j];
+            t[k][ci][di] = cmul(Tinv_entry(i, a, pa.first, pa.pair), T_entry(b, j, pb.first, pb.pair));
+            if ((ci && !pa.pair) || (di && !pb.pair)) t[k][ci][di] = {0.0, 0.0};
+          }
+      }
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        double re = 0.0;
+#pragma unroll
+        for (int ci = 0; ci < 2; ++ci)
+#pragma unroll
+          for (int di = 0; di < 2; ++di)
+            re += t[k][ci][di].re * h[k][ci][di].x - t[k][ci][di].im * h[k][ci][di].y;
+        if (e0 + 256 * k < KK) sX[e0 + 256 * k] = re;
       }
     }
-    sX[e] = re;
   }
   __syncthreads();
   for (int e = threadIdx.x; e < BR * Kp; e += 256) {
     const int ii = e / Kp, j = e % Kp;
     double r = 0.0;
+#pragma unroll 8
     for (int l = 0; l < Kp; ++l) r += sVi[l * BR + ii] * sX[l * Kp + j];
     sY[e] = r;
   }
   __syncthreads();
   double* sV = sX;  // row stride Kp + 1
-  for (int e = threadIdx.x; e < KK; e += 256) sV[(e / Kp) * (Kp + 1) + e % Kp] = V[(size_t)s * KK + e];
+#pragma unroll
+  for (int k = 0; k < kFinalV; ++k) {
+    const int e = threadIdx.x + 256 * k;
+    if (e < KK) sV[(e / Kp) * (Kp + 1) + e % Kp] = v[k];
+  }
   __syncthreads();
   for (int e = threadIdx.x; e < BR * Kp; e += 256) {
     const int i = r0 + e / Kp, j = e % Kp;
     if (i < K && j < K) {
       double r = 0.0;
+#pragma unroll 8
       for (int l = 0; l < Kp; ++l) r += sY[(i - r0) * Kp + l] * sV[j * (Kp + 1) + l];
       dQ[((size_t)s * K + i) * K + j] = r;
     }

@@ -92,7 +92,11 @@ __global__ __launch_bounds__(256) void tgrad_end_kernel(const T* __restrict__ Pm
 
 // One block per (crossing, category).  A crossing (v, m, j): branch v spans
 // boundary m, and its first j segments (parent side) lie above it.  Forms
-// Z = X^T G Y^T and returns x <Z, Q_phi(m) - Q_phi(m+1)>.
+// Z = X^T G Y^T and returns x <Z, Q_phi(m) - Q_phi(m+1)>.  A block's chain of
+// steps is serial, so the latency of a step's loads bounds it: the dot products
+// run over the padded states (V, V^-1 and W hold zeros there), whose constant
+// number lets the loads of a dot go out together (7 states, 13 intervals: 18 ->
+// 12 us).
 template <int KP>
 __global__ __launch_bounds__(256) void tgrad_cross_kernel(
     const int4* __restrict__ cross, const double* __restrict__ G, const double* __restrict__ eigV,
@@ -110,7 +114,9 @@ __global__ __launch_bounds__(256) void tgrad_cross_kernel(
   const int v = cr.x, m = cr.y, j = cr.z;
   const double x = rate[v] * cat[c];
   const int seg0 = seg_offset[v], L = seg_offset[v + 1] - seg0;
-  for (int e = threadIdx.x; e < KK; e += 256) sW[e] = G[((size_t)v * C + c) * KK + e];
+  constexpr int UNROLL = KP <= 16 ? KP : 8;
+  for (int e = threadIdx.x; e < KK; e += 256)
+    sW[e] = e / KP < K && e % KP < K ? G[((size_t)v * C + c) * KK + e] : 0.0;
   __syncthreads();
   // step k applies factor k: before the boundary W <- F_k^T W (k = 0 .. j-1, parent side first),
   // after it W <- W F_k^T (k = L-1 down to j)
@@ -138,9 +144,11 @@ __global__ __launch_bounds__(256) void tgrad_cross_kernel(
       const int r = e / KP, q = e % KP;
       double t = 0.0;
       if (left) {
-        for (int l = 0; l < K; ++l) t += V[l * KP + r] * sW[l * KP + q];
+#pragma unroll UNROLL
+        for (int l = 0; l < KP; ++l) t += V[l * KP + r] * sW[l * KP + q];
       } else {
-        for (int l = 0; l < K; ++l) t += sW[r * KP + l] * Vi[q * KP + l];
+#pragma unroll UNROLL
+        for (int l = 0; l < KP; ++l) t += sW[r * KP + l] * Vi[q * KP + l];
       }
       sT[e] = t;
     }
@@ -173,9 +181,11 @@ __global__ __launch_bounds__(256) void tgrad_cross_kernel(
       if (r >= K || q >= K) continue;
       double t = 0.0;
       if (left) {
-        for (int a = 0; a < K; ++a) t += Vi[a * KP + r] * sT[a * KP + q];
+#pragma unroll UNROLL
+        for (int a = 0; a < KP; ++a) t += Vi[a * KP + r] * sT[a * KP + q];
       } else {
-        for (int a = 0; a < K; ++a) t += sT[r * KP + a] * V[q * KP + a];
+#pragma unroll UNROLL
+        for (int a = 0; a < KP; ++a) t += sT[r * KP + a] * V[q * KP + a];
       }
       sW[e] += t;
     }
@@ -193,7 +203,9 @@ __global__ __launch_bounds__(256) void tgrad_cross_kernel(
 }
 
 // dlogL/dh_u = sum over u's children of their top terms - u's own bottom term;
-// dlogL/db_m = the sum of boundary m's crossing terms (fixed orders).
+// dlogL/db_m = the sum of boundary m's crossing terms (fixed orders).  The first
+// blocks take a thread per node, the others a wavefront per boundary (one thread
+// adding up a boundary's some hundred terms took 9.3 us, this 3.6).
 __global__ __launch_bounds__(256) void tgrad_finish_kernel(const double* __restrict__ ends,
                                                            const double* __restrict__ cross_terms,
                                                            const int32_t* __restrict__ cross_off,
@@ -202,9 +214,10 @@ __global__ __launch_bounds__(256) void tgrad_finish_kernel(const double* __restr
                                                            const int32_t* __restrict__ right, int n_nodes,
                                                            int n_bound, int C, double* __restrict__ d_height,
                                                            double* __restrict__ d_bound) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t < n_nodes) {
-    const int u = t;
+  const int node_blocks = (n_nodes + 255) / 256;
+  if ((int)blockIdx.x < node_blocks) {
+    const int u = blockIdx.x * 256 + threadIdx.x;
+    if (u >= n_nodes) return;
     double d = 0.0;
     if (left[u] >= 0)
       for (int side = 0; side < 2; ++side) {
@@ -214,13 +227,17 @@ __global__ __launch_bounds__(256) void tgrad_finish_kernel(const double* __restr
     if (parent[u] >= 0)
       for (int c = 0; c < C; ++c) d -= ends[2 * ((size_t)u * C + c) + 1];
     d_height[u] = d;
-  } else if (t < n_nodes + n_bound) {
-    const int m = t - n_nodes;
-    double d = 0.0;
-    for (int k = cross_off[m]; k < cross_off[m + 1]; ++k)
-      for (int c = 0; c < C; ++c) d += cross_terms[(size_t)k * C + c];
-    d_bound[m] = d;
+    return;
   }
+  const int m = (blockIdx.x - node_blocks) * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (m >= n_bound) return;  // whole wavefronts
+  const long k1 = (long)cross_off[m + 1] * C;
+  double d = 0.0;
+#pragma unroll 4
+  for (long k = (long)cross_off[m] * C + lane; k < k1; k += 64) d += cross_terms[k];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) d += __shfl_xor(d, o, 64);
+  if (lane == 0) d_bound[m] = d;
 }
 
 int interval_of(const std::vector<double>& b, double h) {
@@ -328,7 +345,7 @@ int launch_time_gradient(EpochInstance* in, double** d_height, double** d_bound)
     rc = hip_check(hipGetLastError(), "tgrad_cross launch");
     if (rc) return rc;
   }
-  hipLaunchKernelGGL(tgrad_finish_kernel, dim3((n + nb + 255) / 256), dim3(256), 0, in->stream, ends, cterms, off,
+  hipLaunchKernelGGL(tgrad_finish_kernel, dim3((n + 255) / 256 + (nb + 3) / 4), dim3(256), 0, in->stream, ends, cterms, off,
                      in->d_parent, in->d_left, in->d_right, n, nb, C, dh, db);
   *d_height = dh;
   *d_bound = db;

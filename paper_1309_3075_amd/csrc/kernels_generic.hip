@@ -24,11 +24,11 @@ namespace epochlik {
 namespace {
 
 // ---------------------------------------------------------------------------
-// P stage.  One item = (node v, category c).  For Kp^2 <= 256 several items
-// share a block; otherwise one item per block and EPT elements per thread.
+// P stage above 16 states.  One item = (node v, category c) = one block, EPT
+// elements per thread.
 // ---------------------------------------------------------------------------
 template <typename T, typename TO, bool GRAD, int EPT>
-__device__ inline void pstage_generic_block(const PStageGenericArgs& A) {
+__global__ __launch_bounds__(256) void pstage_generic_kernel(const PStageGenericArgs A) {
   const int n_nodes = A.n_nodes, Kp = A.Kp, C = A.C;
   const int32_t* __restrict__ node_list = A.node_list;
   const T* __restrict__ eigV = static_cast<const T*>(A.V);
@@ -43,36 +43,24 @@ __device__ inline void pstage_generic_block(const PStageGenericArgs& A) {
   const double* __restrict__ cat_rates = A.cat_rates;
   TO* __restrict__ Pout = static_cast<TO*>(A.Pout);
   TO* __restrict__ dPout = static_cast<TO*>(A.dPout);
-  TO* __restrict__ PTout = static_cast<TO*>(A.PTout);
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int KK = Kp * Kp;
-  const int ipb = (EPT == 1) ? max(1, 256 / KK) : 1;
-  const int tid = threadIdx.x;
-  const int slot = (EPT == 1) ? tid / KK : 0;
-  const bool in_slot = slot < ipb;
-  const int item = blockIdx.x * ipb + slot;
-  const bool valid = in_slot && item < n_nodes * C;
+  const int tid = threadIdx.x, item = blockIdx.x;
   // node_list (or null: every node) names the branches whose matrices are formed
-  const int v = valid ? (node_list ? node_list[item / C] : item / C) : 0;
-  const int c = valid ? item % C : 0;
-  T* sX = reinterpret_cast<T*>(smem_raw) + (in_slot ? slot : 0) * KK;
-  T* sD = reinterpret_cast<T*>(smem_raw) + ipb * KK + (in_slot ? slot : 0) * KK;
-  __shared__ int s_maxm;
+  const int v = node_list ? node_list[item / C] : item / C;
+  const int c = item % C;
+  T* sX = reinterpret_cast<T*>(smem_raw);
+  T* sD = sX + KK;
 
   int idx[EPT];
   bool eok[EPT];
 #pragma unroll
   for (int e = 0; e < EPT; ++e) {
-    idx[e] = (EPT == 1) ? tid % KK : tid + e * 256;
-    eok[e] = valid && idx[e] < KK;
+    idx[e] = tid + e * 256;
+    eok[e] = idx[e] < KK;
   }
-  const int seg0 = valid ? seg_offset[v] : 0;
-  const int m = valid ? seg_offset[v + 1] - seg0 : 0;
-  if constexpr (EPT == 1) {
-    if (tid == 0) s_maxm = 0;
-    __syncthreads();
-    if (valid) atomicMax(&s_maxm, m);
-  }
+  const int seg0 = seg_offset[v];
+  const int m = seg_offset[v + 1] - seg0;
 #pragma unroll
   for (int e = 0; e < EPT; ++e)
     if (eok[e]) {
@@ -81,14 +69,11 @@ __device__ inline void pstage_generic_block(const PStageGenericArgs& A) {
       if (GRAD) sD[idx[e]] = T(0);
     }
   __syncthreads();
-  int maxm = m;  // one item per block when EPT > 1
-  if constexpr (EPT == 1) maxm = s_maxm;
-  const double rho = valid ? cat_rates[c] : 0.0;
-  for (int k = 0; k < maxm; ++k) {
-    const bool act = valid && k < m;
-    const int s = act ? seg_process[seg0 + k] : 0;
-    const T tau = act ? T(rho * rate[v] * seg_time[seg0 + k]) : T(0);
-    const T dsc = act ? T(rho * seg_frac[seg0 + k]) : T(0);
+  const double rho = cat_rates[c];
+  for (int k = 0; k < m; ++k) {
+    const int s = seg_process[seg0 + k];
+    const T tau = T(rho * rate[v] * seg_time[seg0 + k]);
+    const T dsc = T(rho * seg_frac[seg0 + k]);
     const T* V = eigV + (size_t)s * KK;
     const T* Vi = eigVi + (size_t)s * KK;
     const T* lr = lre + (size_t)s * Kp;
@@ -101,7 +86,7 @@ __device__ inline void pstage_generic_block(const PStageGenericArgs& A) {
       yd[e] = 0;
       xold[e] = eok[e] ? sX[idx[e]] : T(0);
       dold[e] = (GRAD && eok[e]) ? sD[idx[e]] : T(0);
-      if (eok[e] && act) {
+      if (eok[e]) {
         const int i = idx[e] / Kp, j = idx[e] % Kp;
         for (int l = 0; l < Kp; ++l) {
           const T vv = V[l * Kp + j];
@@ -113,7 +98,7 @@ __device__ inline void pstage_generic_block(const PStageGenericArgs& A) {
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < EPT; ++e)
-      if (eok[e] && act) {
+      if (eok[e]) {
         sX[idx[e]] = y[e];
         if (GRAD) sD[idx[e]] = yd[e];
       }
@@ -121,7 +106,7 @@ __device__ inline void pstage_generic_block(const PStageGenericArgs& A) {
     // X' = Y (E - I), D' = YD (E - I) + Y dE   (dE = dsc * d/dtau E)
 #pragma unroll
     for (int e = 0; e < EPT; ++e)
-      if (eok[e] && act) {
+      if (eok[e]) {
         const int i = idx[e] / Kp, j = idx[e] % Kp;
         BlockCoef<T> bc = block_coef(lr, li, j, tau);
         const T xs = sX[idx[e]];
@@ -136,7 +121,7 @@ __device__ inline void pstage_generic_block(const PStageGenericArgs& A) {
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < EPT; ++e)
-      if (eok[e] && act) {
+      if (eok[e]) {
         sX[idx[e]] = y[e];
         if (GRAD) sD[idx[e]] = yd[e];
       }
@@ -146,7 +131,7 @@ __device__ inline void pstage_generic_block(const PStageGenericArgs& A) {
     for (int e = 0; e < EPT; ++e) {
       y[e] = xold[e];
       yd[e] = dold[e];
-      if (eok[e] && act) {
+      if (eok[e]) {
         const int i = idx[e] / Kp, j = idx[e] % Kp;
         for (int l = 0; l < Kp; ++l) {
           const T vv = Vi[l * Kp + j];
@@ -158,7 +143,7 @@ __device__ inline void pstage_generic_block(const PStageGenericArgs& A) {
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < EPT; ++e)
-      if (eok[e] && act) {
+      if (eok[e]) {
         sX[idx[e]] = y[e];
         if (GRAD) sD[idx[e]] = yd[e];
       }
@@ -170,20 +155,122 @@ __device__ inline void pstage_generic_block(const PStageGenericArgs& A) {
     if (eok[e]) {
       Pout[base + idx[e]] = TO(sX[idx[e]]);
       if (GRAD) dPout[base + idx[e]] = TO(sD[idx[e]]);
-      if (EPT == 1 && PTout) PTout[base + (idx[e] % Kp) * Kp + idx[e] / Kp] = TO(sX[idx[e]]);
     }
 }
-template <typename T, typename TO, bool GRAD, int EPT>
-__global__ __launch_bounds__(256) void pstage_generic_kernel(const PStageGenericArgs A) {
-  pstage_generic_block<T, TO, GRAD, EPT>(A);
+
+// P stage up to 16 states (KP = 4, 8 or 16): a thread per entry, 256 / KP^2 items per block.  The
+// chain of a branch's segments is serial and each of its steps short, so latency bounds it: the dots
+// have a constant length (their loads of V and V^-1 go out together), the eigenvalue functions of a
+// step are taken before its products, an item of up to 8 states lies within one wavefront, which then
+// orders its LDS accesses without barriers and walks only its own items' segments, and the first
+// segment, whose X is I and D is 0, reads X V = V instead of forming it.  7 states, 1,042 branches,
+// FP64: 19 -> 11 us; 4 states, 1,022 branches, four categories, FP32: 10.6 -> 6.6.
+template <typename T, typename TO, bool GRAD, int KP>
+__device__ inline void pstage_small_block(const PStageGenericArgs& A) {
+  constexpr int KK = KP * KP, IPB = 256 / KK;
+  constexpr bool ONE_WAVE = KK <= 64;
+  const int C = A.C;
+  const T* __restrict__ eigV = static_cast<const T*>(A.V);
+  const T* __restrict__ eigVi = static_cast<const T*>(A.Vi);
+  const T* __restrict__ lre = static_cast<const T*>(A.lr);
+  const T* __restrict__ lim = static_cast<const T*>(A.li);
+  __shared__ T sXs[IPB][KK], sDs[IPB][KK];
+  const int slot = threadIdx.x / KK, e = threadIdx.x % KK, i = e / KP, j = e % KP;
+  const int item = blockIdx.x * IPB + slot;
+  const bool valid = item < A.n_nodes * C;
+  // node_list (or null: every node) names the branches whose matrices are formed
+  const int v = valid ? (A.node_list ? A.node_list[item / C] : item / C) : 0;
+  const int c = valid ? item % C : 0;
+  T* sX = sXs[slot];
+  T* sD = sDs[slot];
+  const int seg0 = valid ? A.seg_offset[v] : 0;
+  const int m = valid ? A.seg_offset[v + 1] - seg0 : 0;
+  auto order = [&] {
+    if constexpr (ONE_WAVE) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    } else {
+      __syncthreads();
+    }
+  };
+  int steps = m;  // of every item that shares the order points
+  if constexpr (KK < 64) {
+#pragma unroll
+    for (int o = KK; o < 64; o <<= 1) steps = max(steps, __shfl_xor(steps, o, 64));
+  }
+  T x = (i == j) ? T(1) : T(0), d = 0;
+  const double rho = valid ? A.cat_rates[c] : 0.0;
+  const double scale = valid ? rho * A.rate[v] : 0.0;
+  for (int k = 0; k < steps; ++k) {
+    const bool act = k < m;
+    const int s = act ? A.seg_process[seg0 + k] : 0;
+    const T tau = act ? T(scale * A.seg_time[seg0 + k]) : T(0);
+    const T dsc = act ? T(rho * A.seg_frac[seg0 + k]) : T(0);
+    const T* V = eigV + (size_t)s * KK;
+    const T* Vi = eigVi + (size_t)s * KK;
+    T vc[KP], vic[KP];
+#pragma unroll
+    for (int l = 0; l < KP; ++l) vic[l] = Vi[l * KP + j];
+    T y, yd = 0;
+    if (k == 0) {  // uniform: X = I, D = 0
+      y = V[e];
+    } else {
+#pragma unroll
+      for (int l = 0; l < KP; ++l) vc[l] = V[l * KP + j];
+    }
+    const BlockCoef<T> bc = block_coef(lre + (size_t)s * KP, lim + (size_t)s * KP, j, tau);
+    if (k > 0) {  // Y = X V, YD = D V
+      sX[e] = x;
+      if (GRAD) sD[e] = d;
+      order();
+      y = 0;
+#pragma unroll
+      for (int l = 0; l < KP; ++l) {
+        y += sX[i * KP + l] * vc[l];
+        if (GRAD) yd += sD[i * KP + l] * vc[l];
+      }
+      order();
+    }
+    sX[e] = y;
+    if (GRAD) sD[e] = yd;
+    order();
+    // X' = Y (E - I), D' = YD (E - I) + Y dE   (dE = dsc * d/dtau E)
+    const T xo = bc.partner >= 0 ? sX[i * KP + bc.partner] : T(0);
+    const T dd = GRAD && bc.partner >= 0 ? sD[i * KP + bc.partner] : T(0);
+    order();
+    sX[e] = bc.m_self * y + bc.m_other * xo;
+    if (GRAD) sD[e] = bc.m_self * yd + bc.m_other * dd + dsc * (bc.dm_self * y + bc.dm_other * xo);
+    order();
+    // X = X_old + X' V^-1, D = D_old + D' V^-1
+    T xn = x, dn = d;
+#pragma unroll
+    for (int l = 0; l < KP; ++l) {
+      xn += sX[i * KP + l] * vic[l];
+      if (GRAD) dn += sD[i * KP + l] * vic[l];
+    }
+    order();
+    if (act) {
+      x = xn;
+      d = dn;
+    }
+  }
+  if (!valid) return;
+  const size_t base = ((size_t)v * C + c) * KK;
+  static_cast<TO*>(A.Pout)[base + e] = TO(x);
+  if (GRAD) static_cast<TO*>(A.dPout)[base + e] = TO(d);
+  if (A.PTout) static_cast<TO*>(A.PTout)[base + j * KP + i] = TO(x);
 }
-// One launch for many instances (blockIdx.y), all of the same padded state count (Kp^2 <= 256).
+template <typename T, typename TO, bool GRAD, int KP>
+__global__ __launch_bounds__(256) void pstage_small_kernel(const PStageGenericArgs A) {
+  pstage_small_block<T, TO, GRAD, KP>(A);
+}
+// One launch for many 4-state instances (blockIdx.y).
 template <typename T, typename TO, bool GRAD>
-__global__ __launch_bounds__(256) void pstage_generic_multi_kernel(const PStageGenericArgs* __restrict__ args) {
+__global__ __launch_bounds__(256) void pstage_small_multi_kernel(const PStageGenericArgs* __restrict__ args) {
   const PStageGenericArgs A = args[blockIdx.y];
-  const int ipb = 256 / (A.Kp * A.Kp);
-  if ((int)blockIdx.x * ipb >= A.n_nodes * A.C) return;  // uniform
-  pstage_generic_block<T, TO, GRAD, 1>(A);
+  if ((int)blockIdx.x * 16 >= A.n_nodes * A.C) return;  // uniform
+  pstage_small_block<T, TO, GRAD, 4>(A);
 }
 
 // ---------------------------------------------------------------------------
@@ -512,17 +599,26 @@ int lanes_per_pattern(int Kp) {
 template <typename T, typename TO>
 int pstage_dispatch(EpochInstance* in, const int32_t* d_nodes, int n_list) {
   const PStageGenericArgs A = pstage_generic_args(in, d_nodes, n_list);
-  const int KK = A.Kp * A.Kp;
+  const int KK = A.Kp * A.Kp, items = A.n_nodes * A.C;
   const bool grad = (in->cfg.flags & (EPOCH_GRAD_BRANCH | EPOCH_GRAD_Q)) != 0;
-  const int ept = KK <= 256 ? 1 : (KK + 255) / 256;
-  const int ipb = ept == 1 ? std::max(1, 256 / KK) : 1;
-  const int items = A.n_nodes * A.C;
-  dim3 grid((items + ipb - 1) / ipb);
-  const size_t shm = 2 * (size_t)ipb * KK * sizeof(T);
+#define EPOCH_PSMALL(KP)                                                                                        \
+  case KP: {                                                                                                    \
+    const dim3 grid((items + 256 / (KP * KP) - 1) / (256 / (KP * KP)));                                         \
+    if (grad) hipLaunchKernelGGL((pstage_small_kernel<T, TO, true, KP>), grid, dim3(256), 0, in->stream, A);    \
+    else hipLaunchKernelGGL((pstage_small_kernel<T, TO, false, KP>), grid, dim3(256), 0, in->stream, A);        \
+    return hip_check(hipGetLastError(), "pstage_small launch");                                                 \
+  }
+  switch (A.Kp) {
+    EPOCH_PSMALL(4)
+    EPOCH_PSMALL(8)
+    EPOCH_PSMALL(16)
+  }
+#undef EPOCH_PSMALL
+  const int ept = (KK + 255) / 256;
+  const dim3 grid(items);
+  const size_t shm = 2 * (size_t)KK * sizeof(T);
 #define EPOCH_PSTAGE(G, E) hipLaunchKernelGGL((pstage_generic_kernel<T, TO, G, E>), grid, dim3(256), shm, in->stream, A)
-  if (ept == 1) {
-    if (grad) EPOCH_PSTAGE(true, 1); else EPOCH_PSTAGE(false, 1);
-  } else if (ept <= 4) {
+  if (ept <= 4) {
     if (grad) EPOCH_PSTAGE(true, 4); else EPOCH_PSTAGE(false, 4);
   } else if (ept <= 9) {
     if (grad) EPOCH_PSTAGE(true, 9); else EPOCH_PSTAGE(false, 9);
@@ -749,18 +845,16 @@ PStageGenericArgs pstage_generic_args(const EpochInstance* in, const int32_t* d_
 // The P stages of n 4-state FP32 instances that share the reconstruction's arithmetic and gradient flag.
 int launch_pstage_generic_multi(const PStageGenericArgs* d_args, int n, int max_items, bool wide, bool grad,
                                 hipStream_t st) {
-  constexpr int KK = 16, ipb = 256 / KK;
-  const dim3 grid((max_items + ipb - 1) / ipb, n);
-  const size_t shm = 2 * (size_t)ipb * KK * (wide ? sizeof(double) : sizeof(float));
+  const dim3 grid((max_items + 15) / 16, n);
   if (wide) {
     if (grad)
-      hipLaunchKernelGGL((pstage_generic_multi_kernel<double, float, true>), grid, dim3(256), shm, st, d_args);
+      hipLaunchKernelGGL((pstage_small_multi_kernel<double, float, true>), grid, dim3(256), 0, st, d_args);
     else
-      hipLaunchKernelGGL((pstage_generic_multi_kernel<double, float, false>), grid, dim3(256), shm, st, d_args);
+      hipLaunchKernelGGL((pstage_small_multi_kernel<double, float, false>), grid, dim3(256), 0, st, d_args);
   } else if (grad) {
-    hipLaunchKernelGGL((pstage_generic_multi_kernel<float, float, true>), grid, dim3(256), shm, st, d_args);
+    hipLaunchKernelGGL((pstage_small_multi_kernel<float, float, true>), grid, dim3(256), 0, st, d_args);
   } else {
-    hipLaunchKernelGGL((pstage_generic_multi_kernel<float, float, false>), grid, dim3(256), shm, st, d_args);
+    hipLaunchKernelGGL((pstage_small_multi_kernel<float, float, false>), grid, dim3(256), 0, st, d_args);
   }
   return hip_check(hipGetLastError(), "pstage_generic_multi launch");
 }

@@ -473,7 +473,7 @@ __global__ __launch_bounds__(256) void few_grad_kernel(const FewArgs<T> g, const
   }
   const int u = parent[v], w = g.left[u] == v ? g.right[u] : g.left[u];
   const int pl = threadIdx.x / KQ, i = threadIdx.x % KQ;
-  T gr[GPT];
+  double gr[GPT];  // FP64 over the tiles of TP patterns, as the partial-sum slots of the general form are added up
 #pragma unroll
   for (int k = 0; k < GPT; ++k) gr[k] = 0;
   for (int p0 = 0; p0 < P; p0 += TP) {
@@ -510,7 +510,7 @@ __global__ __launch_bounds__(256) void few_grad_kernel(const FewArgs<T> g, const
         if (ii < K && jj < K) {
           T s = 0;
           for (int q = 0; q < np; ++q) s += sAc[c][q * KQ + ii] * sBc[c][q * KQ + jj];
-          gr[k] += s;
+          gr[k] += (double)s;
         }
       }
     }
@@ -521,8 +521,8 @@ __global__ __launch_bounds__(256) void few_grad_kernel(const FewArgs<T> g, const
   for (int k = 0; k < GPT; ++k) {
     const int e = threadIdx.x + k * 256;
     if (e < nG) {
-      if (G) G[(size_t)v * nG + e] = (double)gr[k];
-      d += (double)gr[k] * (double)dP[(size_t)v * nG + e];
+      if (G) G[(size_t)v * nG + e] = gr[k];
+      d += gr[k] * (double)dP[(size_t)v * nG + e];
     }
   }
   d = block_sum<256>(d, sRed);

@@ -746,7 +746,7 @@ namespace {
 // and the last bits of the FP32 P show it in the results.
 int chain_split_line(const EpochInstance* in, int64_t n_seg) {
   if (in->chain_split_min >= 0) return in->chain_split_min;
-  if (!in->fp64) return 16;
+  if (!in->fp64 || in->Kp < 16) return 16;  // below 16 states no kernel reads the parts
   const int nt = in->Kp / 16;
   const int64_t rounds = n_seg * in->C * nt / (1024 * (nt >= 4 ? 1 : 2));
   return (int)std::min<int64_t>(16, std::max<int64_t>(8, rounds));

@@ -259,16 +259,16 @@ int stage_reserve(EpochInstance* in, size_t bytes) {
   }
   if (!in->stage_event) EPOCH_TRY(hip_check(hipEventCreateWithFlags(&in->stage_event, hipEventDisableTiming), "staging event"));
   if (in->stage_bytes >= bytes) return EPOCH_OK;
-  if (in->stage_host) (void)hipHostFree(in->stage_host);
-  in->stage_host = nullptr;
-  in->host_out = nullptr;
-  in->stage_bytes = 0;
-  // the evaluation's results share the allocation (every evaluation needs an eigensystem first)
+  // the evaluation's results share the allocation (every evaluation needs an eigensystem first); the
+  // present buffer is kept until the larger one is there, so host_out stays valid when it is refused
   const size_t at = (bytes + 255) / 256 * 256;
-  if (hipHostMalloc(&in->stage_host, at + Delivery::doubles(in) * sizeof(double), hipHostMallocDefault) != hipSuccess) {
-    in->stage_host = nullptr;
+  void* larger = nullptr;
+  if (hipHostMalloc(&larger, at + Delivery::doubles(in) * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
     return set_error(EPOCH_ERR_OOM, "pinned staging buffer of %zu bytes", bytes);
   }
+  if (in->stage_host) (void)hipHostFree(in->stage_host);
+  in->stage_host = larger;
   in->host_out = reinterpret_cast<double*>(static_cast<char*>(in->stage_host) + at);
   in->stage_bytes = bytes;
   return EPOCH_OK;

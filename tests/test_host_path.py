@@ -1,0 +1,34 @@
+"""The library's host path on a recording stand-in for the HIP runtime (no GPU, no kernel runs): failures a
+GPU run cannot bring about, and the order and number of the calls around the launches."""
+import pytest
+
+import fake_hip
+
+CREATE = """
+rng = np.random.default_rng(5)
+prob = W.random_problem(rng, {taxa}, {states}, {patterns}, n_categories=1, n_intervals=2, reversible=True)
+lik = from_problem(prob, {precision!r}, **{flags!r})
+"""
+
+
+def created(states=4, taxa=40, patterns=50, precision="fp32", **flags):
+    return CREATE.format(states=states, taxa=taxa, patterns=patterns, precision=precision, flags=flags)
+
+
+@pytest.mark.parametrize("flags", [{"grad_branch": True}, {"grad_branch": True, "grad_Q": True}])
+def test_results_buffer_survives_a_failed_pinned_allocation(tmp_path, flags):
+    """A refused staging buffer (more rates at once than it held) leaves the results' place on the host as it
+    was: the next evaluation's launch does not write through a null pointer."""
+    fake_hip.run(tmp_path, created(**flags) + """
+fake.fake_fail_host_mallocs(1)
+nodes = np.arange(prob.parent.shape[0] - 1)
+try:
+    lik.set_branch_rates(nodes, np.ones(len(nodes)))
+except _abi.EpochError as e:
+    assert e.code == _abi.EPOCH_ERR_OOM
+fake.fake_fail_host_mallocs(0)
+fake.fake_clear()
+lik.evaluate(branch=True, site=True)
+dst = [int(l.split()[-1], 16) for l in log() if "publish_kernel" in l]
+assert dst and all(d > 4096 for d in dst), dst
+""")

@@ -207,6 +207,15 @@ int epoch_set_branch_rates(EpochInstance* in, int32_t n, const int32_t* nodes, c
     if (!std::isfinite(rates[k]) || !(rates[k] > 0))
       return set_error(EPOCH_ERR_ARG, "rate %d must be finite and > 0", k);
   }
+  // the device first: a refused upload leaves the host's rates, which later calls hand over, as they were
+  if (n <= kInlineRates) {
+    if (const int rc = launch_set_rates(in, n, nodes, rates)) return rc;
+  } else {
+    std::vector<double> all(in->plan.rate);
+    for (int k = 0; k < n; ++k)
+      if (nodes[k] != in->plan.root) all[nodes[k]] = rates[k];
+    if (const int rc = stage_upload(in, in->d_rate, all.data(), all.size() * sizeof(double))) return rc;
+  }
   in->dirty.resize(in->n_nodes, 0);
   for (int k = 0; k < n; ++k) {
     const int v = nodes[k];
@@ -214,10 +223,6 @@ int epoch_set_branch_rates(EpochInstance* in, int32_t n, const int32_t* nodes, c
     in->plan.rate[v] = rates[k];
     in->dirty[v] = 1;
   }
-  const int rc = n <= kInlineRates ? launch_set_rates(in, n, nodes, rates)
-                                   : stage_upload(in, in->d_rate, in->plan.rate.data(),
-                                                  in->plan.rate.size() * sizeof(double));
-  if (rc) return rc;
   in->P_valid = in->partials_valid = in->logL_valid = false;
   return EPOCH_OK;
 }

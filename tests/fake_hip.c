@@ -80,7 +80,9 @@ hipError_t hipHostFree(void* p) { note("hostfree\n"); free(p); return hipSuccess
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind k) { (void)k; memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind k, hipStream_t st) {
   (void)k;
-  note("copy %p %zu\n", (void*)st, n);
+  double first = 0;
+  if (n >= sizeof(first)) memcpy(&first, s, sizeof(first));
+  note("copy %p %zu first %.17g\n", (void*)st, n, first);
   memcpy(d, s, n);
   return hipSuccess;
 }

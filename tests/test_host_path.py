@@ -32,3 +32,20 @@ lik.evaluate(branch=True, site=True)
 dst = [int(l.split()[-1], 16) for l in log() if "publish_kernel" in l]
 assert dst and all(d > 4096 for d in dst), dst
 """)
+
+
+def test_refused_branch_rates_change_nothing(tmp_path):
+    """Rates of a call that returned an error are not handed over by a later one."""
+    fake_hip.run(tmp_path, created(grad_branch=True) + """
+n = prob.parent.shape[0]
+fake.fake_fail_host_mallocs(1)
+try:
+    lik.set_branch_rates(np.arange(70), np.full(70, 3.0))
+    assert False
+except _abi.EpochError as e:
+    assert e.code == _abi.EPOCH_ERR_OOM
+fake.fake_clear()
+lik.set_branch_rates(np.arange(1, n - 1), np.full(n - 2, 2.0))
+sent = [l.split() for l in log() if l.startswith("copy") and int(l.split()[2]) == 8 * n]
+assert len(sent) == 1 and float(sent[0][-1]) == prob.branch_rate[0], sent
+""")

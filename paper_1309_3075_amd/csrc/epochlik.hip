@@ -1121,8 +1121,15 @@ int epoch_set_option(EpochInstance* in, int32_t key, int64_t value) {
   }
   in->partials_valid = in->logL_valid = false;
   if (!in->have_tree) return EPOCH_OK;
-  const int rc = fastpath_tree_changed(in);
+  const bool walked = in->path == 1 && in->walk_ok;
+  int rc = fastpath_tree_changed(in);
   if (rc) in->have_tree = false;
+  // the walk reads what a P stage that serves it writes besides P (transposed matrices, tip columns):
+  // where the matrices stay valid and it was off when they were formed, they are formed again
+  if (!rc && in->P_valid && in->path == 1 && in->walk_ok && !walked) {
+    in->async_pending = true;
+    rc = fastpath_pstage(in);
+  }
   return rc;
 }
 

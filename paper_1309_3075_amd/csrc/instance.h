@@ -243,7 +243,7 @@ struct EpochInstance {
   bool few = false;              // generic path, few patterns: the kernels of kernels_few.hip
   epochlik::FewPlan few_plan;    // their launches for the current tree
   epochlik::DevBuf few_dev;      // int32: the plan's item lists
-  epochlik::DevBuf few_S;        // T [n_nodes][C][P][Kp]: child vectors P_v L_v
+  epochlik::DevBuf few_S;        // T [n_nodes, without gradient N][C][P][Kp]: child vectors P_v L_v
   epochlik::DevBuf seglist;    // int32 segments grouped by process: offsets [S+1], items [nseg*C]
   epochlik::DevBuf gslots;     // int32 [n]: partial-sum slots written per branch (4-state / 64-state gradient)
   epochlik::DevBuf codon_dev;  // 64-state path: descriptor + work items

@@ -9,8 +9,8 @@
 //     level's matrix rows while it finishes the current one;
 //   - wide levels pack their (node, pattern) items densely (a block per node left 248 of 256
 //     threads idle for 7 states and one pattern);
-//   - the post-order pass keeps every branch's child vector S_v = P_v L_v, which the pre-order pass
-//     and dlogL/dP would otherwise form again from the matrices.
+//   - with a gradient, the post-order pass keeps every branch's child vector S_v = P_v L_v, which the
+//     pre-order pass and dlogL/dP would otherwise form again from the matrices.
 // 522 taxa, 7 states, one column, FP64: the post- and pre-order passes took 294 us in 64 launches and
 // take 77 us in two; 2,000 taxa, 40 states, FP32: 253 us in 44 launches, now 202 us in 23, and dlogL/dP
 // 66 -> 43 us.  What is left of a run is latency: about 0.7 us a level down, 1.2 us up.
@@ -157,7 +157,8 @@ struct FewArgs {
   T* part;
   T* pre;
   int32_t* scales;
-  T* S;  // [n_nodes][C][P][Kp] child vectors
+  T* S;  // [n_nodes, or tips][C][P][Kp] child vectors
+  bool keep;  // every branch's child vector is kept for the gradient (else the tips' of a run, for the run itself)
   const double* pi;
   int root, N, P, K, Kp, C;
   unsigned inv_P;  // ceil(2^32 / P), 0 for one pattern
@@ -198,7 +199,7 @@ __global__ __launch_bounds__(256) void few_post_level_kernel(const FewArgs<T> g,
       va = child_vector(a, N, p, P, K, Kp, i, g.Pm + ((size_t)a * C + c) * KK + (size_t)i * Kp, g.tips, g.amb, sA + own);
       vb = child_vector(b, N, p, P, K, Kp, i, g.Pm + ((size_t)b * C + c) * KK + (size_t)i * Kp, g.tips, g.amb, sB + own);
     }
-    if (ok && i < Kp) {
+    if (g.keep && ok && i < Kp) {
       g.S[(((size_t)a * C + c) * P + p) * Kp + i] = va;
       g.S[(((size_t)b * C + c) * P + p) * Kp + i] = vb;
     }
@@ -306,7 +307,7 @@ __global__ __launch_bounds__(NT) void few_post_run_kernel(const FewArgs<T> g) {
       wave_lds_order();
       r = i < K ? r : T(0);
       mine[i] = r;
-      if (row_ok) g.S[((size_t)br[0] * P + at.p) * Kp + i] = r;
+      if (g.keep && row_ok) g.S[((size_t)br[0] * P + at.p) * Kp + i] = r;
     }
     const T ta = tip_a, tb = tip_b;
     const int ea = out_sa, eb = out_sb;
@@ -529,6 +530,8 @@ __global__ __launch_bounds__(256) void few_grad_kernel(const FewArgs<T> g, const
   if (threadIdx.x == 0) dbranch[v] = d;
 }
 
+bool few_gradient(const EpochConfig& c) { return (c.flags & (EPOCH_GRAD_BRANCH | EPOCH_GRAD_Q | EPOCH_GRAD_TIME)) != 0; }
+
 int few_lanes(const EpochInstance* in) {
   int q = 4;
   while (q < in->Kp) q <<= 1;
@@ -547,6 +550,7 @@ FewArgs<T> few_args(EpochInstance* in) {
   g.pre = static_cast<T*>(in->pre.ptr);
   g.scales = static_cast<int32_t*>(in->scales.ptr);
   g.S = static_cast<T*>(in->few_S.ptr);
+  g.keep = few_gradient(in->cfg);
   g.pi = static_cast<const double*>(in->pi.ptr);
   g.root = in->plan.root;
   g.N = in->N;
@@ -759,17 +763,21 @@ void few_plan(const EpochInstance* in, const int32_t* nodes, const int32_t* leve
   }
 }
 
-// Few patterns on the generic path, all evaluated at once.
-bool few_applies(const EpochInstance* in) {
-  return in->path == 0 && in->budget == 0 && in->P <= kFewMaxPatterns &&
-         (size_t)in->n_nodes * in->C * in->P * in->Kp * in->real_size <= kFewVectorBytes;
+// Few patterns on the generic path, all evaluated at once: bytes of the child vectors, 0 where the
+// per-level kernels run.  Without a gradient only the tips' are kept.
+size_t few_vector_bytes(const EpochConfig& c, int Kp) {
+  const size_t row = (size_t)c.n_categories * c.n_patterns * Kp * (c.precision == EPOCH_FP64 ? 8 : 4);
+  const size_t n_nodes = 2 * (size_t)c.n_tips - 1;
+  if (c.hbm_budget_bytes != 0 || c.n_patterns > kFewMaxPatterns || n_nodes * row > kFewVectorBytes) return 0;
+  return (few_gradient(c) ? n_nodes : c.n_tips) * row;
 }
 
 int few_prepare(EpochInstance* in) {
-  in->few = few_applies(in);
+  const size_t bytes = few_vector_bytes(in->cfg, in->Kp);
+  in->few = bytes != 0;
   if (!in->few) return EPOCH_OK;
   few_plan(in, in->plan.level_nodes.data(), in->plan.level_offset.data(), true, in->few_plan);
-  int rc = ensure(in->few_S, (size_t)in->n_nodes * in->C * in->P * in->Kp * in->real_size);
+  int rc = ensure(in->few_S, bytes);
   if (!rc) rc = ensure(in->few_dev, std::max<size_t>(1, in->few_plan.data.size()) * sizeof(int32_t));
   if (!rc && !in->few_plan.data.empty())
     rc = stage_upload(in, in->few_dev.ptr, in->few_plan.data.data(), in->few_plan.data.size() * sizeof(int32_t));

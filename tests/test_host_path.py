@@ -49,3 +49,14 @@ lik.set_branch_rates(np.arange(1, n - 1), np.full(n - 2, 2.0))
 sent = [l.split() for l in log() if l.startswith("copy") and int(l.split()[2]) == 8 * n]
 assert len(sent) == 1 and float(sent[0][-1]) == prob.branch_rate[0], sent
 """)
+
+
+@pytest.mark.parametrize("grad", [False, True])
+def test_child_vectors_kept_for_a_gradient_only(tmp_path, grad):
+    """Seven states, three columns, 40 taxa: the child vectors of every branch with a gradient, of the tips without."""
+    rows = 79 if grad else 40
+    fake_hip.run(tmp_path, created(states=7, patterns=3, precision="fp64", grad_branch=grad) + f"""
+sizes = [int(l.split()[1]) for l in log() if l.startswith("malloc")]
+one = 3 * 8 * 8
+assert {rows} * one in sizes and {79 + 40 - rows} * one not in sizes, sizes
+""")

@@ -30,7 +30,17 @@ namespace {
 
 constexpr int kFewMaxPatterns = 16;            // more patterns fill the per-level kernels' blocks
 constexpr size_t kFewLds = 64 * 1024;          // LDS of a run of levels, at most, besides its matrix buffers
-constexpr int kFewWide = 2;                    // a level of more items than this many passes of a block is launched alone
+// Blocks of a post-order level launch, until they are full: a block of items from several nodes reads
+// their matrices through one CU, and its wavefronts walk every kind of child among them.  40 states,
+// 64 taxa, one column, FP64, four categories, post-order pass: 177 us in full blocks, 159 in these.
+constexpr int kFewBlocks = 2048;
+constexpr int kFewWide = 2;                    // a level of more items than this many passes of a block is launched alone,
+// and so is one whose matrices are more than one CU reads in about the time of a launch (a lane per row,
+// of more than a cache line from 32 states in FP64 on, reads slower than a wavefront per matrix).  FP64,
+// one category, without gradient, per-level kernels and runs by the number of items alone and by this:
+// 20 states (generic kernels), 64 taxa, 16 columns 104, 162 and 99 us; 12 states, 1,500 taxa, 8 columns
+// 137, 157 and 138; 40 states, 1,500 taxa, one column 219, 195 and 191.
+constexpr size_t few_run_bytes(int lanes) { return (lanes == 32 ? 128 : 256) * 1024; }
 constexpr size_t kFewVectorBytes = 256 << 20;  // child vectors, at most
 
 // Orders LDS accesses of one wavefront (write, then read by other lanes).
@@ -179,11 +189,11 @@ __device__ inline Place place_of(const FewArgs<T>& g, int k) {
 // Post-order, one level: an item is (node, pattern), KQ lanes each.
 template <typename T, int KQ>
 __global__ __launch_bounds__(256) void few_post_level_kernel(const FewArgs<T> g, const int32_t* __restrict__ nodes,
-                                                             int n) {
+                                                             int n, int per) {
   __shared__ T sA[256], sB[256];
-  const int i = threadIdx.x % KQ, item = blockIdx.x * (256 / KQ) + threadIdx.x / KQ;
-  const bool ok = item < n * g.P;
-  const Place at = place_of(g, ok ? item : 0);
+  const int i = threadIdx.x % KQ, item = blockIdx.x * per + threadIdx.x / KQ;
+  const bool ok = (int)threadIdx.x / KQ < per && item < n * g.P;
+  const Place at = place_of(g, ok ? item : blockIdx.x * per);  // idle lanes repeat the block's first item
   const int u = nodes[at.node], p = at.p;
   const int a = g.left[u], b = g.right[u];
   const int N = g.N, P = g.P, K = g.K, Kp = g.Kp, C = g.C;
@@ -562,6 +572,8 @@ FewArgs<T> few_args(EpochInstance* in) {
   return g;
 }
 
+int few_level_items(int items, int kq) { return std::min(256 / kq, std::max(1, (items + kFewBlocks - 1) / kFewBlocks)); }
+
 // LDS of a run (kernel layouts above).
 size_t few_matrix_lds(const EpochInstance* in) {  // every item's matrix buffer
   if (in->Kp <= 32) return 0;
@@ -582,9 +594,9 @@ int few_post_launch(EpochInstance* in, const FewPlan& plan, const int32_t* d_dat
   FewArgs<T> g = few_args<T>(in);
   for (const FewStep& s : plan.post) {
     if (!s.run) {
-      constexpr int per = 256 / KQ;
-      hipLaunchKernelGGL((few_post_level_kernel<T, KQ>), dim3((s.n_nodes * in->P + per - 1) / per), dim3(256), 0,
-                         in->stream, g, d_data + s.at, s.n_nodes);
+      const int items = s.n_nodes * in->P, per = few_level_items(items, KQ);
+      hipLaunchKernelGGL((few_post_level_kernel<T, KQ>), dim3((items + per - 1) / per), dim3((per * KQ + 63) / 64 * 64),
+                         0, in->stream, g, d_data + s.at, s.n_nodes, per);
       continue;
     }
     g.data = d_data + s.at;
@@ -655,7 +667,11 @@ void few_plan(const EpochInstance* in, const int32_t* nodes, const int32_t* leve
   const int kq = few_lanes(in), threads = few_threads(in->fp64, in->Kp), groups = threads / kq;
   const size_t row = (size_t)P * kq * in->real_size;
   auto width = [&](int l) { return level_off[l + 1] - level_off[l]; };
-  auto narrow = [&](int l) { return in->C == 1 && width(l) * P <= kFewWide * groups; };
+  const size_t pair = 2 * (size_t)in->Kp * in->Kp * in->real_size;  // an item's matrices
+  auto narrow = [&](int l) {
+    const int items = width(l) * P;
+    return in->C == 1 && items <= kFewWide * groups && items * pair <= few_run_bytes(kq);
+  };
   std::vector<int32_t> slot(in->n_nodes, -1);
   // post-order, lowest level first
   for (int l = 1; l <= pl.n_levels;) {
@@ -764,10 +780,13 @@ void few_plan(const EpochInstance* in, const int32_t* nodes, const int32_t* leve
 }
 
 // Few patterns on the generic path, all evaluated at once: bytes of the child vectors, 0 where the
-// per-level kernels run.  Without a gradient only the tips' are kept.
+// per-level kernels run.  Without a gradient only the tips' are kept, and several categories, which no
+// run serves, leave nothing to gain: 16 states, 1,000 taxa, one column, FP64, four categories 247 us
+// by the per-level kernels and 322 by these.
 size_t few_vector_bytes(const EpochConfig& c, int Kp) {
   const size_t row = (size_t)c.n_categories * c.n_patterns * Kp * (c.precision == EPOCH_FP64 ? 8 : 4);
   const size_t n_nodes = 2 * (size_t)c.n_tips - 1;
+  if (!few_gradient(c) && c.n_categories > 1) return 0;
   if (c.hbm_budget_bytes != 0 || c.n_patterns > kFewMaxPatterns || n_nodes * row > kFewVectorBytes) return 0;
   return (few_gradient(c) ? n_nodes : c.n_tips) * row;
 }

@@ -6,13 +6,14 @@ import fake_hip
 
 CREATE = """
 rng = np.random.default_rng(5)
-prob = W.random_problem(rng, {taxa}, {states}, {patterns}, n_categories=1, n_intervals=2, reversible=True)
+prob = W.random_problem(rng, {taxa}, {states}, {patterns}, n_categories={categories}, n_intervals=2, reversible=True)
 lik = from_problem(prob, {precision!r}, **{flags!r})
 """
 
 
-def created(states=4, taxa=40, patterns=50, precision="fp32", **flags):
-    return CREATE.format(states=states, taxa=taxa, patterns=patterns, precision=precision, flags=flags)
+def created(states=4, taxa=40, patterns=50, categories=1, precision="fp32", **flags):
+    return CREATE.format(states=states, taxa=taxa, patterns=patterns, categories=categories, precision=precision,
+                         flags=flags)
 
 
 @pytest.mark.parametrize("flags", [{"grad_branch": True}, {"grad_branch": True, "grad_Q": True}])
@@ -60,3 +61,27 @@ sizes = [int(l.split()[1]) for l in log() if l.startswith("malloc")]
 one = 3 * 8 * 8
 assert {rows} * one in sizes and {79 + 40 - rows} * one not in sizes, sizes
 """)
+
+
+def launched(tmp_path, evaluate="", **kw):
+    """Names of the kernels one evaluation launches, shortened to what stands before the template's arguments."""
+    out = fake_hip.run(tmp_path, created(**kw) + f"""
+fake.fake_clear()
+lik.evaluate({evaluate})
+print("\\n".join(l.split()[2] for l in log() if l.startswith("launch")))
+""")
+    return out.split()
+
+
+@pytest.mark.parametrize("states, patterns, flags, kernel, absent", [
+    # no gradient to keep child vectors for, and no run of several categories
+    (16, 1, {"categories": 4}, "post_level_generic", "few_"),
+    (16, 1, {"categories": 4, "grad_branch": True}, "few_post_level", "post_level_generic"),
+    # a lane per 256-byte row: sixteen columns of one node are more than a run's level takes
+    (20, 16, {"kernel": "generic", "grad_branch": True}, "few_post_level", "few_post_run"),
+    (7, 1, {"grad_branch": True}, "few_post_run", "post_level"),
+    (7, 1, {}, "few_post_run", "post_level"),
+])
+def test_kernels_for_few_patterns(tmp_path, states, patterns, flags, kernel, absent):
+    names = launched(tmp_path, states=states, patterns=patterns, precision="fp64", taxa=64, **flags)
+    assert any(kernel in n for n in names) and not any(absent in n for n in names), names

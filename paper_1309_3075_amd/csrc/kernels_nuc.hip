@@ -19,6 +19,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <utility>
 #include <vector>
 
@@ -757,18 +758,29 @@ int tiles_per_wave(int tiles, int n_l, int r_min, int r_max, long target_waves) 
 }
 
 // Whether n nodes on `levels` tree levels are formed faster by one launch over the list than by a
-// launch per level.  Model in microseconds, from timings of whole trees and of the paths above one
-// branch (16 to 190 taxa, 100 to 100,000 patterns, 4 categories): a level launch costs 5.5 plus 0.49
-// per MB of a node's vectors; a node of the list costs a wavefront 1.1 (FP32) or 1.3 (FP64), and
-// 0.65 or 1.25 times the wavefronts per SIMD once they share its arithmetic units.  Measured,
-// levels against list: FP32 16 taxa x 1,000 patterns 52 -> 39 us, 48 x 20,011 108 -> 72, 190 x 1,000
-// 99 -> 175; FP64 100 x 20,011 206 -> 139, 190 x 5,003 164 -> 218.
+// launch per level.  Model in microseconds, fitted to 374 whole trees (8 to 220 taxa, 64 to 50,000
+// patterns, 1 to 8 categories, both precisions), each evaluated both ways.  A node of the list costs its
+// serial step, which grows with the matrices a block stages, and more the more wavefronts share a SIMD;
+// a level launch costs itself plus a share of its nodes' vectors, which grows with the wavefronts per
+// pattern.  The form it picks was slower than the other by more than 2 % in 9 of the 374, by 15 % at
+// most.  Whole evaluations, levels against list: FP32, four categories, 16 taxa x 1,000 patterns 38
+// and 35 us, 100 x 10,000 93 and 106; FP64, four categories, 16 x 1,000 47 and 36; one category,
+// 150 x 50,000 121 and 147.
 bool list_serves(const EpochInstance* in, int n, int levels) {
   const int TPW = 64 / cp_of(in->C);
-  const double waves = (in->P + TPW - 1) / TPW, simds = 1024.0;
-  const double mb = (double)in->C * in->P * 4 * in->real_size * 1e-6;
-  const double list = n * std::max(in->fp64 ? 1.3 : 1.1, (in->fp64 ? 1.25 : 0.65) * waves / simds);
-  return 1.15 * list < 5.5 * levels + 0.49 * mb * n;
+  const double waves = (in->P + TPW - 1) / TPW / 1024.0;  // per SIMD
+  const double mb = (double)in->C * in->P * 4 * in->real_size * 1e-6, split = std::log2((double)in->C);
+  double node, launch, per_mb;
+  if (in->fp64) {
+    node = std::max(1.0 + 0.11 * in->C + 0.35 * waves, (0.75 + 0.125 * in->C) * waves);
+    launch = in->C <= 2 ? 5.3 : 6.3;
+    per_mb = 0.25 + 0.2 * split;
+  } else {
+    node = 0.95 + 0.06 * in->C + 0.18 * waves;
+    launch = 5.2;
+    per_mb = std::min(0.5, 0.3 + 0.2 * split);
+  }
+  return n * node < launch * levels + per_mb * mb * n;
 }
 
 // The listed nodes as one launch's operations, ordered so that a node soon follows its children;

@@ -85,3 +85,13 @@ print("\\n".join(l.split()[2] for l in log() if l.startswith("launch")))
 def test_kernels_for_few_patterns(tmp_path, states, patterns, flags, kernel, absent):
     names = launched(tmp_path, states=states, patterns=patterns, precision="fp64", taxa=64, **flags)
     assert any(kernel in n for n in names) and not any(absent in n for n in names), names
+
+
+@pytest.mark.parametrize("taxa, patterns, categories, precision, listed", [
+    (16, 1000, 4, "fp64", True), (100, 20011, 4, "fp64", True),
+    (150, 50000, 1, "fp64", False), (150, 20000, 4, "fp32", False)])
+def test_short_list_or_levels(tmp_path, taxa, patterns, categories, precision, listed):
+    """Either form where it was measured the faster one."""
+    names = launched(tmp_path, taxa=taxa, patterns=patterns, categories=categories, precision=precision)
+    assert any("nuc_post_list" in n for n in names) == listed, names
+    assert any("nuc_post_level" in n for n in names) != listed, names

@@ -621,11 +621,6 @@ int epoch_batch_evaluate(EpochBatch* b, uint32_t what, double* logL) {
   what |= kLogL;
   int rc = check_members(b, what);
   if (rc) return rc;
-  if (b->merged && !b->tuned) {
-    rc = autotune(b);
-    if (rc) return rc;
-    b->tuned = true;
-  }
   // a member's setters may have left copies or launches on its own stream
   for (EpochInstance* in : b->insts)
     if (in->async_pending) {
@@ -633,6 +628,11 @@ int epoch_batch_evaluate(EpochBatch* b, uint32_t what, double* logL) {
       if (rc) return rc;
       in->async_pending = false;
     }
+  if (b->merged && !b->tuned) {
+    rc = autotune(b);
+    if (rc) return rc;
+    b->tuned = true;
+  }
   rc = replay(b, what);
   if (rc) return rc;
   const size_t n = b->insts.size();

@@ -95,3 +95,18 @@ def test_short_list_or_levels(tmp_path, taxa, patterns, categories, precision, l
     names = launched(tmp_path, taxa=taxa, patterns=patterns, categories=categories, precision=precision)
     assert any("nuc_post_list" in n for n in names) == listed, names
     assert any("nuc_post_level" in n for n in names) != listed, names
+
+
+def test_batch_waits_for_its_members_before_it_tunes(tmp_path):
+    """What a setter left on a member's stream is waited for before the batch's first replay, a timed one."""
+    fake_hip.run(tmp_path, created(states=61, taxa=6, patterns=20) + """
+other = from_problem(prob, "fp32")
+batch = EpochBatchEvaluator([lik, other])
+lik.set_branch_rates([0], [2.0])
+fake.fake_clear()
+batch.evaluate(grad_branch=False)
+lines = log()
+first = next(i for i, l in enumerate(lines) if l.startswith("graph"))
+assert "sync (nil)" in lines[:first], lines[:first]
+assert sum(l.startswith("graph") for l in lines) > 6  # it tuned
+""")

@@ -250,6 +250,15 @@ void invalidate_downstream(EpochInstance* in) {
   in->logL_valid = false;
 }
 
+// What an instance of this size hands over through its staging buffer at most, so that one allocation serves every later
+// call: the rates of all branches, a restricted pass' lists (branches and their chain items, nodes, the
+// matrix-core kernels' items or the few-pattern kernels' lists), a tree's few-pattern lists.  Trees of a
+// million nodes or so, where that is past 64 MB, grow it on demand.
+size_t stage_bound(const EpochInstance* in) {
+  const size_t per_branch = sizeof(int32_t) + sizeof(int4);
+  const size_t per_node = sizeof(int32_t) + std::max(in->C * sizeof(int4), 19 * sizeof(int32_t));
+  return std::min<size_t>(in->n_nodes * per_branch + in->n_int * per_node + 1024, 64 << 20);
+}
 // The instance's pinned staging buffer: what a setter hands over is copied there and read by work
 // enqueued on the instance's stream without waiting; the next use waits (stage_event) first.
 int stage_reserve(EpochInstance* in, size_t bytes) {
@@ -261,15 +270,21 @@ int stage_reserve(EpochInstance* in, size_t bytes) {
   if (in->stage_bytes >= bytes) return EPOCH_OK;
   // the evaluation's results share the allocation (every evaluation needs an eigensystem first); the
   // present buffer is kept until the larger one is there, so host_out stays valid when it is refused
-  const size_t at = (bytes + 255) / 256 * 256;
+  const size_t results = Delivery::doubles(in) * sizeof(double);
   void* larger = nullptr;
-  if (hipHostMalloc(&larger, at + Delivery::doubles(in) * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+  for (const size_t room : {std::max(bytes, stage_bound(in)), bytes}) {
+    const size_t at = (room + 255) / 256 * 256;
+    if (hipHostMalloc(&larger, at + results, hipHostMallocDefault) == hipSuccess) {
+      bytes = at;
+      break;
+    }
+    larger = nullptr;
     (void)hipGetLastError();
-    return set_error(EPOCH_ERR_OOM, "pinned staging buffer of %zu bytes", bytes);
   }
+  if (!larger) return set_error(EPOCH_ERR_OOM, "pinned staging buffer of %zu bytes", bytes);
   if (in->stage_host) (void)hipHostFree(in->stage_host);
   in->stage_host = larger;
-  in->host_out = reinterpret_cast<double*>(static_cast<char*>(in->stage_host) + at);
+  in->host_out = reinterpret_cast<double*>(static_cast<char*>(in->stage_host) + bytes);
   in->stage_bytes = bytes;
   return EPOCH_OK;
 }

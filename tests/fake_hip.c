@@ -12,6 +12,7 @@
 static char log_text[1 << 22];
 static size_t log_used;
 static int fail_host_mallocs; /* pinned allocations still to fail */
+static int fail_copies;       /* asynchronous copies still to fail */
 static uintptr_t next_handle = 0x1000;
 
 static void note(const char* fmt, ...) {
@@ -23,6 +24,7 @@ static void note(const char* fmt, ...) {
 const char* fake_log(void) { return log_text; }
 void fake_clear(void) { log_used = 0, log_text[0] = 0; }
 void fake_fail_host_mallocs(int n) { fail_host_mallocs = n; }
+void fake_fail_copies(int n) { fail_copies = n; }
 
 /* kernels by the address of their host stub */
 static struct { const void* stub; char name[160]; } kernels[4096];
@@ -80,6 +82,10 @@ hipError_t hipHostFree(void* p) { note("hostfree\n"); free(p); return hipSuccess
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind k) { (void)k; memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind k, hipStream_t st) {
   (void)k;
+  if (fail_copies) {
+    --fail_copies;
+    return hipErrorInvalidValue;
+  }
   double first = 0;
   if (n >= sizeof(first)) memcpy(&first, s, sizeof(first));
   note("copy %p %zu first %.17g\n", (void*)st, n, first);

@@ -39,12 +39,12 @@ def test_refused_branch_rates_change_nothing(tmp_path):
     """Rates of a call that returned an error are not handed over by a later one."""
     fake_hip.run(tmp_path, created(grad_branch=True) + """
 n = prob.parent.shape[0]
-fake.fake_fail_host_mallocs(1)
+fake.fake_fail_copies(1)
 try:
     lik.set_branch_rates(np.arange(70), np.full(70, 3.0))
     assert False
 except _abi.EpochError as e:
-    assert e.code == _abi.EPOCH_ERR_OOM
+    assert e.code == _abi.EPOCH_ERR_HIP
 fake.fake_clear()
 lik.set_branch_rates(np.arange(1, n - 1), np.full(n - 2, 2.0))
 sent = [l.split() for l in log() if l.startswith("copy") and int(l.split()[2]) == 8 * n]
@@ -109,4 +109,20 @@ lines = log()
 first = next(i for i, l in enumerate(lines) if l.startswith("graph"))
 assert "sync (nil)" in lines[:first], lines[:first]
 assert sum(l.startswith("graph") for l in lines) > 6  # it tuned
+""")
+
+
+@pytest.mark.parametrize("kw", [{}, {"precision": "fp64"}, {"states": 7, "patterns": 2}, {"states": 61, "patterns": 90}])
+def test_proposals_allocate_no_pinned_memory(tmp_path, kw):
+    """Lists of any length, and more rates at once than travel in a launch's arguments."""
+    fake_hip.run(tmp_path, created(**kw) + """
+lik.set_option("tree_walk", 0)
+lik.evaluate()
+n = prob.parent.shape[0]
+fake.fake_clear()
+for k in (1, 4, 16, 64, n - 1):
+    lik.set_branch_rates(np.arange(k), np.full(k, 1.5))
+    lik.evaluate()
+assert lik.work_counts()[0] > 0
+assert not [l for l in log() if l.startswith("host")], log()
 """)

@@ -107,9 +107,11 @@ typedef struct EpochConfig {
   void* workspace;         /* NULL, or caller-owned device memory (e.g. a torch tensor) of
                             * workspace_bytes bytes that holds the pattern-sized buffers (tip
                             * states, weights, partials, outside vectors, scale exponents,
-                            * per-pattern log-likelihoods); it must stay allocated until
-                            * epoch_destroy.  Not combinable with hbm_budget_bytes. */
-  int64_t workspace_bytes; /* >= epoch_workspace_bytes(cfg) when workspace is set */
+                            * per-pattern log-likelihoods, and for at most 16 patterns on the
+                            * generic kernels the child vectors P_v L_v); it must stay allocated
+                            * until epoch_destroy.  Not combinable with hbm_budget_bytes. */
+  int64_t workspace_bytes; /* epoch_workspace_bytes(cfg) when workspace is set; one without room
+                            * for the child vectors alone is taken, and runs slower kernels */
 } EpochConfig;
 
 /* Message for the last non-zero return on this thread ("" if none). */

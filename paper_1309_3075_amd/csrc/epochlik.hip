@@ -112,6 +112,7 @@ struct WorkspaceItem {
   size_t bytes;
 };
 size_t scale_sets(const EpochConfig& c);
+bool generic_config(const EpochConfig& c);
 std::vector<WorkspaceItem> workspace_items(const EpochConfig& c, int Kp) {
   const size_t N = c.n_tips, P = c.n_patterns, C = c.n_categories, R = c.precision == EPOCH_FP64 ? 8 : 4;
   const bool grad = (c.flags & (EPOCH_GRAD_BRANCH | EPOCH_GRAD_Q | EPOCH_GRAD_TIME)) != 0;
@@ -122,12 +123,21 @@ std::vector<WorkspaceItem> workspace_items(const EpochConfig& c, int Kp) {
                                   {&EpochInstance::scales, (N - 1) * P * sizeof(int32_t) * scale_sets(c)},
                                   {&EpochInstance::site, P * sizeof(double)}};
   if (grad) v.push_back({&EpochInstance::pre, (N - 1) * C * P * Kp * R});
+  const size_t few = generic_config(c) ? few_vector_bytes(c, Kp) : 0;
+  if (few) v.push_back({&EpochInstance::few_S, few});
   return v;
 }
 size_t aligned256(size_t b) { return (b + 255) / 256 * 256; }
 size_t workspace_total(const EpochConfig& c, int Kp) {
   size_t t = 0;
   for (const auto& it : workspace_items(c, Kp)) t += aligned256(it.bytes);
+  return t;
+}
+// The least a workspace has to hold: without room for the child vectors the per-level kernels run.
+size_t workspace_least(const EpochConfig& c, int Kp) {
+  size_t t = 0;
+  for (const auto& it : workspace_items(c, Kp))
+    if (it.buf != &EpochInstance::few_S) t += aligned256(it.bytes);
   return t;
 }
 
@@ -146,6 +156,9 @@ bool codon_config(const EpochConfig& c) {
   return ((c.n_states > 48 && c.n_states <= 64) || (c.n_states > 16 && c.n_states <= 32)) &&
          c.kernel_path == EPOCH_KERNEL_AUTO &&
          (c.hbm_budget_bytes == 0 || (c.n_categories == 1 && c.precision == EPOCH_FP32));
+}
+bool generic_config(const EpochConfig& c) {
+  return c.kernel_path == EPOCH_KERNEL_GENERIC || (c.n_states != 4 && !codon_config(c));
 }
 int padded_states(const EpochConfig& c) { return padded_states(c.n_states); }
 // The 64-state kernels keep one scale exponent and one weight row per rate category.
@@ -346,9 +359,9 @@ int epoch_create(const EpochConfig* cfg, EpochInstance** out) {
                      (long long)c.hbm_budget_bytes, chunk_pattern_bytes * (size_t)std::min(c.n_patterns, 64));
   if (c.workspace && c.hbm_budget_bytes > 0)
     return set_error(EPOCH_ERR_ARG, "a workspace cannot be combined with hbm_budget_bytes");
-  if (c.workspace && (c.workspace_bytes < 0 || (size_t)c.workspace_bytes < workspace_total(c, padded_states(c))))
-    return set_error(EPOCH_ERR_ARG, "workspace_bytes %lld is below the %zu bytes epoch_workspace_bytes asks for",
-                     (long long)c.workspace_bytes, workspace_total(c, padded_states(c)));
+  if (c.workspace && (c.workspace_bytes < 0 || (size_t)c.workspace_bytes < workspace_least(c, padded_states(c))))
+    return set_error(EPOCH_ERR_ARG, "workspace_bytes %lld is below the %zu bytes this configuration needs at least",
+                     (long long)c.workspace_bytes, workspace_least(c, padded_states(c)));
   if (c.workspace && (reinterpret_cast<uintptr_t>(c.workspace) & 255))
     return set_error(EPOCH_ERR_ARG, "workspace must be 256-byte aligned");
   const size_t N = c.n_tips, P = c.n_patterns;
@@ -389,6 +402,7 @@ int epoch_create(const EpochConfig* cfg, EpochInstance** out) {
   if (c.workspace) {  // pattern-sized buffers inside the caller's memory
     size_t off = 0;
     for (const auto& it : workspace_items(c, (int)Kp)) {
+      if (off + it.bytes > (size_t)c.workspace_bytes) break;  // the child vectors, which come last
       DevBuf& b = in->*(it.buf);
       b.ptr = static_cast<char*>(c.workspace) + off;
       b.bytes = std::max<size_t>(it.bytes, 256);
@@ -435,6 +449,9 @@ int epoch_create(const EpochConfig* cfg, EpochInstance** out) {
     A(in->scales, (N - 1) * P * sizeof(int32_t) * scale_sets(c));
     if (grad) A(in->pre, (N - 1) * C * P * Kp * R);
   }
+  // without room for the child vectors the generic path keeps to its per-level kernels
+  if (const size_t few = generic_config(c) && !c.workspace ? few_vector_bytes(c, (int)Kp) : 0; few && rc == EPOCH_OK)
+    (void)ensure(in->few_S, few);
   A(in->site, P * sizeof(double));
   A(in->blocksum, ((P + 15) / 16 + 1) * sizeof(double));  // a root block serves 16 patterns at least
   A(in->arrived, sizeof(unsigned));

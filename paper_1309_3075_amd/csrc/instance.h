@@ -342,6 +342,7 @@ int launch_pstage_generic(EpochInstance* in);
 int launch_pstage_generic_nodes(EpochInstance* in, const int32_t* d_nodes, int n);  // listed branches only
 // few patterns (kernels_few.hip)
 int few_prepare(EpochInstance* in);
+size_t few_vector_bytes(const EpochConfig& c, int Kp);  // a generic path's child vectors, 0: per-level kernels
 void few_plan(const EpochInstance* in, const int32_t* nodes, const int32_t* level_off, bool with_pre, FewPlan& out);
 int launch_few_post(EpochInstance* in, const FewPlan& plan, const int32_t* d_data);
 int launch_few_pre(EpochInstance* in);

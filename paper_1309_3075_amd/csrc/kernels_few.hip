@@ -792,15 +792,12 @@ size_t few_vector_bytes(const EpochConfig& c, int Kp) {
 }
 
 int few_prepare(EpochInstance* in) {
-  const size_t bytes = few_vector_bytes(in->cfg, in->Kp);
-  in->few = bytes != 0;
+  in->few = in->few_S.ptr != nullptr;
   if (!in->few) return EPOCH_OK;
   few_plan(in, in->plan.level_nodes.data(), in->plan.level_offset.data(), true, in->few_plan);
-  int rc = ensure(in->few_S, bytes);
-  if (!rc) rc = ensure(in->few_dev, std::max<size_t>(1, in->few_plan.data.size()) * sizeof(int32_t));
-  if (!rc && !in->few_plan.data.empty())
-    rc = stage_upload(in, in->few_dev.ptr, in->few_plan.data.data(), in->few_plan.data.size() * sizeof(int32_t));
-  return rc;
+  const int rc = ensure(in->few_dev, std::max<size_t>(1, in->few_plan.data.size()) * sizeof(int32_t));
+  if (rc || in->few_plan.data.empty()) return rc;
+  return stage_upload(in, in->few_dev.ptr, in->few_plan.data.data(), in->few_plan.data.size() * sizeof(int32_t));
 }
 
 #define EPOCH_FEW(T, FN, ...)                            \

@@ -32,3 +32,22 @@ def test_levels(states, taxa, patterns, categories, precision):
         assert np.max(np.abs(got[1] - want[1])) <= TOL[precision] * np.max(np.abs(want[1]))
         if grad:
             assert_grad(got[2], want[2], TOL_GRAD[precision], "dlogL/dl")
+
+
+@pytest.mark.parametrize("room", [True, False])
+def test_workspace(room):
+    """The child vectors in a caller's memory, and per-level kernels in one without room for them."""
+    import torch
+    from paper_1309_3075_amd.likelihood import EpochLikelihood
+    prob = W.random_problem(np.random.default_rng(8), 30, 7, 2, n_intervals=3, missing_frac=0.1)
+    need = EpochLikelihood.workspace_bytes(30, 2, 7, 1, "fp64", grad_branch=True)
+    vectors = 59 * 2 * 8 * 8
+    ws = torch.zeros(need - (0 if room else -(-vectors // 256) * 256), dtype=torch.uint8, device="cuda")
+    with from_problem(prob, "fp64", grad_branch=True, workspace=ws) as lik:
+        got = lik.evaluate(branch=True, site=True)
+    torch.cuda.synchronize()
+    with from_problem(prob, "fp64", grad_branch=True) as lik:
+        want = lik.evaluate(branch=True, site=True)
+    assert rel(got[0], want[0]) <= TOL["fp64"]
+    assert np.max(np.abs(got[1] - want[1])) <= TOL["fp64"] * np.max(np.abs(want[1]))
+    assert_grad(got[2], want[2], TOL_GRAD["fp64"], "dlogL/dl")

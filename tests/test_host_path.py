@@ -126,3 +126,37 @@ for k in (1, 4, 16, 64, n - 1):
 assert lik.work_counts()[0] > 0
 assert not [l for l in log() if l.startswith("host")], log()
 """)
+
+
+@pytest.mark.parametrize("states, categories, grad", [(7, 1, True), (7, 1, False), (14, 3, True), (14, 3, False)])
+def test_workspace_holds_the_child_vectors(tmp_path, states, categories, grad):
+    """With a workspace nothing pattern-sized is allocated beside it; one without room for the child vectors
+    is taken, by the per-level kernels; one below that is refused."""
+    fake_hip.run(tmp_path, created(states=states, patterns=3, categories=categories, precision="fp64") + f"""
+class Workspace:
+    def __init__(self, n):
+        self.n, self.raw = n, ctypes.create_string_buffer(n + 256)
+    def data_ptr(self): return (ctypes.addressof(self.raw) + 255) // 256 * 256
+    def numel(self): return self.n
+    def element_size(self): return 1
+
+C, P, K, N = {categories}, 3, {states}, 40
+row, rows = C * P * (8 if K == 7 else 16) * 8, (2 * N - 1 if {grad} else N)
+few = rows * row if {grad} or C == 1 else 0
+full = EpochLikelihood.workspace_bytes(N, P, K, C, "fp64", grad_branch={grad})
+least = full - -(-few // 256) * 256
+for n in (full, least, least - 1):
+    fake.fake_clear()
+    try:
+        lik = from_problem(prob, "fp64", grad_branch={grad}, workspace=Workspace(n))
+    except _abi.EpochError as e:
+        assert e.code == _abi.EPOCH_ERR_ARG and n < least
+        continue
+    assert n >= least
+    lik.evaluate(branch={grad})
+    lines = log()
+    assert not few or "malloc %d" % few not in lines
+    assert any("few_post" in l for l in lines) == bool(few and n == full), (n, few)
+    assert any("post_level_generic" in l for l in lines) == (not few or n == least), (n, few)
+    lik.close()
+""")

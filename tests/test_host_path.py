@@ -160,3 +160,15 @@ for n in (full, least, least - 1):
     assert any("post_level_generic" in l for l in lines) == (not few or n == least), (n, few)
     lik.close()
 """)
+
+
+@pytest.mark.parametrize("last, blocks", [(1, 65), (1041, 66), (4096, 256), (4097, 65)])
+def test_root_blocks_of_pattern_chunks(tmp_path, last, blocks):
+    """Chunks of 4,160 patterns and a last one: the root launches hold the blocks of the chunk with the most."""
+    out = fake_hip.run(tmp_path, created(states=20, taxa=4, patterns=4160 + last, hbm_budget_bytes=4160 * 3 * 132) + """
+assert lik.kernel_path() == "matrix_core64"
+fake.fake_clear()
+lik.evaluate()
+print("\\n".join(l for l in log() if "codon_root" in l))
+""")
+    assert [int(l.split()[3]) for l in out.splitlines()] == [blocks] * 2, out

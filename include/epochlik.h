@@ -305,10 +305,11 @@ int epoch_get_timing(EpochInstance* inst, double* ms_out, int64_t* counts_out);
  *   EPOCH_OPT_LEVEL_MIN_TILES: 1..64 (default 8): fewest pattern tiles a
  *     wavefront of the 4-state pre-order level kernels walks; smaller values
  *     give narrow levels more wavefronts and more dlogL/dP partial sums.
- *   EPOCH_OPT_CHAIN_SPLIT: 0..2^30 (default 16 in FP32, between 8 and 16 by
- *     the size of the tree in FP64): on the matrix-core P stage and dlogL/dQ chain, a branch whose
- *     ordered product has at least this many segments is computed as parts in
- *     parallel and combined (the same quantities, rounded differently); 0 = never.
+ *   EPOCH_OPT_CHAIN_SPLIT: -1..2^30: on the matrix-core P stage and dlogL/dQ
+ *     chain, a branch whose ordered product has at least this many segments is
+ *     computed as parts in parallel and combined (the same quantities, rounded
+ *     differently); 0 = never; -1 (default) = 16 in FP32, between 8 and 16 by
+ *     the size of the tree in FP64.
  *   EPOCH_OPT_TARGET_BLOCKS: 1..2^30 (default 1024): on the 64-state path,
  *     the blocks each tree-level launch aims for (it sets how many 64-pattern
  *     tiles a block walks, and so the number of dlogL/dP partial sums).

@@ -1124,7 +1124,7 @@ int epoch_set_option(EpochInstance* in, int32_t key, int64_t value) {
       if (int rc = fastpath_init(in)) return rc;
       break;
     case EPOCH_OPT_CHAIN_SPLIT:
-      if (value < 0 || value > (1 << 30)) return set_error(EPOCH_ERR_ARG, "EPOCH_OPT_CHAIN_SPLIT out of range");
+      if (value < -1 || value > (1 << 30)) return set_error(EPOCH_ERR_ARG, "EPOCH_OPT_CHAIN_SPLIT out of range");
       in->chain_split_min = (int)value;
       // the parts' scratch (prefixes, suffixes) belongs to the P stage that formed it: evaluate again
       in->P_valid = in->partials_valid = in->logL_valid = false;

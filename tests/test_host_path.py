@@ -6,14 +6,14 @@ import fake_hip
 
 CREATE = """
 rng = np.random.default_rng(5)
-prob = W.random_problem(rng, {taxa}, {states}, {patterns}, n_categories={categories}, n_intervals=2, reversible=True)
+prob = W.random_problem(rng, {taxa}, {states}, {patterns}, n_categories={categories}, n_intervals={intervals}, reversible=True)
 lik = from_problem(prob, {precision!r}, **{flags!r})
 """
 
 
-def created(states=4, taxa=40, patterns=50, categories=1, precision="fp32", **flags):
-    return CREATE.format(states=states, taxa=taxa, patterns=patterns, categories=categories, precision=precision,
-                         flags=flags)
+def created(states=4, taxa=40, patterns=50, categories=1, intervals=2, precision="fp32", **flags):
+    return CREATE.format(states=states, taxa=taxa, patterns=patterns, categories=categories, intervals=intervals,
+                         precision=precision, flags=flags)
 
 
 @pytest.mark.parametrize("flags", [{"grad_branch": True}, {"grad_branch": True, "grad_Q": True}])
@@ -172,3 +172,26 @@ lik.evaluate()
 print("\\n".join(l for l in log() if "codon_root" in l))
 """)
     assert [int(l.split()[3]) for l in out.splitlines()] == [blocks] * 2, out
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_chain_split_back_to_its_default(tmp_path, precision):
+    """The line on long epoch chains that an instance chose by itself can be had back (-1)."""
+    fake_hip.run(tmp_path, created(states=20, patterns=2, intervals=40, precision=precision) + """
+def launches():
+    fake.fake_clear()
+    lik.evaluate()
+    return [l.split()[2:] for l in log() if l.startswith("launch")]
+
+default = launches()
+lik.set_option("chain_split", 0)
+assert launches() != default  # some chain was cut
+lik.set_option("chain_split", -1)
+assert launches() == default
+for bad in (-2, (1 << 30) + 1):
+    try:
+        lik.set_option("chain_split", bad)
+        assert False
+    except _abi.EpochError as e:
+        assert e.code == _abi.EPOCH_ERR_ARG
+""")

@@ -628,7 +628,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 || NT == 2 ? 2 : 1) void codon_
   __shared__ __align__(16) T sT[TILE * LDP];  // t of one side for the block tile, pattern-major
   __shared__ __align__(16) T sL[TILE * LDP];  // that side's child partials for the block tile
   __shared__ __align__(16) T sCF[TILE];         // w_p / L_p of the block tile
-  __shared__ __align__(16) int sCol[2][TILE];   // tip columns of the block tile
+  __shared__ __align__(16) int sCol[2][TILE];   // tip columns of the block tile (where sL does not hold their indicator)
   const int4 it = items[blockIdx.y];
   const CodonProblem& pr = probs[it.x];
   const int N = pr.N, P = pr.P, K = pr.K;
@@ -709,8 +709,10 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 || NT == 2 ? 2 : 1) void codon_
       const int p = p0 + drow<T>(g, v);
       if (r == 0) {
         sCF[WT * w + drow<T>(g, v)] = (p < P && sum > T(0)) ? wts[v] / sum : T(0);
-        if (!La) sCol[0][WT * w + drow<T>(g, v)] = cola[v];
-        if (!Lb) sCol[1][WT * w + drow<T>(g, v)] = colb[v];
+        if constexpr (!tip_bf16<NT, AMB, T>()) {
+          if (!La) sCol[0][WT * w + drow<T>(g, v)] = cola[v];
+          if (!Lb) sCol[1][WT * w + drow<T>(g, v)] = colb[v];
+        }
       }
     }
     // loads of this wavefront's part of the next tile, in flight during the rest
@@ -900,7 +902,8 @@ __global__ __launch_bounds__(512, 1) void codon_pre_split_kernel(const CodonProb
         const int p = p0 + 4 * g + v;
         if (r == 0) sh.sCF[WT * w + 4 * g + v] = (p < P && sum > 0.f) ? gptr(pr.weightsT)[p] / sum : 0.f;
       }
-      if (r == 0 && !Lc) sh.sCol[s][WT * w + 4 * g + v] = col[v];
+      if constexpr (!tip_bf16<4, AMB, float>())
+        if (r == 0 && !Lc) sh.sCol[s][WT * w + 4 * g + v] = col[v];
     }
     if (bt + 1 < n_tiles) split_load_tile(nxt, pr, Lc, Qu, c, p0 + TILE, g, r);
 #pragma unroll

@@ -815,6 +815,8 @@ int build_chain_items(EpochInstance* in, const std::vector<int32_t>& off) {  // 
     }
   }
   std::stable_sort(split.begin(), split.end(), [](const int4& a, const int4& b) { return a.z - a.y > b.z - b.y; });
+  in->chain_longest = whole.front().z;
+  in->chain_longest_part = split.front().z - split.front().y;
   in->n_chain_split_items = (int)split.size();
   in->n_chain_splits = (int)info.size();
   in->chain_max_tail = max_tail;

@@ -234,6 +234,7 @@ struct EpochInstance {
   // transpose [Kp][Kp] (compute type)
   epochlik::DevBuf chain_scratch;
   int n_chain_split_items = 0, n_chain_splits = 0, chain_max_tail = 0;
+  int chain_longest = 0, chain_longest_part = 0;  // segments of the longest whole chain, and of the longest item when some are cut
   int chain_split_min = -1;        // chains of at least this many segments are cut (0: never, -1: by the tree's work)
   bool pstage_split = false;       // the last P stage launched ran the split items (the dQ chain follows it)
   epochlik::DevBuf dQ;         // double [S][Kp][Kp]

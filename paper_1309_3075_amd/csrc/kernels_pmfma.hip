@@ -47,13 +47,23 @@ __device__ inline T* chain_mat(void* scratch, int slot, int C, int c, int part, 
 // for pstage_combine_kernel).  With GRAD one wavefront carries both X and D (each
 // operand of V and V^-1 then feeds two products), or, with APART, a block has a
 // wavefront for X and one for D, which takes the X V that its step reads from
-// LDS.  A chain's products are serial, each 4 NT^2 matrix instructions of 64
-// cycles in FP64, so a launch that does not fill the chip lasts as long as its
-// longest chain, and the two wavefronts, on SIMDs of their own, halve that; a
-// full one is bound by the operands.  61 states, 254 branches of up to 4
-// segments (1,016 units): 40 us together, 28 apart; 16 such problems (some
-// 16,000): 206 and 274; 40 states, 3,998 branches (12,000): 95 and 91.
-constexpr int kApartUnits = 4096;
+// LDS: the same products in the same order.  A chain's products are serial, each
+// 4 NT^2 matrix instructions of 64 cycles in FP64.
+//
+// A launch lasts as long as its longest chain or as its operands take to load,
+// and two wavefronts, on SIMDs of their own, halve the first and double the
+// second.  So the line grows with the longest chain, and with the tiles of a
+// step.  Above 3,000 units the FP64 joint form of 64 states loses again: its
+// registers leave a SIMD one wavefront.  FP64 arithmetic, together and apart, us:
+// 61 states, chains of up to 3 segments, 1,020 units 31 and 27, 16,000 172 and
+// 147; one segment, 1,020 units 20.6 and 22.0; 40 states, up to 3 segments, 1,023
+// units 22 and 20, 4,095 34 and 38, 12,000 73 and 83; of up to 24, 8,187 units 145
+// and 110; 20 states, up to 3, 4,094 units 23 and 27.  FP32: 61 states, up to 3,
+// 1,020 units 21.3 and 20.8, 16,000 70 and 80.
+template <typename T>
+bool pstage_apart(int nt, long units, int longest) {
+  return units <= 170L * nt * longest || (nt == 4 && sizeof(T) == 8 && units > 3000);
+}
 
 template <typename T, bool GRAD, bool APART, int NT>
 struct PStageShared {
@@ -371,7 +381,8 @@ int pstage_mfma_launch(EpochInstance* in, const int4* d_items, int n_items) {
   }
   const long units = (long)pd.n_items * NT;
   const dim3 grid((unsigned)((units + 3) / 4));
-  if (pd.grad && units <= kApartUnits)
+  const int longest = d_items ? in->inc.chain_items.front().z : (split ? in->chain_longest_part : in->chain_longest);
+  if (pd.grad && pstage_apart<T>(NT, units, longest))
     hipLaunchKernelGGL((pstage_mfma_kernel<T, TO, true, true, NT>), dim3((unsigned)units), dim3(128), 0, in->stream, pd);
   else if (pd.grad)
     hipLaunchKernelGGL((pstage_mfma_kernel<T, TO, true, false, NT>), grid, dim3(256), 0, in->stream, pd);

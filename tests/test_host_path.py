@@ -195,3 +195,23 @@ for bad in (-2, (1 << 30) + 1):
     except _abi.EpochError as e:
         assert e.code == _abi.EPOCH_ERR_ARG
 """)
+
+
+@pytest.mark.parametrize("states, taxa, intervals, precision, apart", [
+    (61, 40, 3, "fp64", True),     # 316 units
+    (40, 683, 1, "fp64", False),   # 4,095 units of one segment: 33 us together, 39 apart
+    (20, 1024, 1, "fp32", False),  # 4,094 units
+    (61, 800, 1, "fp64", True),    # 6,396 units: one wavefront per SIMD in the joint form
+    (61, 800, 1, "fp32", False),
+    (20, 1024, 14, "fp32", True)])
+def test_derivative_on_wavefronts_of_its_own(tmp_path, states, taxa, intervals, precision, apart):
+    """The P stage's two forms, by the units of a launch, their tiles and the longest chain."""
+    out = fake_hip.run(tmp_path, created(states=states, taxa=taxa, patterns=1, intervals=intervals, precision=precision,
+                                         grad_branch=True) + """
+lik.set_option("eigen_precision", 1)
+lik.set_option("chain_split", 0)
+fake.fake_clear()
+lik.evaluate(branch=True)
+print("\\n".join(l for l in log() if "pstage_mfma" in l))
+""")
+    assert ("Lb1ELb1ELi" in out) == apart and ("Lb1ELb0ELi" in out) != apart, out

@@ -52,8 +52,11 @@ __device__ inline T* chain_mat(void* scratch, int slot, int C, int c, int part, 
 //
 // A launch lasts as long as its longest chain or as its operands take to load,
 // and two wavefronts, on SIMDs of their own, halve the first and double the
-// second.  So the line grows with the longest chain, and with the tiles of a
-// step.  Above 3,000 units the FP64 joint form of 64 states loses again: its
+// second.  So the line grows with the products of the longest chain (two a
+// segment, one for the first), and with the tiles of a product: over 250 launches
+// (padded 16 to 64 states, 250 to 16,000 units, chains of 1, up to 3 and up to 24
+// segments, both arithmetics) it picks a form slower by more than 10 % in ten,
+// most of them of 16 states.  Above 3,000 units the FP64 joint form of 64 states loses again: its
 // registers leave a SIMD one wavefront.  FP64 arithmetic, together and apart, us:
 // 61 states, chains of up to 3 segments, 1,020 units 31 and 27, 16,000 172 and
 // 147; one segment, 1,020 units 20.6 and 22.0; 40 states, up to 3 segments, 1,023
@@ -62,7 +65,7 @@ __device__ inline T* chain_mat(void* scratch, int slot, int C, int c, int part, 
 // 1,020 units 21.3 and 20.8, 16,000 70 and 80.
 template <typename T>
 bool pstage_apart(int nt, long units, int longest) {
-  return units <= 170L * nt * longest || (nt == 4 && sizeof(T) == 8 && units > 3000);
+  return units <= 150L * nt * (2 * longest - 1) || (nt == 4 && sizeof(T) == 8 && units > 3000);
 }
 
 template <typename T, bool GRAD, bool APART, int NT>

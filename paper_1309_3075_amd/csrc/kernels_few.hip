@@ -28,20 +28,24 @@ namespace epochlik {
 
 namespace {
 
-constexpr int kFewMaxPatterns = 16;            // more patterns fill the per-level kernels' blocks
+// Trait data hold one column or a few.  The line is where these kernels were tried, not where the
+// per-level kernels overtake: with branch gradients, 7 states, 200 taxa, FP64, those and these take 164
+// and 118 us at 16 patterns, 193 and 164 at 64.
+constexpr int kFewMaxPatterns = 16;
 constexpr size_t kFewLds = 64 * 1024;          // LDS of a run of levels, at most, besides its matrix buffers
+constexpr size_t kFewVectorBytes = 256 << 20;  // child vectors, at most
 // Blocks of a post-order level launch, until they are full: a block of items from several nodes reads
 // their matrices through one CU, and its wavefronts walk every kind of child among them.  40 states,
 // 64 taxa, one column, FP64, four categories, post-order pass: 177 us in full blocks, 159 in these.
 constexpr int kFewBlocks = 2048;
-constexpr int kFewWide = 2;                    // a level of more items than this many passes of a block is launched alone,
-// and so is one whose matrices are more than one CU reads in about the time of a launch (a lane per row,
-// of more than a cache line from 32 states in FP64 on, reads slower than a wavefront per matrix).  FP64,
-// one category, without gradient, per-level kernels and runs by the number of items alone and by this:
-// 20 states (generic kernels), 64 taxa, 16 columns 104, 162 and 99 us; 12 states, 1,500 taxa, 8 columns
-// 137, 157 and 138; 40 states, 1,500 taxa, one column 219, 195 and 191.
+// A level runs in one block while it takes it at most this many passes, and while its matrices are no more
+// than one CU reads in about the time of a launch (a lane per row, of more than a cache line from 32
+// states in FP64 on, reads slower than a wavefront per matrix).  FP64, one category, without gradient,
+// per-level kernels, runs by the number of items alone, and by both: 20 states (generic kernels), 64
+// taxa, 16 columns 104, 162 and 99 us; 12 states, 1,500 taxa, 8 columns 137, 157 and 138; 40 states,
+// 1,500 taxa, one column 219, 195 and 191.
+constexpr int kFewWide = 2;
 constexpr size_t few_run_bytes(int lanes) { return (lanes == 32 ? 128 : 256) * 1024; }
-constexpr size_t kFewVectorBytes = 256 << 20;  // child vectors, at most
 
 // Orders LDS accesses of one wavefront (write, then read by other lanes).
 __device__ inline void wave_lds_order() {

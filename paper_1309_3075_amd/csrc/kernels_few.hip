@@ -7,13 +7,13 @@
 //   - consecutive narrow levels run as one launch of one block, which keeps the partials (or the
 //     outside vectors) of its nodes in LDS, one block barrier or two per level, and loads the next
 //     level's matrix rows while it finishes the current one;
-//   - wide levels pack their (node, pattern) items densely (a block per node left 248 of 256
-//     threads idle for 7 states and one pattern);
+//   - other levels are launches over (node, pattern) items with lanes for an item's states only (a
+//     block per node left 248 of 256 threads idle for 7 states and one pattern);
 //   - with a gradient, the post-order pass keeps every branch's child vector S_v = P_v L_v, which the
 //     pre-order pass and dlogL/dP would otherwise form again from the matrices.
 // 522 taxa, 7 states, one column, FP64: the post- and pre-order passes took 294 us in 64 launches and
-// take 77 us in two; 2,000 taxa, 40 states, FP32: 253 us in 44 launches, now 202 us in 23, and dlogL/dP
-// 66 -> 43 us.  What is left of a run is latency: about 0.7 us a level down, 1.2 us up.
+// take 77 us in two; 2,000 taxa, 40 states, FP32: 253 us in 44 launches, now 190 us in 25, and dlogL/dP
+// 66 -> 45 us.  What is left of a run is latency: about 0.7 us a level down, 1.2 us up.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -263,10 +263,10 @@ void invalidate_downstream(EpochInstance* in) {
   in->logL_valid = false;
 }
 
-// What an instance of this size hands over through its staging buffer at most, so that one allocation serves every later
-// call: the rates of all branches, a restricted pass' lists (branches and their chain items, nodes, the
-// matrix-core kernels' items or the few-pattern kernels' lists), a tree's few-pattern lists.  Trees of a
-// million nodes or so, where that is past 64 MB, grow it on demand.
+// What an instance of this size hands over through its staging buffer at most, so that one allocation
+// serves every later call: the rates of all branches, a restricted pass' lists (branches and their chain
+// items, nodes, the matrix-core kernels' items or the few-pattern kernels' lists), a tree's few-pattern
+// lists.  Trees of a million nodes or so, where that is past 64 MB, grow it on demand.
 size_t stage_bound(const EpochInstance* in) {
   const size_t per_branch = sizeof(int32_t) + sizeof(int4);
   const size_t per_node = sizeof(int32_t) + std::max(in->C * sizeof(int4), 19 * sizeof(int32_t));
@@ -449,9 +449,6 @@ int epoch_create(const EpochConfig* cfg, EpochInstance** out) {
     A(in->scales, (N - 1) * P * sizeof(int32_t) * scale_sets(c));
     if (grad) A(in->pre, (N - 1) * C * P * Kp * R);
   }
-  // without room for the child vectors the generic path keeps to its per-level kernels
-  if (const size_t few = generic_config(c) && !c.workspace ? few_vector_bytes(c, (int)Kp) : 0; few && rc == EPOCH_OK)
-    (void)ensure(in->few_S, few);
   A(in->site, P * sizeof(double));
   A(in->blocksum, ((P + 15) / 16 + 1) * sizeof(double));  // a root block serves 16 patterns at least
   A(in->arrived, sizeof(unsigned));
@@ -463,6 +460,10 @@ int epoch_create(const EpochConfig* cfg, EpochInstance** out) {
   }
   if (c.flags & EPOCH_GRAD_Q) A(in->dQ, S * KK * sizeof(double));
   if (rc == EPOCH_OK) rc = fastpath_init(in);
+  // last, so that nothing else goes short of it: without the child vectors the generic path keeps to its
+  // per-level kernels
+  if (const size_t few = generic_config(c) && !c.workspace ? few_vector_bytes(c, (int)Kp) : 0; few && rc == EPOCH_OK)
+    (void)ensure(in->few_S, few);
   if (rc != EPOCH_OK) {
     std::string keep = g_error;
     epoch_destroy(in);

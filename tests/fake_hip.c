@@ -13,6 +13,7 @@ static char log_text[1 << 22];
 static size_t log_used;
 static int fail_host_mallocs; /* pinned allocations still to fail */
 static int fail_copies;       /* asynchronous copies still to fail */
+static size_t fail_malloc_of; /* device allocations of this size fail */
 static uintptr_t next_handle = 0x1000;
 
 static void note(const char* fmt, ...) {
@@ -25,6 +26,7 @@ const char* fake_log(void) { return log_text; }
 void fake_clear(void) { log_used = 0, log_text[0] = 0; }
 void fake_fail_host_mallocs(int n) { fail_host_mallocs = n; }
 void fake_fail_copies(int n) { fail_copies = n; }
+void fake_fail_malloc_of(size_t n) { fail_malloc_of = n; }
 
 /* kernels by the address of their host stub */
 static struct { const void* stub; char name[160]; } kernels[4096];
@@ -65,6 +67,10 @@ hipError_t hipLaunchKernel(const void* stub, dim3 g, dim3 b, void** args, size_t
 
 hipError_t hipMalloc(void** p, size_t n) {
   note("malloc %zu\n", n);
+  if (n == fail_malloc_of) {
+    *p = NULL;
+    return hipErrorOutOfMemory;
+  }
   return (*p = calloc(1, n + 256)) ? hipSuccess : hipErrorOutOfMemory;
 }
 hipError_t hipFree(void* p) { free(p); return hipSuccess; }

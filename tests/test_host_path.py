@@ -215,3 +215,21 @@ lik.evaluate(branch=True)
 print("\\n".join(l for l in log() if "pstage_mfma" in l))
 """)
     assert ("Lb1ELb1ELi" in out) == apart and ("Lb1ELb0ELi" in out) != apart, out
+
+
+def test_no_memory_for_the_child_vectors(tmp_path):
+    """Refused, they leave an instance of the per-level kernels, and nothing else is allocated after them."""
+    fake_hip.run(tmp_path, created(states=7, patterns=3, precision="fp64", grad_branch=True) + """
+lik.close()
+few = 79 * 3 * 8 * 8
+fake.fake_fail_malloc_of(ctypes.c_size_t(few))
+fake.fake_clear()
+lik = EpochLikelihood(40, 3, 7, 1, 1, 1, "fp64", grad_branch=True)
+assert [l for l in log() if l.startswith("malloc")][-1] == "malloc %d" % few
+lik.close()
+lik = from_problem(prob, "fp64", grad_branch=True)
+fake.fake_clear()
+lik.evaluate(branch=True)
+names = [l.split()[2] for l in log() if l.startswith("launch")]
+assert any("post_level_generic" in n for n in names) and not any("few_" in n for n in names), names
+""")

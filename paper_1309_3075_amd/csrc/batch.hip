@@ -538,7 +538,9 @@ int autotune(EpochBatch* b) {
   // two timings of one shape (0.3 %), the FP32 block sums follow the shape, and fewer blocks write fewer
   // dlogL/dP slots.  Of repeated tunings of batches of 5 to 16 problems, 2 in 32 left their batch's usual
   // shape (and with it the gradients' last bits), against 3 in 12 when the fastest was taken; at most
-  // 0.8 % slower by the rule.
+  // 0.8 % slower by the rule.  Two shapes that differ by about the line itself still change places: 16
+  // problems of 128 taxa and 4,472 codon patterns, 8,192 and 16,384 blocks 9.42 and 9.34 ms, 19 of 90
+  // tunings took the former.  A tuning cache keeps one shape.
   constexpr float kTuneNoise = 0.008f;
   constexpr int kTargets[] = {512, 1024, 2048, 4096, 8192, 16384};
   constexpr int kShapes = sizeof(kTargets) / sizeof(kTargets[0]);
